@@ -165,10 +165,10 @@ typedef enum ff_plan_query_key {
                                        input side at once; more when the support is dense) */
     FF_Q_GEN_TILE_TOKENS_F32 = 11,  /* most tokens per generic-kernel tile with those chunks, fp32 */
     FF_Q_GEN_TILE_TOKENS_BF16 = 12, /* the same, bf16 activations */
-    FF_Q_GEN_TOKEN_GROUPS = 13      /* 1 if bf16 calls on the generic kernels keep four tokens of
-                                       a coefficient together in their tiles (frames whose blocks
-                                       are applied directly, up to 128 wide, or in one radix-4
-                                       stage); their tiles are then a multiple of four tokens */
+    FF_Q_GEN_TOKEN_GROUPS = 13      /* 1 if bf16 calls keep several tokens of a coefficient together
+                                       (frames whose blocks are applied directly, up to 128 wide, or
+                                       in one radix-4 stage); the reported bf16 tile is then a
+                                       multiple of four tokens */
 } ff_plan_query_key;
 ff_status ff_plan_query(const ff_plan* p, int key, int64_t* value);
 
@@ -210,15 +210,17 @@ ff_status ff_adapter_bwd(const ff_plan* p, int64_t T, int act, const void* X, in
  * device memory or use a plan's workspace (code under HIP graph capture, tight
  * serving loops, harnesses that forbid allocation).  Arguments, results
  * (bitwise those of ff_adapter_bwd) and errors are those of ff_adapter_bwd;
- * the backward's scratch (the coefficients in its own order and the dC partial
- * sums) lives instead in a 32 MiB array that the library's code object holds
- * on every device it runs on, until the process ends.  Nothing is allocated
+ * the backward's scratch (the coefficients in its own order, the dC partial
+ * sums and, where the coefficients of a side pass through memory, those of some
+ * tokens at a time) lives instead in an array that the library's code object
+ * holds on every device it runs on, until the process ends.  Nothing is allocated
  * and no memset node is issued: the scratch is cleared by a fill kernel where
  * it must start at zero.
- *   Limit: a call needing more than 32 MiB of scratch returns FF_EINVAL and
- *   writes nothing (the q_proj layer, 4096 x 4096 with 10,000 coefficients,
- *   needs about 13 MB at 4096 bf16 tokens); split the tokens over several
- *   calls with accumulate_dc = 1.
+ *   Limit: a call needing more than 32 MiB of coefficients and partial sums
+ *   (a row of them per tile, at most one per compute unit on the generic
+ *   kernels) returns FF_EINVAL and writes nothing (the q_proj layer, 4096 x 4096
+ *   with 10,000 coefficients, needs about 13 MB at 4096 bf16 tokens); split the
+ *   tokens over several calls with accumulate_dc = 1.
  *   All calls on one device share that array: calls that overlap in time on
  *   one device (different streams, threads or processes' streams without an
  *   ordering between them) race and give undefined results.

@@ -15,15 +15,17 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 BUILD_DIR = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libframeft.so")
-# (source, object name, extra flags): the generic kernels are instantiated by one source compiled
-# once per direction and activation type, so that their long compiles run in parallel
+# (source, object name, extra flags): the generic and slab kernels are instantiated by one source
+# each, compiled once per variant, so that their long compiles run in parallel
 SOURCES = [("capi.cpp", "capi.cpp.o", []), ("framegen.cpp", "framegen.cpp.o", []), ("plan.cpp", "plan.cpp.o", []),
            ("kernels.hip", "kernels.hip.o", []), ("kernels_w128.hip", "kernels_w128.hip.o", []),
            ("optim.hip", "optim.hip.o", []), ("group.cpp", "group.cpp.o", []),
-           ("lift.hip", "lift.hip.o", [])] + [
+           ("lift.hip", "lift.hip.o", []), ("slab.hip", "slab.hip.o", [])] + [
+    ("slab_inst.hip", f"slab_bf16_{r}.o", ["-DSLAB_BF16=1", f"-DSLAB_RADIX={int(r == 'radix')}"])
+    for r in ("direct", "radix")] + [
     ("gen_inst.hip", f"gen_{d}_{t}{'_ms' if ms else ''}.o",
      [f"-DGEN_BWD={int(d == 'bwd')}", f"-DGEN_BF16={int(t == 'bf16')}", f"-DGEN_MS={ms}"])
-    for d in ("bwd", "fwd") for t in ("bf16", "f32") for ms in (0, 1)]
+    for d in ("bwd", "fwd") for t, ms in (("bf16", 1), ("f32", 0), ("f32", 1))]
 
 ARCH = "gfx950"
 COMMON = [

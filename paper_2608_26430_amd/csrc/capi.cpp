@@ -106,8 +106,11 @@ ff_status check_bwd(const ff_plan* p, int64_t T, int act, const void* X, int64_t
 // has its own copy of the array at its own address, taken once per device with
 // hipGetSymbolAddress; host code uses that address only, never the array's name.  Calls on one
 // device share the array, so overlapping calls on one device race.
+// Calls are accepted up to kScratchBytes (the generic kernels' need); the slab kernels split a call
+// so that its entries, dC partial rows and at least one source slab fit kScratchArray.
 constexpr size_t kScratchBytes = (size_t)32 << 20;
-static __device__ __align__(256) unsigned char scratch[kScratchBytes];
+constexpr size_t kScratchArray = (size_t)96 << 20;
+static __device__ __align__(256) unsigned char scratch[kScratchArray];
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
 void* g_scratch_ptr[kMaxDevices] = {};
@@ -230,7 +233,7 @@ ff_status ff_adapter_bwd_noalloc(const ff_plan* p, int64_t T, int act, const voi
                     "scratch (use fewer tokens per call)", need, kScratchBytes);
   void* base = nullptr;
   if ((st = scratch_address(p->device, &base)) != FF_OK) return st;
-  const ff::BwdScratch ws{static_cast<float*>(base), kScratchBytes / sizeof(float)};
+  const ff::BwdScratch ws{static_cast<float*>(base), kScratchArray / sizeof(float)};
   if (p->lifted)
     return launched(ff::launch_bwd_lifted(p, act == FF_BF16, (int)T, X, ldx, G, ldg, c_vals, scale, beta_dx, dX, lddx,
                                           want_dx, accumulate_dc, dC, want_dc, (hipStream_t)stream, &ws),

@@ -63,6 +63,12 @@ struct FrameDev {
   int nst;
   int ncol;
   const float2* twk;
+  // The same matrices for the slab kernels, whose contraction windows are clamped to the column:
+  // lane (q, L) of step ks holds elements min(KS ks + VL q, W2 - VL) .. + VL - 1 (KS, VL as above),
+  // those below KS ks + VL q having zero weight (an earlier window holds them).  Frames in one
+  // radix-4 stage have one matrix per column a', [4][MT][KT][64], with the stage's twiddles folded in.
+  const void* wa16;
+  const void* ws16;
 };
 
 // The lift L of a frame P = L^T Pv (every frame the library builds has one).  Pv is the block-
@@ -155,6 +161,56 @@ struct FastPlanDev {
   int bwd16 = 0;   // the backward runs 16-token tiles (slot words address 32-byte rows)
 };
 
+// Streams of the slab kernels (slab_kernels.h), one per direction.  Destination rows (coefficient
+// positions of the destination side) are taken in groups of blocks; a group's rows with entries are
+// sorted by entry count into bundles of 16, a bundle being as many steps of 16 entries as its
+// longest row (shorter rows padded with entries that read the source slab's row of zeros).  Each of
+// a workgroup's waves walks a contiguous run of the group's steps, a multiple of four; entry l of step
+// k of a batch of four is element 64 batch + 4 l + k.  Entry word: source position |
+// row in the group << kSlabDstShift | kRowLast at a bundle's last step.
+constexpr int kSlabRowBytes = 128;      // one coefficient of one slab: 64 bf16 or 32 fp32 tokens
+constexpr int kSlabWaves = 4;
+constexpr int kSlabThreads = 64 * kSlabWaves;
+constexpr int kSlabPadSteps = 16;       // readable steps past a stream's end
+constexpr int kSlabRows = 128;          // destination rows a group of narrow blocks aims at
+constexpr uint32_t kSlabSrcMask = 0x1FFFFu;
+constexpr int kSlabDstShift = 17;
+constexpr uint32_t kSlabDstMask = 0x3FFu;
+// Bytes of workspace a plan spends on slabs (all its adapters together): calls that need more are
+// split.  Half the 256 MB last-level cache, so that the second pass finds the first one's
+// results there beside the activations streaming through.
+constexpr size_t kSlabPoolBytes = (size_t)128 << 20;
+// dC partial rows of one adapter: at most this many, and at most kSlabPartialBytes.
+constexpr int kSlabMaxRows = 256;
+constexpr size_t kSlabPartialBytes = (size_t)40 << 20;
+struct SlabStream {
+  const uint32_t* word;         // [16 (steps + kSlabPadSteps)]
+  const int* coef;              // coefficient slot of the entry, -1 for padding
+  const int* wstep;             // [groups][kSlabWaves + 1]: first step of each wave
+  const int* zptr;              // [groups + 1] into zrow
+  const unsigned short* zrow;   // rows of the group without entries
+  int steps;
+  int nb, ngroups;              // blocks per group, groups of the destination side
+};
+struct SlabPlanDev {
+  int enabled = 0;
+  SlabStream fwd{}, bwd{};
+  unsigned char* pool = nullptr;   // slabs of one side
+  size_t pool_bytes = 0;
+  uint2* ent = nullptr;            // [batch][ent_adapter]: entry words with a call's coefficients
+  long ent_adapter = 0;
+  int rows = 0;                    // dC partial rows per adapter
+};
+// Blocks per group of a side.
+inline int slab_group_blocks(const FrameDev& f) {
+  const int nb = kSlabRows / f.W;
+  return nb < 1 ? 1 : nb < f.nblk ? nb : f.nblk;
+}
+// Frames the slab kernels take: blocks applied directly or in one radix-4 stage.
+inline bool slab_frame(const FrameDev& f) {
+  return (f.radix == 1 && f.nst == 0 && f.W <= 128) || (f.radix == 4 && f.nst == 1 && f.W2 <= 128);
+}
+
 // One adapter's view of its plan inside a plan group (ff_plan_group): the tables and the
 // workspace (batch slot 0 of the plan's own) that the group kernels read per adapter.
 struct FastDesc {   // fused 128-wide kernels
@@ -172,6 +228,12 @@ struct FastDesc {   // fused 128-wide kernels
   float* partial;   // dC partials, [tile][bwd_slots + 256]
   int npad, nbpad, slots, coef_slots;
   int bwd16;        // this plan's backward runs 16-token tiles (else 8)
+};
+struct SlabDesc {   // slab kernels
+  SlabStream fwd, bwd;
+  unsigned char* ws;
+  uint2* ent;
+  float* partial;
 };
 struct GenDesc {    // generic kernels
   GenStream fwd, bwd;
@@ -217,8 +279,9 @@ struct ff_plan {
   int gen_ldt_in[2] = {0, 0};      // LDS token stride of the input-side chunk tile
   int gen_tile_tokens[2] = {0, 0};
   size_t gen_lds_bytes[2] = {0, 0};
-  // bf16 generic kernels on token-grouped tiles (four tokens per coefficient; tiles a multiple of
-  // four tokens): frames applied directly (blocks up to 128 wide) or in one radix-4 stage, no lift.
+  // bf16 tile geometry in whole groups of four tokens (frames applied directly or in one radix-4
+  // stage, no lift); those calls run in the slab kernels, and the geometry is what the queries report
+  // and what bounds ff_adapter_bwd_noalloc.
   int gen_g4 = 0;
   int gen_wgs = 1;                 // compute units: resident workgroups of the generic kernels
   int gen_rows = 1;                // dC partial rows per adapter = most workgroups of the generic backward
@@ -241,6 +304,7 @@ struct ff_plan {
   void* dev_mem = nullptr;
   ff::PlanDev dev{};
   ff::FastPlanDev fast{};
+  ff::SlabPlanDev slab{};
   std::vector<int64_t> user_order;  // user index of each coefficient slot, -1 for padding
 };
 
@@ -264,6 +328,10 @@ struct ff_plan_group {
   void* dev_mem = nullptr;
   const ff::FastDesc* fast = nullptr;   // [count], device
   const ff::GenDesc* gen = nullptr;     // [count], device
+  // slab kernels: smallest pool and row count, longest streams
+  size_t slab_pool = 0;
+  int slab_rows = 0, max_slab_fwd = 0, max_slab_bwd = 0;   // (entries, padding steps included)
+  const ff::SlabDesc* slab = nullptr;   // [count], device
 };
 
 namespace ff {
@@ -329,6 +397,27 @@ hipError_t launch_bwd_lifted(const ff_plan* p, int bf16, int T, const void* X, i
                              const BwdScratch* ws = nullptr);
 hipError_t launch_merge_lifted(const ff_plan* p, const float* c, float scale, int w_bf16, float beta, void* W,
                                int64_t ldw, hipStream_t s);
+// Slab kernels (slab.hip): the calls of plans with slab.enabled, arguments as for launch_fwd / launch_bwd and
+// the group calls.
+hipError_t configure_slab();
+hipError_t launch_fwd_slab(const ff_plan* p, int bf16, int count, int T, ActPtrs X, int64_t ldx, const float* c,
+                           const float* const* cs, float scale, float beta, ActPtrs Y, int64_t ldy, hipStream_t s);
+hipError_t launch_bwd_slab(const ff_plan* p, int bf16, int count, int T, ActPtrs X, int64_t ldx, ActPtrs G,
+                           int64_t ldg, const float* c, const float* const* cs, float scale, float beta_dx, ActPtrs dX,
+                           int64_t lddx, bool want_dx, int accumulate_dc, float* dC, float* const* dCs, bool want_dc,
+                           hipStream_t s, const BwdScratch* ws);
+hipError_t launch_fwd_group_slab(const ff_plan_group* g, int bf16, int T, const int* tokens, const void* const* X,
+                                 int64_t ldx, const float* const* cs, float scale, float beta, void* const* Y,
+                                 int64_t ldy, hipStream_t s);
+hipError_t launch_bwd_group_slab(const ff_plan_group* g, int bf16, int T, const int* tokens, const void* const* X,
+                                 int64_t ldx, const void* const* G, int64_t ldg, const float* const* cs, float scale,
+                                 float beta_dx, void* const* dX, int64_t lddx, bool want_dx, int accumulate_dc,
+                                 float* const* dCs, bool want_dc, hipStream_t s);
+// dC from partial rows (kernels.hip): partial [batch][nrows][len] summed over the rows in order and
+// scattered to the slots coef[element] (-1: none); the slots in pad (npad of them) are zeroed unless
+// accumulating.
+hipError_t launch_dc_reduce(const float* partial, long nrows, int len, const int* coef, const int* pad, int npad,
+                            float scale, int accumulate, float* dC, float* const* dCs, int count, hipStream_t s);
 // Generic-kernel tile size of a call (kernels.hip), shared by single, batched and group calls.
 int call_tile_tokens(int tt, long T, int count, int slots, bool g4);
 

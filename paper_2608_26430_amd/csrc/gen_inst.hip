@@ -1,6 +1,7 @@
 // Instantiation of one generic kernel (fwd_kernel or bwd_kernel, GEN_BWD) for one activation type
 // (GEN_BF16), and for frames applied in several radix-4 stages or the others (GEN_MS): the build
-// compiles this file eight times with those macros set, in parallel.
+// compiles this file once per combination in use, in parallel.  bf16 has the multi-stage kernels
+// only (its other frames run in the slab kernels).
 #include "gen_kernels.h"
 
 #if !defined(GEN_BWD) || !defined(GEN_BF16) || !defined(GEN_MS)
@@ -41,6 +42,14 @@ namespace gen {
 hipError_t GEN_LAUNCH_MS(const GEN_ARGS& a, dim3 grid, size_t lds, hipStream_t s);
 hipError_t GEN_CONFIGURE_MS();
 
+#if GEN_BF16
+hipError_t GEN_LAUNCH(const GEN_ARGS& a, dim3 grid, size_t lds, hipStream_t s) {
+  if (a.fin.nst < 2 && a.fout.nst < 2) return hipErrorInvalidValue;   // (not reached: the plan takes the slab kernels)
+  return GEN_LAUNCH_MS(a, grid, lds, s);
+}
+hipError_t GEN_CONFIGURE() { return GEN_CONFIGURE_MS(); }
+#endif
+
 #if GEN_MS
 hipError_t GEN_LAUNCH_MS(const GEN_ARGS& a, dim3 grid, size_t lds, hipStream_t s) {
   hipLaunchKernelGGL((GEN_KERNEL<GEN_BF16 != 0, false, true>), grid, dim3(kFusedThreads), lds, s, a);
@@ -54,33 +63,17 @@ hipError_t GEN_CONFIGURE_MS() {
 #else
 hipError_t GEN_LAUNCH(const GEN_ARGS& a, dim3 grid, size_t lds, hipStream_t s) {
   if (a.fin.nst >= 2 || a.fout.nst >= 2) return GEN_LAUNCH_MS(a, grid, lds, s);
-#if GEN_BF16
-  if (a.g4) {   // token-grouped tiles (the plan sets g4 only for frames in at most one radix-4 stage)
-    if (a.nch > 1)
-      hipLaunchKernelGGL((GEN_KERNEL<true, true, false, true>), grid, dim3(kFusedThreads), lds, s, a);
-    else
-      hipLaunchKernelGGL((GEN_KERNEL<true, false, false, true>), grid, dim3(kFusedThreads), lds, s, a);
-    return hipGetLastError();
-  }
-#endif
   if (a.nch > 1)
-    hipLaunchKernelGGL((GEN_KERNEL<GEN_BF16 != 0, true>), grid, dim3(kFusedThreads), lds, s, a);
+    hipLaunchKernelGGL((GEN_KERNEL<false, true>), grid, dim3(kFusedThreads), lds, s, a);
   else
-    hipLaunchKernelGGL((GEN_KERNEL<GEN_BF16 != 0, false>), grid, dim3(kFusedThreads), lds, s, a);
+    hipLaunchKernelGGL((GEN_KERNEL<false, false>), grid, dim3(kFusedThreads), lds, s, a);
   return hipGetLastError();
 }
 
 hipError_t GEN_CONFIGURE() {
   hipError_t e = GEN_CONFIGURE_MS();
-  for (const void* fn : {reinterpret_cast<const void*>(&GEN_KERNEL<GEN_BF16 != 0, true>),
-                         reinterpret_cast<const void*>(&GEN_KERNEL<GEN_BF16 != 0, false>),
-#if GEN_BF16
-                         reinterpret_cast<const void*>(&GEN_KERNEL<true, false, false, true>),
-                         reinterpret_cast<const void*>(&GEN_KERNEL<true, true, false, true>)
-#else
-                         reinterpret_cast<const void*>(&GEN_KERNEL<false, false>)
-#endif
-       }) {
+  for (const void* fn : {reinterpret_cast<const void*>(&GEN_KERNEL<false, true>),
+                         reinterpret_cast<const void*>(&GEN_KERNEL<false, false>)}) {
     const hipError_t r = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLdsBytes);
     if (r != hipSuccess) e = r;
   }

@@ -61,6 +61,8 @@ ff_status ff_plan_group_create(int64_t count, const ff_plan* const* plans, ff_pl
     if (p->device != ref->device) return ff::fail(FF_EINVAL, "plan %lld is on another device", (long long)i);
     if (p->fast.enabled != ref->fast.enabled)
       return ff::fail(FF_EUNSUPPORTED, "plan %lld takes another kernel path than plan 0", (long long)i);
+    if (p->slab.enabled != ref->slab.enabled)
+      return ff::fail(FF_EUNSUPPORTED, "plan %lld takes another kernel path than plan 0", (long long)i);
     bool same = p->gen_nch == ref->gen_nch && p->gen_g4 == ref->gen_g4 && p->dev.fwd_by_pos == ref->dev.fwd_by_pos;
     for (int k = 0; k < 2; ++k)
       same = same && p->gen_tile_tokens[k] == ref->gen_tile_tokens[k] && p->gen_ldt_in[k] == ref->gen_ldt_in[k] &&
@@ -78,6 +80,9 @@ ff_status ff_plan_group_create(int64_t count, const ff_plan* const* plans, ff_pl
   g->min_gen_rows = ref->gen_rows;
   std::vector<ff::FastDesc> fast((size_t)count);
   std::vector<ff::GenDesc> gen((size_t)count);
+  std::vector<ff::SlabDesc> slab((size_t)count);
+  g->slab_pool = ref->slab.pool_bytes;
+  g->slab_rows = ref->slab.rows;
   for (int64_t i = 0; i < count; ++i) {
     const ff_plan* p = plans[i];
     g->max_tokens = std::min(g->max_tokens, p->max_tokens);
@@ -90,6 +95,12 @@ ff_status ff_plan_group_create(int64_t count, const ff_plan* const* plans, ff_pl
     g->fast8 |= f.bwd16 ? 0 : 1;
     const ff::PlanDev& d = p->dev;
     gen[i] = ff::GenDesc{d.fwd, d.bwd, d.coef_pad, d.c_fwd, d.c_bwd, p->partial, d.fwd_by_pos, d.ncoef_pad};
+    const ff::SlabPlanDev& sp = p->slab;
+    slab[i] = ff::SlabDesc{sp.fwd, sp.bwd, sp.pool, sp.ent, p->partial};
+    g->slab_pool = std::min(g->slab_pool, sp.pool_bytes);
+    g->slab_rows = std::min(g->slab_rows, sp.rows);
+    g->max_slab_fwd = std::max(g->max_slab_fwd, 16 * (sp.fwd.steps + ff::kSlabPadSteps));
+    g->max_slab_bwd = std::max(g->max_slab_bwd, 16 * (sp.bwd.steps + ff::kSlabPadSteps));
     g->max_fast_items = std::max(g->max_fast_items, f.coef_slots + f.nbpad);
     g->max_fast_slots = std::max(g->max_fast_slots, f.bwd_slots);
     g->max_fast_npad = std::max(g->max_fast_npad, f.npad);
@@ -99,20 +110,23 @@ ff_status ff_plan_group_create(int64_t count, const ff_plan* const* plans, ff_pl
     g->any_fwd_gather |= d.fwd_by_pos ? 0 : 1;
   }
   const size_t fb = fast.size() * sizeof(ff::FastDesc), gb = gen.size() * sizeof(ff::GenDesc);
-  const size_t goff = (fb + 255) & ~(size_t)255;
+  const size_t sb = slab.size() * sizeof(ff::SlabDesc);
+  const size_t goff = (fb + 255) & ~(size_t)255, soff = (goff + gb + 255) & ~(size_t)255;
   void* mem = nullptr;
-  if (hipMalloc(&mem, goff + gb) != hipSuccess) {
+  if (hipMalloc(&mem, soff + sb) != hipSuccess) {
     (void)hipGetLastError();
     return ff::fail(FF_ENOMEM, "hipMalloc of the group's descriptors failed");
   }
   if (hipMemcpy(mem, fast.data(), fb, hipMemcpyHostToDevice) != hipSuccess ||
-      hipMemcpy((char*)mem + goff, gen.data(), gb, hipMemcpyHostToDevice) != hipSuccess) {
+      hipMemcpy((char*)mem + goff, gen.data(), gb, hipMemcpyHostToDevice) != hipSuccess ||
+      hipMemcpy((char*)mem + soff, slab.data(), sb, hipMemcpyHostToDevice) != hipSuccess) {
     (void)hipFree(mem);
     return ff::fail(FF_EDEVICE, "copying the group's descriptors failed");
   }
   g->dev_mem = mem;
   g->fast = static_cast<const ff::FastDesc*>(mem);
   g->gen = reinterpret_cast<const ff::GenDesc*>((char*)mem + goff);
+  g->slab = reinterpret_cast<const ff::SlabDesc*>((char*)mem + soff);
   *out = g.release();
   return FF_OK;
 }

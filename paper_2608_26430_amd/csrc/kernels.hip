@@ -12,7 +12,7 @@
 // LDS, where one tile's coefficient vectors are kept whole because the
 // support of C is uniformly random.
 //
-// Kernels:
+// Generic kernels (fp32 activations, and frames in several radix-4 stages):
 //   fwd_kernel    x -> z = P_in^T x (LDS) -> v = C z (LDS) -> y = beta y + s P_out v
 //   bwd_kernel    g -> u = P_out^T g (LDS), x -> z = P_in^T x (LDS)
 //                 -> dC partial per tile: sum_t u[a_e] z[b_e]
@@ -426,7 +426,7 @@ hipError_t configure_kernels() {
   static hipError_t once = [] {
     hipError_t e = hipSuccess;
     for (const hipError_t r : {gen::configure_fwd_bf16(), gen::configure_fwd_f32(), gen::configure_bwd_bf16(),
-                               gen::configure_bwd_f32()})
+                               gen::configure_bwd_f32(), configure_slab()})
       if (r != hipSuccess) e = r;
     return e;
   }();
@@ -445,7 +445,8 @@ hipError_t launch_gather(const float* c, const float* const* cs, const int* idx,
 // workgroup per CU, so tiles go in rounds of `slots` and a call costs about rounds x (token rows
 // its sparse walks read per table row + a fixed part worth kTileOverhead of them).  Of the tile
 // sizes up to tt (the plan's LDS limit) the cheapest is taken, the larger one on ties (fewer
-// passes over the tables).  Token-grouped tiles (g4) read whole groups of four tokens.
+// passes over the tables).  g4 counts whole groups of four tokens: the tiles that bf16 calls once took,
+// which still bound what ff_adapter_bwd_noalloc accepts.
 constexpr int kTileOverhead = 2;
 
 int call_tile_tokens(int tt, long T, int count, int slots, bool g4) {
@@ -462,10 +463,21 @@ int call_tile_tokens(int tt, long T, int count, int slots, bool g4) {
   return best;
 }
 
+hipError_t launch_dc_reduce(const float* partial, long nrows, int len, const int* coef, const int* pad, int npad,
+                            float scale, int accumulate, float* dC, float* const* dCs, int count, hipStream_t s) {
+  const int nmain = (len + 63) / 64, npadb = (npad + 64 * kDcWaves - 1) / (64 * kDcWaves);
+  if (nmain + npadb > 0)
+    hipLaunchKernelGGL(dc_reduce, dim3((unsigned)(nmain + npadb), (unsigned)count), dim3(64 * kDcWaves), 0, s, partial,
+                       nrows, len, coef, pad, npad, scale, accumulate, dC, dCs);
+  return hipGetLastError();
+}
+
 hipError_t launch_fwd(const ff_plan* p, int bf16, int count, int T, ActPtrs X, int64_t ldx, const float* c,
                       const float* const* cs, float scale, float beta, ActPtrs Y, int64_t ldy, float* c_saved,
                       hipStream_t s) {
   if (bf16 && p->fast.enabled) return launch_fwd128(p, count, T, X, ldx, c, cs, scale, beta, Y, ldy, c_saved, s);
+  if (bf16 && p->slab.enabled)
+    return launch_fwd_slab(p, bf16, count, T, X, ldx, c, cs, scale, beta, Y, ldy, s);
   FwdArgs a{};
   a.fin = p->fin->dev;
   a.fout = p->fout->dev;
@@ -474,7 +486,6 @@ hipError_t launch_fwd(const ff_plan* p, int bf16, int count, int T, ActPtrs X, i
   a.ldt_in = p->gen_ldt_in[bf16];
   a.ldt_out = p->ldt_out[bf16];
   a.nch = p->gen_nch;
-  a.g4 = bf16 ? p->gen_g4 : 0;
   for (int i = 0; i <= p->gen_nch; ++i) a.chunk_blk[i] = p->gen_chunk_blk[i];
   a.ldb_in = p->ldb_in;
   a.ldb_out = p->ldb_out;
@@ -530,6 +541,9 @@ hipError_t launch_bwd(const ff_plan* p, int bf16, int count, int T, ActPtrs X, i
     return launch_bwd128(p, count, T, X, ldx, G, ldg, c, cs, scale, beta_dx, dX, lddx, want_dx, accumulate_dc, dC, dCs,
                          want_dc, c_saved, s, ws);
   if (ws && count != 1) return hipErrorInvalidValue;   // a caller's scratch serves one adapter
+  if (bf16 && p->slab.enabled)
+    return launch_bwd_slab(p, bf16, count, T, X, ldx, G, ldg, c, cs, scale, beta_dx, dX, lddx, want_dx, accumulate_dc,
+                           dC, dCs, want_dc, s, ws);
   BwdArgs a{};
   a.fin = p->fin->dev;
   a.fout = p->fout->dev;
@@ -540,7 +554,6 @@ hipError_t launch_bwd(const ff_plan* p, int bf16, int count, int T, ActPtrs X, i
   a.ldb_in = p->ldb_in;
   a.ldb_out = p->ldb_out;
   a.nch = p->gen_nch;
-  a.g4 = bf16 ? p->gen_g4 : 0;
   for (int i = 0; i <= p->gen_nch; ++i) a.chunk_blk[i] = p->gen_chunk_blk[i];
   a.X = X.one;
   a.Xs = X.many;
@@ -586,13 +599,9 @@ hipError_t launch_bwd(const ff_plan* p, int bf16, int count, int T, ActPtrs X, i
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  if (want_dc) {
-    const int len = (int)a.cstride, nmain = (len + 63) / 64;
-    const int npadb = (p->dev.ncoef_pad + 64 * kDcWaves - 1) / (64 * kDcWaves);
-    const dim3 grid((unsigned)(nmain + npadb), (unsigned)count);
-    hipLaunchKernelGGL(dc_reduce, grid, dim3(64 * kDcWaves), 0, s, a.partial, nwg, len, a.st.coef,
-                       p->dev.coef_pad, p->dev.ncoef_pad, scale, accumulate_dc, dC, dCs);
-  }
+  if (want_dc)
+    return launch_dc_reduce(a.partial, nwg, (int)a.cstride, a.st.coef, p->dev.coef_pad, p->dev.ncoef_pad, scale,
+                            accumulate_dc, dC, dCs, count, s);
   return hipGetLastError();
 }
 
@@ -601,6 +610,8 @@ hipError_t launch_fwd_group(const ff_plan_group* g, int bf16, int T, const int* 
                             hipStream_t s) {
   const ff_plan* p = g->ref;
   if (bf16 && p->fast.enabled) return launch_fwd128_group(g, T, tokens, X, ldx, cs, scale, beta, Y, ldy, s);
+  if (bf16 && p->slab.enabled)
+    return launch_fwd_group_slab(g, bf16, T, tokens, X, ldx, cs, scale, beta, Y, ldy, s);
   const unsigned count = (unsigned)g->count;
   FwdArgs a{};
   a.fin = p->fin->dev;
@@ -610,7 +621,6 @@ hipError_t launch_fwd_group(const ff_plan_group* g, int bf16, int T, const int* 
   a.ldt_in = p->gen_ldt_in[bf16];
   a.ldt_out = p->ldt_out[bf16];
   a.nch = p->gen_nch;
-  a.g4 = bf16 ? p->gen_g4 : 0;
   for (int i = 0; i <= p->gen_nch; ++i) a.chunk_blk[i] = p->gen_chunk_blk[i];
   a.ldb_in = p->ldb_in;
   a.ldb_out = p->ldb_out;
@@ -645,6 +655,9 @@ hipError_t launch_bwd_group(const ff_plan_group* g, int bf16, int T, const int* 
   if (bf16 && p->fast.enabled)
     return launch_bwd128_group(g, T, tokens, X, ldx, G, ldg, cs, scale, beta_dx, dX, lddx, want_dx, accumulate_dc,
                                dCs, want_dc, s);
+  if (bf16 && p->slab.enabled)
+    return launch_bwd_group_slab(g, bf16, T, tokens, X, ldx, G, ldg, cs, scale, beta_dx, dX, lddx, want_dx,
+                                 accumulate_dc, dCs, want_dc, s);
   const unsigned count = (unsigned)g->count;
   BwdArgs a{};
   a.fin = p->fin->dev;
@@ -656,7 +669,6 @@ hipError_t launch_bwd_group(const ff_plan_group* g, int bf16, int T, const int* 
   a.ldb_in = p->ldb_in;
   a.ldb_out = p->ldb_out;
   a.nch = p->gen_nch;
-  a.g4 = bf16 ? p->gen_g4 : 0;
   for (int i = 0; i <= p->gen_nch; ++i) a.chunk_blk[i] = p->gen_chunk_blk[i];
   a.Xs = X;
   a.ldx = (long)ldx;

@@ -267,6 +267,79 @@ void append_stream(StreamHost& all, const StreamHost& h) {
   all.rows += h.rows;
 }
 
+// A slab stream (SlabStream) on the host.  id: user entry of every element (-1: padding).
+struct SlabStreamHost {
+  std::vector<uint32_t> word;
+  std::vector<int> id;
+  std::vector<int> wstep, zptr;
+  std::vector<unsigned short> zrow;
+  int64_t steps = 0;
+  int nb = 1, ngroups = 0;
+};
+
+// lists[pos]: entries of destination position pos; src(e): source position of entry e; zero_src: the
+// source slab's row of zeros.
+template <class Src>
+SlabStreamHost build_slab_stream(const std::vector<std::vector<int>>& lists, const ff::FrameDev& dst, Src src,
+                                 uint32_t zero_src) {
+  SlabStreamHost h;
+  h.nb = ff::slab_group_blocks(dst);
+  h.ngroups = (dst.nblk + h.nb - 1) / h.nb;
+  h.zptr.push_back(0);
+  for (int g = 0; g < h.ngroups; ++g) {
+    const int64_t p0 = (int64_t)g * h.nb * dst.W, p1 = std::min<int64_t>(p0 + (int64_t)h.nb * dst.W,
+                                                                         (int64_t)dst.nblk * dst.W);
+    const uint32_t dump = (uint32_t)(h.nb * dst.W);   // tile row of lanes that hold no row
+    std::vector<int> rows;
+    for (int64_t r = p0; r < p1; ++r) {
+      if (lists[r].empty())
+        h.zrow.push_back((unsigned short)(r - p0));
+      else
+        rows.push_back((int)r);
+    }
+    h.zptr.push_back((int)h.zrow.size());
+    std::stable_sort(rows.begin(), rows.end(), [&](int a, int b) { return lists[a].size() > lists[b].size(); });
+    // bundles of 16 rows, longest first, each to the wave with the fewest steps so far
+    const int nbun = ((int)rows.size() + 15) / 16;
+    std::vector<std::vector<int>> of_wave(ff::kSlabWaves);
+    std::vector<int64_t> load(ff::kSlabWaves, 0);
+    for (int b = 0; b < nbun; ++b) {
+      const int w = (int)(std::min_element(load.begin(), load.end()) - load.begin());
+      of_wave[w].push_back(b);
+      load[w] += (int64_t)lists[rows[16 * b]].size();
+    }
+    for (int w = 0; w < ff::kSlabWaves; ++w) {
+      h.wstep.push_back((int)h.steps);
+      const int64_t len4 = (load[w] + 3) / 4 * 4;   // whole batches: the last steps are padding into the spare row
+      const size_t at = h.word.size();
+      h.word.resize(at + 16 * (size_t)len4, zero_src | dump << ff::kSlabDstShift);
+      h.id.resize(h.word.size(), -1);
+      int64_t k0 = 0;
+      for (int b : of_wave[w]) {
+        const int64_t len = (int64_t)lists[rows[16 * b]].size();
+        for (int64_t k = 0; k < len; ++k)
+          for (int l = 0; l < 16; ++l) {
+            const bool real = 16 * b + l < (int)rows.size();
+            const int r = real ? rows[16 * b + l] : 0;
+            const int e = real && k < (int64_t)lists[r].size() ? lists[r][k] : -1;
+            const uint32_t d = real ? (uint32_t)(r - p0) : dump;
+            // batches of four steps: entry l of step k at 64 (k / 4) + 4 l + k % 4
+            const size_t j = at + (size_t)((k0 + k) / 4 * 64 + 4 * l + (k0 + k) % 4);
+            h.word[j] = (e >= 0 ? (uint32_t)src(e) : zero_src) | d << ff::kSlabDstShift |
+                        (k == len - 1 ? (uint32_t)ff::kRowLast : 0u);
+            h.id[j] = e;
+          }
+        k0 += len;
+      }
+      h.steps += len4;
+    }
+    h.wstep.push_back((int)h.steps);
+  }
+  h.word.resize(h.word.size() + 16 * ff::kSlabPadSteps, zero_src);
+  h.id.resize(h.word.size(), -1);
+  return h;
+}
+
 extern "C" ff_status ff_plan_create(const ff_frame* f_in, const ff_frame* f_out, int64_t nnz,
                                     const int32_t* rows, const int32_t* cols, int64_t max_tokens,
                                     int64_t max_batch, ff_plan** out) {
@@ -346,13 +419,9 @@ extern "C" ff_status ff_plan_create(const ff_frame* f_in, const ff_frame* f_out,
       }
     p->gen_nch = nch;
     for (int c = 0; c <= nch; ++c) p->gen_chunk_blk[c] = (int)((int64_t)c * FI.nblk / nch);
-    // bf16 token-grouped tiles (gen_kernels.h): every table row of the sparse phases reads four
-    // tokens per LDS access; they need whole groups of four tokens, and frames whose blocks are
-    // applied directly (up to 128 wide) or in one radix-4 stage
-    auto grouped_ok = [](const ff::FrameDev& f) {
-      return (f.radix == 1 && f.nst == 0 && f.W <= 128) || (f.radix == 4 && f.nst == 1 && f.W2 <= 128);
-    };
-    p->gen_g4 = grouped_ok(FI) && grouped_ok(FO) && !f_in->lifted && !f_out->lifted && chunk_tokens(nch, FF_BF16) >= 4;
+    // bf16 tiles in whole groups of four tokens, where the slab kernels take the calls (the reported
+    // geometry, and the bound of ff_adapter_bwd_noalloc)
+    p->gen_g4 = ff::slab_frame(FI) && ff::slab_frame(FO) && !f_in->lifted && !f_out->lifted && chunk_tokens(nch, FF_BF16) >= 4;
     for (int dt = 0; dt < 2; ++dt) {
       const int esz = dt == FF_BF16 ? 2 : 4;
       p->gen_ldt_in[dt] = token_stride((FI.nblk + nch - 1) / nch, p->ldb_in, esz);
@@ -433,6 +502,33 @@ extern "C" ff_status ff_plan_create(const ff_frame* f_in, const ff_frame* f_out,
       if (so < 0 || so >= cmax * p->ldb_in || e.y < -1 || e.y >= FO.nblk * p->ldb_out)
         return ff::fail(FF_EINVAL, "internal: forward stream offset outside its tile");
     }
+  }
+  // the slab kernels' streams (bf16 calls): rows of C into output positions, columns into input ones
+  const bool slab = ff::slab_frame(FI) && ff::slab_frame(FO) && !f_in->lifted && !f_out->lifted &&
+                    n < (int64_t)ff::kSlabSrcMask && m < (int64_t)ff::kSlabSrcMask;
+  SlabStreamHost sfwd, sbwd;
+  if (slab) {
+    // position of a coefficient: whole blocks in order, a factored block's four columns in turn
+    auto position = [](const ff::FrameDev& f, const Loc& l) {
+      if (f.radix == 1) return l.blk * f.W + l.local;
+      const int i = l.local >> 1;
+      return l.blk * f.W + (i & 3) * f.W2 + 2 * (i >> 2) + (l.local & 1);
+    };
+    auto by_position = [&](const std::vector<std::vector<int>>& by, const ff::FrameDev& f, int64_t rho, auto other) {
+      std::vector<std::vector<int>> out(by.size());
+      for (int64_t c = 0; c < (int64_t)by.size(); ++c) {
+        std::vector<int> l = by[c];
+        std::stable_sort(l.begin(), l.end(), [&](int a, int b) { return other(a) < other(b); });
+        out[(size_t)position(f, locate(c, rho))] = std::move(l);
+      }
+      return out;
+    };
+    auto pos_in = [&](int e) { return position(FI, cloc[e]); };
+    auto pos_out = [&](int e) { return position(FO, rloc[e]); };
+    sfwd = build_slab_stream(by_position(by_row, FO, f_out->rho, pos_in), FO, pos_in, (uint32_t)n);
+    sbwd = build_slab_stream(by_position(by_col, FI, f_in->rho, pos_out), FI, pos_out, (uint32_t)m);
+    if (std::max(sfwd.word.size(), sbwd.word.size()) > (size_t)1 << 30)
+      return ff::fail(FF_EUNSUPPORTED, "support too skewed for the entry streams");
   }
   // merge buckets (R, S)
   const int64_t nb = (int64_t)FO.nblk * FI.nblk;
@@ -556,6 +652,9 @@ extern "C" ff_status ff_plan_create(const ff_frame* f_in, const ff_frame* f_out,
       if (gfwd.id[j] >= 0) slot_of_user[gfwd.id[j]] = (int)j;
   }
   const int64_t nslot = (int64_t)user_of_slot.size();   // coefficient slots (>= nnz)
+  std::vector<int> sfcoef(sfwd.id.size()), sbcoef(sbwd.id.size());
+  for (size_t j = 0; j < sfcoef.size(); ++j) sfcoef[j] = sfwd.id[j] >= 0 ? slot_of_user[sfwd.id[j]] : -1;
+  for (size_t j = 0; j < sbcoef.size(); ++j) sbcoef[j] = sbwd.id[j] >= 0 ? slot_of_user[sbwd.id[j]] : -1;
   // for the 128-wide backward: the backward slot of every coefficient slot (padding slots go
   // to the scratch slot just past the backward slots)
   std::vector<int> bwd_pos;
@@ -597,9 +696,24 @@ extern "C" ff_status ff_plan_create(const ff_frame* f_in, const ff_frame* f_out,
   }
   // (a call may use tiles of fewer tokens than the LDS allows, so up to one tile per token)
   p->gen_rows = (int)std::max<int64_t>(1, std::min<int64_t>(max_tokens, p->gen_wgs));
-  const size_t partial_elems = std::max((size_t)max_batch * (size_t)p->gen_rows * gb_elems,
-                                        (size_t)max_batch * (size_t)fast_tiles *
-                                            (fast ? ff::fast128_partial_floats(b_st.size()) : 0));
+  size_t partial_elems = std::max((size_t)max_batch * (size_t)p->gen_rows * gb_elems,
+                                  (size_t)max_batch * (size_t)fast_tiles *
+                                      (fast ? ff::fast128_partial_floats(b_st.size()) : 0));
+  // slab kernels: dC partial rows (one per slab while they are few), the pool of source slabs
+  // (every adapter's whole call, up to the bound; at least one slab) and the entries' copy
+  const int64_t slab_tokens = ff::kSlabRowBytes / 2, nslabs = std::max<int64_t>(1, (max_tokens + slab_tokens - 1) / slab_tokens);
+  int slab_rows = 0;
+  size_t slab_pool = 0, slab_ent = 0;
+  if (slab) {
+    const size_t row_bytes = std::max<size_t>((size_t)sbwd.steps * 16 * sizeof(float), 1);
+    slab_rows = (int)std::max<int64_t>(1, std::min<int64_t>({nslabs, (int64_t)ff::kSlabMaxRows,
+                                                             (int64_t)(ff::kSlabPartialBytes / row_bytes)}));
+    partial_elems = std::max(partial_elems, (size_t)max_batch * (size_t)slab_rows * (size_t)sbwd.steps * 16);
+    const size_t one = (size_t)(std::max(n, m) + 1) * ff::kSlabRowBytes;
+    const size_t cap = std::max<size_t>(ff::kSlabPoolBytes / one, 1);
+    slab_pool = one * (size_t)std::min<int64_t>((int64_t)cap, nslabs * max_batch);
+    slab_ent = std::max(sfwd.word.size(), sbwd.word.size());
+  }
   struct Blob {
     const void* src;
     size_t bytes;
@@ -607,7 +721,9 @@ extern "C" ff_status ff_plan_create(const ff_frame* f_in, const ff_frame* f_out,
   enum {
     kGfEnt, kGfCoef, kGfWave, kGbEnt, kGbCoef, kGbWave, kCoefPad, kCfwd, kCbwd, kMrgPtr, kMrgEnt,
     kFPl, kBPl, kFSt, kPadSlots, kBW, kPartial, kCoefBwd, kBwdPos, kFEm, kBDst, kBEm, kBPad, kUserOfSlot,
-    kSlotOfUser, kMrgG, kMrgOut, kLiftX, kLiftG, kLiftDX, kNumBlobs
+    kSlotOfUser, kMrgG, kMrgOut, kLiftX, kLiftG, kLiftDX,
+    kSfWord, kSfCoef, kSfWave, kSfZptr, kSfZrow, kSbWord, kSbCoef, kSbWave, kSbZptr, kSbZrow, kSlabPool, kSlabEnt,
+    kNumBlobs
   };
   // frames with a lift merge through the backward, a chunk of (user) rows at a time
   const bool lifted = f_in->lifted || f_out->lifted;
@@ -650,6 +766,17 @@ extern "C" ff_status ff_plan_create(const ff_frame* f_in, const ff_frame* f_out,
   blobs[kLiftX] = {nullptr, lift_rows * (size_t)n * sizeof(float)};
   blobs[kLiftG] = {nullptr, lift_rows * (size_t)m * sizeof(float)};
   blobs[kLiftDX] = {nullptr, lift_rows * (size_t)n * sizeof(float)};
+  auto slab_blobs = [&](int first, const SlabStreamHost& h, const std::vector<int>& coef) {
+    blobs[first] = {h.word.data(), h.word.size() * sizeof(uint32_t)};
+    blobs[first + 1] = {coef.data(), coef.size() * sizeof(int)};
+    blobs[first + 2] = {h.wstep.data(), h.wstep.size() * sizeof(int)};
+    blobs[first + 3] = {h.zptr.data(), h.zptr.size() * sizeof(int)};
+    blobs[first + 4] = {h.zrow.data(), h.zrow.size() * sizeof(unsigned short)};
+  };
+  slab_blobs(kSfWord, sfwd, sfcoef);
+  slab_blobs(kSbWord, sbwd, sbcoef);
+  blobs[kSlabPool] = {nullptr, slab_pool};
+  blobs[kSlabEnt] = {nullptr, (size_t)max_batch * slab_ent * sizeof(uint2)};
   size_t total = 0;
   for (const Blob& b : blobs) total += up(b.bytes);
   int cur = 0;
@@ -720,6 +847,20 @@ extern "C" ff_status ff_plan_create(const ff_frame* f_in, const ff_frame* f_out,
   fp.bwd_pos = (const int*)where[kBwdPos];
   fp.coef_slots = (int)nslot;
   fp.bwd16 = bwd16 ? 1 : 0;
+  ff::SlabPlanDev& sp = p->slab;
+  auto slab_dev = [&](int first, const SlabStreamHost& h) {
+    return ff::SlabStream{(const uint32_t*)where[first], (const int*)where[first + 1], (const int*)where[first + 2],
+                          (const int*)where[first + 3], (const unsigned short*)where[first + 4], (int)h.steps, h.nb,
+                          h.ngroups};
+  };
+  sp.enabled = slab ? 1 : 0;
+  sp.fwd = slab_dev(kSfWord, sfwd);
+  sp.bwd = slab_dev(kSbWord, sbwd);
+  sp.pool = (unsigned char*)where[kSlabPool];
+  sp.pool_bytes = slab_pool;
+  sp.ent = (uint2*)where[kSlabEnt];
+  sp.ent_adapter = (long)slab_ent;
+  sp.rows = slab_rows;
   p->dev_mem = mem;
   p->workspace_bytes = total;
   p->fin->refs.fetch_add(1);
