@@ -32,20 +32,30 @@ hipError_t analysis(const AnaArgs& a, dim3 grid, size_t lds, hipStream_t s) {
 }
 
 hipError_t fwd(const SlabArgs& a, dim3 grid, size_t lds, hipStream_t s) {
-#define X(kt) hipLaunchKernelGGL((slab_fwd<kBf, kt, kRad>), grid, dim3(kSlabThreads), lds, s, a)
+  const bool beta = a.beta != 0.f;
+#define X(kt)                                                                                     \
+  if (beta)                                                                                       \
+    hipLaunchKernelGGL((slab_fwd<kBf, kt, kRad, true>), grid, dim3(kSlabThreads), lds, s, a);      \
+  else                                                                                            \
+    hipLaunchKernelGGL((slab_fwd<kBf, kt, kRad, false>), grid, dim3(kSlabThreads), lds, s, a)
   SLAB_CASES(X)
 #undef X
   return hipGetLastError();
 }
 
 hipError_t bwd(const SlabArgs& a, bool dx, bool dc, dim3 grid, size_t lds, hipStream_t s) {
-#define X(kt)                                                                                       \
-  if (dx && dc)                                                                                     \
-    hipLaunchKernelGGL((slab_bwd<kBf, kt, kRad, true, true>), grid, dim3(kSlabThreads), lds, s, a);  \
-  else if (dx)                                                                                      \
-    hipLaunchKernelGGL((slab_bwd<kBf, kt, kRad, true, false>), grid, dim3(kSlabThreads), lds, s, a); \
-  else                                                                                              \
-    hipLaunchKernelGGL((slab_bwd<kBf, kt, kRad, false, true>), grid, dim3(kSlabThreads), lds, s, a)
+  const bool beta = a.beta != 0.f;
+#define X(kt)                                                                                              \
+  if (dx && dc && beta)                                                                                    \
+    hipLaunchKernelGGL((slab_bwd<kBf, kt, kRad, true, true, true>), grid, dim3(kSlabThreads), lds, s, a);   \
+  else if (dx && dc)                                                                                       \
+    hipLaunchKernelGGL((slab_bwd<kBf, kt, kRad, true, true, false>), grid, dim3(kSlabThreads), lds, s, a);  \
+  else if (dx && beta)                                                                                     \
+    hipLaunchKernelGGL((slab_bwd<kBf, kt, kRad, true, false, true>), grid, dim3(kSlabThreads), lds, s, a);  \
+  else if (dx)                                                                                             \
+    hipLaunchKernelGGL((slab_bwd<kBf, kt, kRad, true, false, false>), grid, dim3(kSlabThreads), lds, s, a); \
+  else                                                                                                     \
+    hipLaunchKernelGGL((slab_bwd<kBf, kt, kRad, false, true, false>), grid, dim3(kSlabThreads), lds, s, a)
   SLAB_CASES(X)
 #undef X
   return hipGetLastError();
@@ -55,10 +65,13 @@ template <int KT>
 hipError_t allow() {
   hipError_t e = hipSuccess;
   for (const void* fn : {reinterpret_cast<const void*>(&slab_analysis<kBf, KT, kRad>),
-                         reinterpret_cast<const void*>(&slab_fwd<kBf, KT, kRad>),
-                         reinterpret_cast<const void*>(&slab_bwd<kBf, KT, kRad, true, true>),
-                         reinterpret_cast<const void*>(&slab_bwd<kBf, KT, kRad, true, false>),
-                         reinterpret_cast<const void*>(&slab_bwd<kBf, KT, kRad, false, true>)}) {
+                         reinterpret_cast<const void*>(&slab_fwd<kBf, KT, kRad, false>),
+                         reinterpret_cast<const void*>(&slab_fwd<kBf, KT, kRad, true>),
+                         reinterpret_cast<const void*>(&slab_bwd<kBf, KT, kRad, true, true, false>),
+                         reinterpret_cast<const void*>(&slab_bwd<kBf, KT, kRad, true, true, true>),
+                         reinterpret_cast<const void*>(&slab_bwd<kBf, KT, kRad, true, false, false>),
+                         reinterpret_cast<const void*>(&slab_bwd<kBf, KT, kRad, true, false, true>),
+                         reinterpret_cast<const void*>(&slab_bwd<kBf, KT, kRad, false, true, false>)}) {
     const hipError_t r = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLdsBytes);
     if (r != hipSuccess) e = r;
   }

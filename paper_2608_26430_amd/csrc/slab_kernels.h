@@ -364,8 +364,9 @@ struct AnaArgs {
   int bwd;               // group calls: which stream's entries
 };
 
-// Workgroups per CU that the widest blocks of a kernel leave LDS for, which bounds its registers.
-constexpr int slab_wgs(int KT, bool RADIX) { return RADIX && KT >= 4 ? 2 : 3; }
+// Workgroups per CU that the widest blocks of a kernel leave LDS for (two also where factored blocks'
+// results wait in fp32), which bounds its registers.
+constexpr int slab_wgs(int KT, bool RADIX, bool BETA = false) { return RADIX && (KT >= 4 || BETA) ? 2 : 3; }
 
 template <bool BF16, int KT, bool RADIX>
 __global__ void __launch_bounds__(kSlabThreads, slab_wgs(KT, RADIX)) slab_analysis(AnaArgs a) {
@@ -586,13 +587,13 @@ __device__ __forceinline__ typename Mfma<BF16>::V tile_operand(const unsigned ch
   }
 }
 
-// out = s P v (+ beta out) from the tile for one group of blocks of a slab, through the stage.  Work
-// items as above; each output is rounded once: directly applied blocks find the old values in the
-// stage, factored ones read them from memory.  Factored blocks: the DFT of size k/4 of the four
+// out = s P v (+ beta out) from the tile for one group of blocks of a slab, through the stage, where
+// the old values wait when BETA, so that each output is rounded once.  Work items as above (token
+// groups past the slab's tokens are left out).  Factored blocks: the DFT of size k/4 of the four
 // columns (with the twiddles) leaves each lane with two complex coordinates of all four, which the
 // radix-4 stage's sums combine in registers; their stage takes the tile's LDS, so the results wait in registers until
 // every wave has read the tile.
-template <bool BF16, int KT, bool RADIX>
+template <bool BF16, int KT, bool RADIX, bool BETA>
 __device__ __forceinline__ void group_synthesis(const FrameDev& f, const void* frag, unsigned char* tile,
                                                 unsigned char* stage, int nb, int nt, unsigned char* dst, long ld,
                                                 float s, float beta) {
@@ -606,13 +607,14 @@ __device__ __forceinline__ void group_synthesis(const FrameDev& f, const void* f
   int have = -1;
   if constexpr (!RADIX) {
     V fr[KT];
-    if (beta != 0.f) {
+    if (BETA) {
       stage_load<S>(dst, ld, nt, cb, stage);
       __syncthreads();
     }
     for (int it = items.i0; it < items.i1; ++it) {
       int mt, bl, th;
       items.get(it, mt, bl, th);
+      if (16 * NTH * th >= nt) continue;   // uniform
       if (mt != have) load_frags<V, KT>(frag, mt, lane, fr);
       have = mt;
       f32x4 acc[NTH];
@@ -631,7 +633,7 @@ __device__ __forceinline__ void group_synthesis(const FrameDev& f, const void* f
         for (int g = 0; g < NTH; ++g) {
           auto* p = reinterpret_cast<typename A::E*>(stage + (16 * (NTH * th + g) + L) * sb) + bl * W2 + o;
           f32x4 v = acc[g] * s;
-          if (beta != 0.f) v += beta * A::ld4(p);
+          if (BETA) v += beta * A::ld4(p);
           A::st4(p, v);
         }
       }
@@ -639,7 +641,8 @@ __device__ __forceinline__ void group_synthesis(const FrameDev& f, const void* f
   } else {
     constexpr int NI = radix_items<BF16>(KT);
     V fr[4][KT];
-    using O = typename std::conditional<BF16, unsigned, float2>::type;
+    // results as stored, or in fp32 until the old values are added
+    using O = typename std::conditional<BF16 && !BETA, unsigned, float2>::type;
     O out[NI][NTH][2][4];   // [item][token group][complex coordinate][a]
 #pragma unroll
     for (int n = 0; n < NI; ++n) {
@@ -647,10 +650,12 @@ __device__ __forceinline__ void group_synthesis(const FrameDev& f, const void* f
       if (it >= items.i1) break;   // uniform
       int mt, bl, th;
       items.get(it, mt, bl, th);
+      if (16 * NTH * th >= nt) continue;   // uniform
       if (mt != have) load_frags4<V, KT>(frag, f.MT, mt, lane, fr);
       have = mt;
 #pragma unroll
       for (int g = 0; g < NTH; ++g) {
+        if (16 * (NTH * th + g) >= nt) break;   // uniform
         f32x4 acc[4];
 #pragma unroll
         for (int a = 0; a < 4; ++a) acc[a] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -661,10 +666,8 @@ __device__ __forceinline__ void group_synthesis(const FrameDev& f, const void* f
           for (int a = 0; a < 4; ++a)
             acc[a] = M::step(fr[a][ks], tile_operand<BF16>(tile, a * W2 + e, NTH * th + g, L), acc[a]);
         }
-        const int t = min(16 * (NTH * th + g) + L, nt - 1);   // (tokens past the end are not stored)
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
-          const int c = min(8 * mt + 2 * q + u, f.k2 - 1);
           float2 y[4];
 #pragma unroll
           for (int a = 0; a < 4; ++a) y[a] = make_float2(acc[a][2 * u], acc[a][2 * u + 1]);
@@ -676,17 +679,10 @@ __device__ __forceinline__ void group_synthesis(const FrameDev& f, const void* f
           x[3] = make_float2(d02.x + d13.y, d02.y - d13.x);   // d02 - i d13
 #pragma unroll
           for (int a = 0; a < 4; ++a) {
-            float2 v = make_float2(s * x[a].x, s * x[a].y);
-            if (beta != 0.f) {
-              const float2 old =
-                  gld2<BF16>(reinterpret_cast<const typename A::E*>(dst + (long)t * ld) + a * W2 + 2 * c);
-              v.x = fmaf(beta, old.x, v.x);
-              v.y = fmaf(beta, old.y, v.y);
-            }
-            if constexpr (BF16)
-              out[n][g][u][a] = pk_bf2(v.x, v.y);
+            if constexpr (BF16 && !BETA)
+              out[n][g][u][a] = pk_bf2(s * x[a].x, s * x[a].y);
             else
-              out[n][g][u][a] = v;
+              out[n][g][u][a] = make_float2(s * x[a].x, s * x[a].y);
           }
         }
         // one token group after the other: the scheduler would interleave them past the registers
@@ -694,6 +690,10 @@ __device__ __forceinline__ void group_synthesis(const FrameDev& f, const void* f
       }
     }
     __syncthreads();   // the tile is read
+    if (BETA) {
+      stage_load<S>(dst, ld, nt, cb, stage);
+      __syncthreads();
+    }
 #pragma unroll
     for (int n = 0; n < NI; ++n) {
       const int it = items.i0 + n;
@@ -705,10 +705,19 @@ __device__ __forceinline__ void group_synthesis(const FrameDev& f, const void* f
         const int o = 16 * mt + 4 * q + 2 * u;
         if (o >= W2) continue;
 #pragma unroll
-        for (int g = 0; g < NTH; ++g)
+        for (int g = 0; g < NTH; ++g) {
+          if (16 * (NTH * th + g) >= nt) break;   // uniform
 #pragma unroll
-          for (int a = 0; a < 4; ++a)
-            *reinterpret_cast<O*>(stage + (16 * (NTH * th + g) + L) * sb + (a * W2 + o) * ESZ) = out[n][g][u][a];
+          for (int a = 0; a < 4; ++a) {
+            auto* p = reinterpret_cast<typename A::E*>(stage + (16 * (NTH * th + g) + L) * sb) + a * W2 + o;
+            if constexpr (BETA) {
+              const float2 old = ld2<BF16>(p), v = out[n][g][u][a];
+              st2<BF16>(p, make_float2(fmaf(beta, old.x, v.x), fmaf(beta, old.y, v.y)));
+            } else {
+              *reinterpret_cast<O*>(p) = out[n][g][u][a];
+            }
+          }
+        }
       }
     }
   }
@@ -746,7 +755,7 @@ struct SlabArgs {
   const int* tokens;
 };
 
-template <bool BF16, int KT, bool RADIX, bool BWD, bool DX, bool DC>
+template <bool BF16, int KT, bool RADIX, bool BWD, bool DX, bool DC, bool BETA>
 __device__ __forceinline__ void slab_pass(SlabArgs& a) {
   constexpr int S = SlabT<BF16>::S, ESZ = SlabT<BF16>::ESZ;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -796,19 +805,19 @@ __device__ __forceinline__ void slab_pass(SlabArgs& a) {
     if constexpr (!BWD || DX) {
       zero_rows(smem, a.zrow + z0, z1 - z0);
       __syncthreads();
-      group_synthesis<BF16, KT, RADIX>(f, a.fs, smem, stage, nb, nt, Y + t0 * a.ldy * ESZ, a.ldy * ESZ, a.scale, a.beta);
+      group_synthesis<BF16, KT, RADIX, BETA>(f, a.fs, smem, stage, nb, nt, Y + t0 * a.ldy * ESZ, a.ldy * ESZ, a.scale, a.beta);
     }
   }
 }
 
-template <bool BF16, int KT, bool RADIX>
-__global__ void __launch_bounds__(kSlabThreads, slab_wgs(KT, RADIX)) slab_fwd(SlabArgs a) {
-  slab_pass<BF16, KT, RADIX, false, true, false>(a);
+template <bool BF16, int KT, bool RADIX, bool BETA>
+__global__ void __launch_bounds__(kSlabThreads, slab_wgs(KT, RADIX, BETA)) slab_fwd(SlabArgs a) {
+  slab_pass<BF16, KT, RADIX, false, true, false, BETA>(a);
 }
 
-template <bool BF16, int KT, bool RADIX, bool DX, bool DC>
-__global__ void __launch_bounds__(kSlabThreads, slab_wgs(KT, RADIX)) slab_bwd(SlabArgs a) {
-  slab_pass<BF16, KT, RADIX, true, DX, DC>(a);
+template <bool BF16, int KT, bool RADIX, bool DX, bool DC, bool BETA>
+__global__ void __launch_bounds__(kSlabThreads, slab_wgs(KT, RADIX, BETA)) slab_bwd(SlabArgs a) {
+  slab_pass<BF16, KT, RADIX, true, DX, DC, BETA>(a);
 }
 
 // One activation type and frame kind (slab_inst.hip).
