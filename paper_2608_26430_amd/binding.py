@@ -86,9 +86,8 @@ def _load():
 
 
 def _check(status: int):
-    if status != 0:
-        msg = _load().ff_last_error().decode()
-        raise FrameFTError(status, msg)
+    if status:
+        raise FrameFTError(status, _load().ff_last_error().decode())
 
 
 # ------------------------------------------------------------------ frames
@@ -165,6 +164,8 @@ class Plan:
         self.nnz = int(rows.size)
         self.max_tokens, self.max_batch = max_tokens, max_batch
         self._order = None
+        # fixed at creation and needed by every call
+        self._coef_slots, self._saved_floats = self.query(5), self.query(6)
 
     @property
     def handle(self):
@@ -190,12 +191,12 @@ class Plan:
     @property
     def coef_slots(self) -> int:
         """Length L of every c / dC array of this plan (nnz plus padding slots)."""
-        return self.query(5)
+        return self._coef_slots
 
     @property
     def saved_floats(self) -> int:
         """Length of the c_saved arrays of adapter_fwd(save=...) / adapter_bwd(saved=...) (0: none needed)."""
-        return self.query(6)
+        return self._saved_floats
 
     @property
     def bwd_tile_tokens(self) -> int:
@@ -273,29 +274,40 @@ def plan_create(f_in: Frame, f_out: Frame, rows, cols, max_tokens: int, max_batc
 
 # ------------------------------------------------------------------ hot path
 
+# A call on a small layer takes the GPU about ten microseconds, so the marshalling of the hot calls
+# counts: torch is looked up once, plan sizes are kept on the plan, the stream is taken as the raw
+# handle (torch.cuda.current_stream() builds a Stream object), and each tensor is checked in one
+# expression.
+_T = None
+
+
 def _torch():
-    import torch
-    return torch
+    global _T
+    if _T is None:
+        import torch
+        _T = torch
+    return _T
 
 
 def _act_code(t) -> int:
-    torch = _torch()
-    if t.dtype == torch.bfloat16:
+    d = t.dtype
+    torch = _T or _torch()
+    if d is torch.bfloat16:
         return FF_BF16
-    if t.dtype == torch.float32:
+    if d is torch.float32:
         return FF_F32
-    raise TypeError(f"unsupported activation dtype {t.dtype}")
+    raise TypeError(f"unsupported activation dtype {d}")
 
 
 def _mat(t, name):
-    if t.dim() != 2 or t.stride(1) != 1 or not t.is_cuda:
+    st = t.stride()
+    if len(st) != 2 or st[1] != 1 or not t.is_cuda:
         raise ValueError(f"{name} must be a 2-D device tensor with unit column stride")
-    return t.data_ptr(), t.stride(0)
+    return t.data_ptr(), st[0]
 
 
 def _vec(t, name, length=None):
-    torch = _torch()
-    if t.dtype != torch.float32 or not t.is_contiguous() or not t.is_cuda:
+    if t.dtype is not (_T or _torch()).float32 or not t.is_cuda or not t.is_contiguous():
         raise ValueError(f"{name} must be a contiguous fp32 device tensor")
     if length is not None and t.numel() != length:
         raise ValueError(f"{name} must hold the plan's {length} coefficient slots (Plan.coef_slots)")
@@ -303,32 +315,32 @@ def _vec(t, name, length=None):
 
 
 def _stream(stream):
-    torch = _torch()
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    torch = _T or _torch()
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def adapter_fwd(plan: Plan, X, c_vals, scale: float, Y=None, beta: float = 0.0, stream=None, save=None):
     """Y = beta*Y + scale * P_out C P_in^T x for each token row of X; returns Y.  With `save` (a
     c_saved array, Plan.new_saved) the forward also stores the coefficients in the backward's
     order, for adapter_bwd(saved=...) with the same c_vals (ff_adapter_fwd_save)."""
-    torch = _torch()
     T = X.shape[0]
     if Y is None:
         if beta != 0.0:
             raise ValueError("beta != 0 needs an existing Y")
-        Y = torch.empty((T, plan.m), dtype=X.dtype, device=X.device)
+        Y = _torch().empty((T, plan.m), dtype=X.dtype, device=X.device)
     xp, ldx = _mat(X, "X")
     yp, ldy = _mat(Y, "Y")
     if Y.dtype != X.dtype or Y.shape[0] != T:
         raise ValueError("Y must match X in dtype and token count")
-    cp = _vec(c_vals, "c_vals", plan.coef_slots)
+    cp = _vec(c_vals, "c_vals", plan._coef_slots)
+    lib = _lib or _load()
     if save is not None:
-        _check(_load().ff_adapter_fwd_save(plan.handle, T, _act_code(X), xp, ldx, cp, scale, beta, yp, ldy,
-                                           _vec(save, "save", plan.saved_floats), _stream(stream)))
+        _check(lib.ff_adapter_fwd_save(plan._h, T, _act_code(X), xp, ldx, cp, scale, beta, yp, ldy,
+                                       _vec(save, "save", plan._saved_floats), _stream(stream)))
     else:
-        _check(_load().ff_adapter_fwd(plan.handle, T, _act_code(X), xp, ldx, cp, scale, beta, yp, ldy,
-                                      _stream(stream)))
+        _check(lib.ff_adapter_fwd(plan._h, T, _act_code(X), xp, ldx, cp, scale, beta, yp, ldy, _stream(stream)))
     return Y
 
 
@@ -337,29 +349,28 @@ def adapter_bwd(plan: Plan, X, G, c_vals, scale: float, dX=None, dC=None, beta_d
                 saved=None):
     """Backward of adapter_fwd for upstream gradient G: returns (dX, dC) (None where not wanted).
     `saved`: the c_saved array of adapter_fwd(save=...) with the same c_vals (ff_adapter_bwd_saved)."""
-    torch = _torch()
     T = G.shape[0]
     act = _act_code(G)
     if want_dx and dX is None:
         if beta_dx != 0.0:
             raise ValueError("beta_dx != 0 needs an existing dX")
-        dX = torch.empty((T, plan.n), dtype=G.dtype, device=G.device)
+        dX = _torch().empty((T, plan.n), dtype=G.dtype, device=G.device)
     if want_dc and dC is None:
         if accumulate_dc:
             raise ValueError("accumulate_dc needs an existing dC")
-        dC = torch.empty((plan.coef_slots,), dtype=torch.float32, device=G.device)
+        dC = _torch().empty((plan._coef_slots,), dtype=_torch().float32, device=G.device)
     gp, ldg = _mat(G, "G")
     xp, ldx = _mat(X, "X") if X is not None else (None, plan.n)
     dxp, lddx = _mat(dX, "dX") if want_dx else (None, plan.n)
-    dcp = _vec(dC, "dC", plan.coef_slots) if want_dc else None
-    cp = _vec(c_vals, "c_vals", plan.coef_slots) if c_vals is not None else None
+    dcp = _vec(dC, "dC", plan._coef_slots) if want_dc else None
+    cp = _vec(c_vals, "c_vals", plan._coef_slots) if c_vals is not None else None
+    lib = _lib or _load()
     if saved is not None:
-        _check(_load().ff_adapter_bwd_saved(plan.handle, T, act, xp, ldx, gp, ldg, cp,
-                                            _vec(saved, "saved", plan.saved_floats), scale, beta_dx,
-                                            dxp, lddx, int(accumulate_dc), dcp, _stream(stream)))
+        _check(lib.ff_adapter_bwd_saved(plan._h, T, act, xp, ldx, gp, ldg, cp, _vec(saved, "saved", plan._saved_floats),
+                                        scale, beta_dx, dxp, lddx, int(accumulate_dc), dcp, _stream(stream)))
     else:
-        _check(_load().ff_adapter_bwd(plan.handle, T, act, xp, ldx, gp, ldg, cp, scale, beta_dx,
-                                      dxp, lddx, int(accumulate_dc), dcp, _stream(stream)))
+        _check(lib.ff_adapter_bwd(plan._h, T, act, xp, ldx, gp, ldg, cp, scale, beta_dx, dxp, lddx,
+                                  int(accumulate_dc), dcp, _stream(stream)))
     return (dX if want_dx else None), (dC if want_dc else None)
 
 
@@ -418,24 +429,22 @@ def lr_linear_warmup(step: int, warmup: int, total: int, base_lr: float) -> floa
 def coef_to_plan(plan: Plan, c_user, c_plan=None, stream=None):
     """Device user-order coefficients (nnz fp32) -> plan layout (Plan.coef_slots, zero padding),
     on the device (ff_coef_to_plan); returns c_plan."""
-    torch = _torch()
     if c_plan is None:
-        c_plan = torch.empty((plan.coef_slots,), dtype=torch.float32, device=c_user.device)
-    _check(_load().ff_coef_to_plan(plan.handle, _vec(c_user, "c_user", plan.nnz),
-                                   _vec(c_plan, "c_plan", plan.coef_slots), _stream(stream)))
+        c_plan = _torch().empty((plan._coef_slots,), dtype=_torch().float32, device=c_user.device)
+    _check((_lib or _load()).ff_coef_to_plan(plan._h, _vec(c_user, "c_user", plan.nnz),
+                                             _vec(c_plan, "c_plan", plan._coef_slots), _stream(stream)))
     return c_plan
 
 
 def coef_to_user(plan: Plan, c_plan, c_user=None, accumulate: bool = False, stream=None):
     """Device plan-layout array (Plan.coef_slots) -> user order (nnz), added to c_user when
     accumulate (ff_coef_to_user); returns c_user."""
-    torch = _torch()
     if c_user is None:
         if accumulate:
             raise ValueError("accumulate needs an existing c_user")
-        c_user = torch.empty((plan.nnz,), dtype=torch.float32, device=c_plan.device)
-    _check(_load().ff_coef_to_user(plan.handle, _vec(c_plan, "c_plan", plan.coef_slots),
-                                   _vec(c_user, "c_user", plan.nnz), int(accumulate), _stream(stream)))
+        c_user = _torch().empty((plan.nnz,), dtype=_torch().float32, device=c_plan.device)
+    _check((_lib or _load()).ff_coef_to_user(plan._h, _vec(c_plan, "c_plan", plan._coef_slots),
+                                             _vec(c_user, "c_user", plan.nnz), int(accumulate), _stream(stream)))
     return c_user
 
 
