@@ -172,7 +172,6 @@ constexpr int kSlabRowBytes = 128;      // one coefficient of one slab: 64 bf16 
 constexpr int kSlabWaves = 4;
 constexpr int kSlabThreads = 64 * kSlabWaves;
 constexpr int kSlabPadSteps = 16;       // readable steps past a stream's end
-constexpr int kSlabRows = 128;          // destination rows a group of narrow blocks aims at
 constexpr uint32_t kSlabSrcMask = 0x1FFFFu;
 constexpr int kSlabDstShift = 17;
 constexpr uint32_t kSlabDstMask = 0x3FFu;
@@ -201,9 +200,14 @@ struct SlabPlanDev {
   long ent_adapter = 0;
   int rows = 0;                    // dC partial rows per adapter
 };
-// Blocks per group of a side.
-inline int slab_group_blocks(const FrameDev& f) {
-  const int nb = kSlabRows / f.W;
+// Blocks of a side per group.  `units`: 128-row groups over all slabs of a call.  Few of them leave
+// CUs idle, so narrow blocks then go in groups of about 64 rows (512 -> 6912 wide, 488 tokens: 50.6 ->
+// 43.0 us a step, 8960 -> 512 wide, 52 tokens: 28.6 -> 22.7 us a forward); with many, groups of up to 160
+// rows amortize each workgroup's start (the ViT qkv forward, 72-wide blocks two at a time instead of
+// one: 37.6 -> 28.5 us).
+inline int slab_group_blocks(const FrameDev& f, int64_t units) {
+  const int rows = units <= 512 ? 64 : units <= 2048 ? 128 : 160;
+  const int nb = rows / f.W;
   return nb < 1 ? 1 : nb < f.nblk ? nb : f.nblk;
 }
 // Frames the slab kernels take: blocks applied directly or in one radix-4 stage.
@@ -331,6 +335,8 @@ struct ff_plan_group {
   // slab kernels: smallest pool and row count, longest streams
   size_t slab_pool = 0;
   int slab_rows = 0, max_slab_fwd = 0, max_slab_bwd = 0;   // (entries, padding steps included)
+  // most blocks per group and most groups of any plan (plans for fewer tokens have smaller groups)
+  int slab_nb_fwd = 0, slab_nb_bwd = 0, slab_groups_fwd = 0, slab_groups_bwd = 0;
   const ff::SlabDesc* slab = nullptr;   // [count], device
 };
 

@@ -99,6 +99,10 @@ ff_status ff_plan_group_create(int64_t count, const ff_plan* const* plans, ff_pl
     slab[i] = ff::SlabDesc{sp.fwd, sp.bwd, sp.pool, sp.ent, p->partial};
     g->slab_pool = std::min(g->slab_pool, sp.pool_bytes);
     g->slab_rows = std::min(g->slab_rows, sp.rows);
+    g->slab_nb_fwd = std::max(g->slab_nb_fwd, sp.fwd.nb);
+    g->slab_nb_bwd = std::max(g->slab_nb_bwd, sp.bwd.nb);
+    g->slab_groups_fwd = std::max(g->slab_groups_fwd, sp.fwd.ngroups);
+    g->slab_groups_bwd = std::max(g->slab_groups_bwd, sp.bwd.ngroups);
     g->max_slab_fwd = std::max(g->max_slab_fwd, 16 * (sp.fwd.steps + ff::kSlabPadSteps));
     g->max_slab_bwd = std::max(g->max_slab_bwd, 16 * (sp.bwd.steps + ff::kSlabPadSteps));
     g->max_fast_items = std::max(g->max_fast_items, f.coef_slots + f.nbpad);

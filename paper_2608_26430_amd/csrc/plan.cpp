@@ -280,10 +280,10 @@ struct SlabStreamHost {
 // lists[pos]: entries of destination position pos; src(e): source position of entry e; zero_src: the
 // source slab's row of zeros.
 template <class Src>
-SlabStreamHost build_slab_stream(const std::vector<std::vector<int>>& lists, const ff::FrameDev& dst, Src src,
-                                 uint32_t zero_src) {
+SlabStreamHost build_slab_stream(const std::vector<std::vector<int>>& lists, const ff::FrameDev& dst, int64_t slabs,
+                                 Src src, uint32_t zero_src) {
   SlabStreamHost h;
-  h.nb = ff::slab_group_blocks(dst);
+  h.nb = ff::slab_group_blocks(dst, slabs * ((int64_t)dst.nblk * dst.W + 127) / 128);
   h.ngroups = (dst.nblk + h.nb - 1) / h.nb;
   h.zptr.push_back(0);
   for (int g = 0; g < h.ngroups; ++g) {
@@ -525,8 +525,9 @@ extern "C" ff_status ff_plan_create(const ff_frame* f_in, const ff_frame* f_out,
     };
     auto pos_in = [&](int e) { return position(FI, cloc[e]); };
     auto pos_out = [&](int e) { return position(FO, rloc[e]); };
-    sfwd = build_slab_stream(by_position(by_row, FO, f_out->rho, pos_in), FO, pos_in, (uint32_t)n);
-    sbwd = build_slab_stream(by_position(by_col, FI, f_in->rho, pos_out), FI, pos_out, (uint32_t)m);
+    const int64_t slabs = (max_tokens + ff::kSlabRowBytes / 2 - 1) / (ff::kSlabRowBytes / 2) * max_batch;
+    sfwd = build_slab_stream(by_position(by_row, FO, f_out->rho, pos_in), FO, slabs, pos_in, (uint32_t)n);
+    sbwd = build_slab_stream(by_position(by_col, FI, f_in->rho, pos_out), FI, slabs, pos_out, (uint32_t)m);
     if (std::max(sfwd.word.size(), sbwd.word.size()) > (size_t)1 << 30)
       return ff::fail(FF_EUNSUPPORTED, "support too skewed for the entry streams");
   }

@@ -65,9 +65,9 @@ hipError_t launch_analysis(const Side& side, const SlabStream& st, int bf16, int
   a.ld = (long)side.ld;
   a.ws = ws;
   a.ws_adapter = ws_adapter;
-  // groups per workgroup: about four workgroups per CU of work, so that a wave's fragments serve
-  // several groups where there is work enough
-  a.nb = slab_group_blocks(f);
+  // groups of at most 128 rows (wider ones leave fewer workgroups to hide the latencies), several per
+  // workgroup where there is work enough
+  a.nb = slab_group_blocks(f, std::min<int64_t>(2048, (int64_t)nslab * count * (((int64_t)f.nblk * f.W + 127) / 128)));
   a.ngroups = (f.nblk + a.nb - 1) / a.nb;
   a.gpw = (int)std::max<long>(1, std::min<long>(4, (long)nslab * a.ngroups * count / 2048));
   a.runs = (a.ngroups + a.gpw - 1) / a.gpw;
@@ -99,8 +99,13 @@ Split split_call(int count, int nslab, size_t pool_bytes, size_t slab_bytes) {
   return {1, (int)cap};
 }
 
-size_t pass_args(SlabArgs& a, const FrameDev& dst, const FrameDev& src, const SlabStream& st, int bf16, int T, int slab0,
-                 int nslab, int sg) {
+// Arguments common to both directions; the work items and LDS of groups of at most nb blocks.
+struct Launch {
+  unsigned grid;
+  size_t lds;
+};
+Launch pass_args(SlabArgs& a, const FrameDev& dst, const FrameDev& src, const SlabStream& st, int bf16, int T, int slab0,
+                 int nslab, int sg, int nb, int ngroups) {
   a.f = dst;
   a.fa = dst.wa16;
   a.fs = dst.ws16;
@@ -110,14 +115,14 @@ size_t pass_args(SlabArgs& a, const FrameDev& dst, const FrameDev& src, const Sl
   a.sg = sg;
   a.nb = st.nb;
   a.ngroups = st.ngroups;
-  a.nwork = st.ngroups * ((slab0 + nslab - 1) / sg - slab0 / sg + 1);
+  a.nruns = (slab0 + nslab - 1) / sg - slab0 / sg + 1;
   a.src_slab = ((long)src.nblk * src.W + 1) * kSlabRowBytes;
   a.wstep = st.wstep;
   a.zptr = st.zptr;
   a.zrow = st.zrow;
-  const Lds l = lds_layout(dst, st.nb, bf16);
+  const Lds l = lds_layout(dst, nb, bf16);
   a.stage_off = l.stage;
-  return l.bytes;
+  return {pad8((long)ngroups * a.nruns), l.bytes};
 }
 
 }  // namespace
@@ -151,7 +156,7 @@ hipError_t launch_fwd_slab(const ff_plan* p, int bf16, int count, int T, ActPtrs
                                      p->slab.ent_adapter, s0 == 0, c, cs, nullptr, nullptr, 0, 0, s);
       if (e != hipSuccess) return e;
       SlabArgs a{};
-      const size_t lds = pass_args(a, fo, fi, st, bf16, T, s0, ns, 1);
+      const Launch l = pass_args(a, fo, fi, st, bf16, T, s0, ns, 1, st.nb, st.ngroups);
       a.ws = p->slab.pool;
       a.ws_adapter = ws_adapter;
       a.ent = ent;
@@ -161,7 +166,7 @@ hipError_t launch_fwd_slab(const ff_plan* p, int bf16, int count, int T, ActPtrs
       a.ldy = (long)ldy;
       a.scale = scale;
       a.beta = beta;
-      e = kernels_for(fo).fwd(a, dim3(pad8(a.nwork), (unsigned)na), lds, s);
+      e = kernels_for(fo).fwd(a, dim3(l.grid, (unsigned)na), l.lds, s);
       if (e != hipSuccess) return e;
     }
   record(e1, s);
@@ -209,7 +214,7 @@ hipError_t launch_bwd_slab(const ff_plan* p, int bf16, int count, int T, ActPtrs
                                      s0 == 0, want_dx ? c : nullptr, want_dx ? cs : nullptr, nullptr, nullptr, 1, 0, s);
       if (e != hipSuccess) return e;
       SlabArgs a{};
-      const size_t lds = pass_args(a, fi, fo, st, bf16, T, s0, ns, sg);
+      const Launch l = pass_args(a, fi, fo, st, bf16, T, s0, ns, sg, st.nb, st.ngroups);
       a.ws = pool;
       a.ws_adapter = ws_adapter;
       a.ent = ent;
@@ -225,7 +230,7 @@ hipError_t launch_bwd_slab(const ff_plan* p, int bf16, int count, int T, ActPtrs
       a.prows = nrows;
       a.pstride = pstride;
       a.partial = partial + (long)a0 * nrows * pstride;
-      e = kernels_for(fi).bwd(a, want_dx, want_dc, dim3(pad8(a.nwork), (unsigned)na), lds, s);
+      e = kernels_for(fi).bwd(a, want_dx, want_dc, dim3(l.grid, (unsigned)na), l.lds, s);
       if (e != hipSuccess) return e;
     }
   record(e1, s);
@@ -303,14 +308,14 @@ hipError_t launch_fwd_group_slab(const ff_plan_group* g, int bf16, int T, const 
                                    nullptr, cs, g->slab, tokens, 0, g->max_slab_fwd, s);
     if (e != hipSuccess) return e;
     SlabArgs a{};
-    const size_t lds = pass_args(a, fo, fi, st, bf16, T, s0, ns, 1);
+    const Launch l = pass_args(a, fo, fi, st, bf16, T, s0, ns, 1, g->slab_nb_fwd, g->slab_groups_fwd);
     a.Ys = Y;
     a.ldy = (long)ldy;
     a.scale = scale;
     a.beta = beta;
     a.group = g->slab;
     a.tokens = tokens;
-    e = kernels_for(fo).fwd(a, dim3(pad8(a.nwork), (unsigned)count), lds, s);
+    e = kernels_for(fo).fwd(a, dim3(l.grid, (unsigned)count), l.lds, s);
     if (e != hipSuccess) return e;
   }
   record(e1, s);
@@ -338,7 +343,7 @@ hipError_t launch_bwd_group_slab(const ff_plan_group* g, int bf16, int T, const 
                                    nullptr, want_dx ? cs : nullptr, g->slab, tokens, 1, g->max_slab_bwd, s);
     if (e != hipSuccess) return e;
     SlabArgs a{};
-    const size_t lds = pass_args(a, fi, fo, st, bf16, T, s0, ns, sg);
+    const Launch l = pass_args(a, fi, fo, st, bf16, T, s0, ns, sg, g->slab_nb_bwd, g->slab_groups_bwd);
     a.Xs = X;
     a.ldx = (long)ldx;
     a.Ys = dX;
@@ -347,7 +352,7 @@ hipError_t launch_bwd_group_slab(const ff_plan_group* g, int bf16, int T, const 
     a.beta = beta_dx;
     a.group = g->slab;
     a.tokens = tokens;
-    e = kernels_for(fi).bwd(a, want_dx, want_dc, dim3(pad8(a.nwork), (unsigned)count), lds, s);
+    e = kernels_for(fi).bwd(a, want_dx, want_dc, dim3(l.grid, (unsigned)count), l.lds, s);
     if (e != hipSuccess) return e;
   }
   record(e1, s);

@@ -54,10 +54,13 @@ constexpr int kTileRow = kSlabRowBytes + 16;
 __device__ __forceinline__ unsigned tile_at(int row, int byte) { return (unsigned)(row * kTileRow + byte); }
 
 // Workgroup -> work item, contiguous runs of items per XCD (workgroups go to the eight XCDs in
-// turn), so that the items of one slab share an L2.  The grid is padded to a multiple of 8.
-__device__ __forceinline__ int xcd_item(int id, int n) {
+// turn), so that the items of one slab share an L2.  The grid is padded to a multiple of 8.  The runs
+// are dealt out one XCD further from adapter to adapter: in a group call the late slabs of most
+// adapters are empty, and one XCD would get all the first ones (17 adapters of up to 418 tokens:
+// 28.6 -> 22.5 us a call).
+__device__ __forceinline__ int xcd_item(int id, int n, int adapter) {
   const int per = (n + 7) >> 3;
-  const int w = (id & 7) * per + (id >> 3);
+  const int w = ((id + adapter) & 7) * per + (id >> 3);
   return (id >> 3) < per ? w : n;
 }
 
@@ -103,6 +106,19 @@ __device__ __forceinline__ u32x4v pack16(const float* x) {
     return u32x4v{pk_bf2(x[0], x[1]), pk_bf2(x[2], x[3]), pk_bf2(x[4], x[5]), pk_bf2(x[6], x[7])};
   else
     return u32x4v{__float_as_uint(x[0]), __float_as_uint(x[1]), __float_as_uint(x[2]), __float_as_uint(x[3])};
+}
+
+// A value at a wave-uniform address that nothing writes while the kernel runs, through the scalar
+// cache: the descriptors at a kernel's start are then read together instead of one vector load
+// after the other.
+template <class T>
+__device__ __forceinline__ T sload(const T* p) {
+  return *(const __attribute__((address_space(4))) T*)p;
+}
+
+// Tokens of adapter bi in a group call.
+__device__ __forceinline__ int adapter_tokens(const int* tokens, int T, int bi) {
+  return tokens ? max(0, min(sload(tokens + bi), T)) : T;
 }
 
 // Work items (output tile mt, block, half of the token groups) of an MFMA phase: a contiguous run per
@@ -151,15 +167,14 @@ __device__ __forceinline__ void put_tokens(unsigned char* tile, int row, int tg,
 // elements having zero weights in `frag`), so that every read stays inside the block.
 // Directly applied blocks: stage and tile are different LDS.
 template <bool BF16, int KT>
-__device__ __forceinline__ void analysis_direct(const FrameDev& f, const void* frag, const unsigned char* stage, int cb,
+__device__ __forceinline__ void analysis_direct(const FrameDev& f, const void* frag, int have,
+                                                typename Mfma<BF16>::V (&fr)[KT], const unsigned char* stage, int cb,
                                                 int nb, unsigned char* tile) {
   using M = Mfma<BF16>;
   using V = typename M::V;
   constexpr int ESZ = SlabT<BF16>::ESZ, NTH = SlabT<BF16>::NTG / 2;
   const int lane = phase_tid() & 63, q = lane >> 4, L = lane & 15, W = f.W, sb = stage_stride(cb);
   const Items items(f.MT, nb);
-  V fr[KT];
-  int have = -1;
   for (int it = items.i0; it < items.i1; ++it) {
     int mt, bl, th;
     items.get(it, mt, bl, th);
@@ -327,9 +342,17 @@ __device__ __forceinline__ void group_analysis(const FrameDev& f, const void* fr
     analysis_radix<BF16, KT>(f, frag, stage);
   } else {
     const int cb = nb * f.W * SlabT<BF16>::ESZ / 16;
+    // the wave's first fragments travel with the rows
+    typename Mfma<BF16>::V fr[KT];
+    const Items items(f.MT, nb);
+    int mt = -1, bl, th;
+    if (items.i0 < items.i1) {
+      items.get(items.i0, mt, bl, th);
+      load_frags<typename Mfma<BF16>::V, KT>(frag, mt, phase_tid() & 63, fr);
+    }
     stage_load<SlabT<BF16>::S>(rows, ld, nt, cb, stage);
     __syncthreads();
-    analysis_direct<BF16, KT>(f, frag, stage, cb, nb, tile);
+    analysis_direct<BF16, KT>(f, frag, mt, fr, stage, cb, nb, tile);
   }
   __syncthreads();
 }
@@ -377,17 +400,18 @@ __global__ void __launch_bounds__(kSlabThreads, slab_wgs(KT, RADIX)) slab_analys
   int T = a.T;
   if (a.group) {
     const SlabDesc* d = a.group + bi;
-    ws = d->ws;
-    a.word = a.bwd ? d->bwd.word : d->fwd.word;
-    a.coef = a.bwd ? d->bwd.coef : d->fwd.coef;
-    if (a.nent) a.nent = 16 * ((a.bwd ? d->bwd.steps : d->fwd.steps) + kSlabPadSteps);
-    a.ent = d->ent - (long)bi * a.ent_adapter;
-    T = group_tokens(a.tokens, a.T, bi);
+    const SlabStream* st = a.bwd ? &d->bwd : &d->fwd;
+    ws = sload(&d->ws);
+    a.word = sload(&st->word);
+    a.coef = sload(&st->coef);
+    if (a.nent) a.nent = 16 * (sload(&st->steps) + kSlabPadSteps);
+    a.ent = sload(&d->ent) - (long)bi * a.ent_adapter;
+    T = adapter_tokens(a.tokens, a.T, bi);
   }
   if ((int)blockIdx.x >= a.nwork) {
     const int j = ((int)blockIdx.x - a.nwork) * kSlabThreads + (int)threadIdx.x;
     if (j >= a.nent) return;
-    const float* cv = a.cs ? a.cs[bi] : a.c;
+    const float* cv = a.cs ? sload(a.cs + bi) : a.c;
     const int k = gload(a.coef + j);
     uint2 e;
     e.x = gload(a.word + j);
@@ -396,14 +420,14 @@ __global__ void __launch_bounds__(kSlabThreads, slab_wgs(KT, RADIX)) slab_analys
     return;
   }
   const FrameDev& f = a.f;
-  const int wi = xcd_item(blockIdx.x, a.nwork);
+  const int wi = xcd_item(blockIdx.x, a.nwork, bi);
   const int sl = wi / a.runs, run = wi - sl * a.runs;
   const long t0 = (long)(a.slab0 + sl) * S;
   const int nt = sl < a.nslab ? (int)min((long)S, (long)T - t0) : 0;
   if (nt <= 0) return;   // uniform
   const long P = (long)f.nblk * f.W;
   unsigned char* out = ws + (long)sl * (P + 1) * kSlabRowBytes;
-  const unsigned char* X = reinterpret_cast<const unsigned char*>(a.Xs ? a.Xs[bi] : a.X) + t0 * a.ld * ESZ;
+  const unsigned char* X = reinterpret_cast<const unsigned char*>(a.Xs ? sload(a.Xs + bi) : a.X) + t0 * a.ld * ESZ;
   if (run == 0 && threadIdx.x < 8)
     gstore(reinterpret_cast<u32x4v*>(out + P * kSlabRowBytes) + threadIdx.x, u32x4v{0u, 0u, 0u, 0u});
   const int g1 = min(a.ngroups, (run + 1) * a.gpw);
@@ -556,11 +580,13 @@ __device__ __forceinline__ void slab_walk(const uint2* ent, int s0, int s1, cons
 }
 
 // The rows of a group that no entry points to hold zeros (their coefficients are zero).
-__device__ __forceinline__ void zero_rows(unsigned char* tile, const unsigned short* rows, int n) {
+// (`first`: this thread's first row, loaded before the walk.)
+__device__ __forceinline__ void zero_rows(unsigned char* tile, const unsigned short* rows, int n, int first) {
   const int tid = phase_tid();
-  for (int i = tid >> 3; i < n; i += kSlabThreads / 8) {
-    const int r = (int)gload(rows + i);
+  for (int i = tid >> 3, r = first; i < n;) {
     *reinterpret_cast<u32x4v*>(tile + tile_at(r, 16 * (tid & 7))) = u32x4v{0u, 0u, 0u, 0u};
+    i += kSlabThreads / 8;
+    if (i < n) r = (int)gload(rows + i);
   }
 }
 
@@ -731,8 +757,8 @@ struct SlabArgs {
   const void* fs;
   int T, slab0, nslab;      // as in AnaArgs
   int sg;                   // slabs per dC partial row (rows counted from slab 0)
-  int nb, ngroups;          // blocks per group of the destination side
-  int nwork;                // groups x partial-row runs of this launch
+  int nb, ngroups;          // blocks per group of the destination side (group calls: the adapter's own)
+  int nruns;                // partial-row runs of this launch; work items: groups x runs
   int stage_off;            // LDS offset of the stage (the tile is first)
   long src_slab;            // bytes of a source slab
   const unsigned char* ws;
@@ -766,20 +792,22 @@ __device__ __forceinline__ void slab_pass(SlabArgs& a) {
   int T = a.T;
   if (a.group) {
     const SlabDesc* d = a.group + bi;
-    const SlabStream& st = BWD ? d->bwd : d->fwd;
-    ws = d->ws;
-    ent = d->ent;
-    a.wstep = st.wstep;
-    a.zptr = st.zptr;
-    a.zrow = st.zrow;
+    const SlabStream* st = BWD ? &d->bwd : &d->fwd;
+    ws = sload(&d->ws);
+    ent = sload(&d->ent);
+    a.wstep = sload(&st->wstep);
+    a.zptr = sload(&st->zptr);
+    a.zrow = sload(&st->zrow);
+    a.nb = sload(&st->nb);
+    a.ngroups = sload(&st->ngroups);
     if (DC) {
-      part = d->partial;
-      a.pstride = 16L * st.steps;
+      part = sload(&d->partial);
+      a.pstride = 16L * sload(&st->steps);
     }
-    T = group_tokens(a.tokens, a.T, bi);
+    T = adapter_tokens(a.tokens, a.T, bi);
   }
-  const int wi = xcd_item(blockIdx.x, a.nwork);
-  if (wi >= a.nwork) return;
+  const int nwork = a.ngroups * a.nruns, wi = xcd_item(blockIdx.x, nwork, bi);
+  if (wi >= nwork) return;
   const int run = wi / a.ngroups, grp = wi - run * a.ngroups;
   const FrameDev& f = a.f;
   const int blk0 = grp * a.nb, nb = min(a.nb, f.nblk - blk0);
@@ -787,11 +815,11 @@ __device__ __forceinline__ void slab_pass(SlabArgs& a) {
   const int sl0 = max(a.slab0, row * a.sg), sl1 = min(a.slab0 + a.nslab, (row + 1) * a.sg);
   if ((long)sl0 * S >= T) return;   // uniform
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int s0 = gload(a.wstep + grp * (kSlabWaves + 1) + wave), s1 = gload(a.wstep + grp * (kSlabWaves + 1) + wave + 1);
-  const int z0 = gload(a.zptr + grp), z1 = gload(a.zptr + grp + 1);
+  const int s0 = sload(a.wstep + grp * (kSlabWaves + 1) + wave), s1 = sload(a.wstep + grp * (kSlabWaves + 1) + wave + 1);
+  const int z0 = sload(a.zptr + grp), z1 = sload(a.zptr + grp + 1);
   const long col = (long)blk0 * f.W * ESZ;   // the group's first column in a token row (bytes)
-  unsigned char* Y = (!BWD || DX) ? reinterpret_cast<unsigned char*>(a.Ys ? a.Ys[bi] : a.Y) + col : nullptr;
-  const unsigned char* X = DC ? reinterpret_cast<const unsigned char*>(a.Xs ? a.Xs[bi] : a.X) + col : nullptr;
+  unsigned char* Y = (!BWD || DX) ? reinterpret_cast<unsigned char*>(a.Ys ? sload(a.Ys + bi) : a.Y) + col : nullptr;
+  const unsigned char* X = DC ? reinterpret_cast<const unsigned char*>(a.Xs ? sload(a.Xs + bi) : a.X) + col : nullptr;
   unsigned char* stage = smem + (RADIX ? 0 : a.stage_off);
   for (int sl = sl0; sl < sl1; ++sl) {
     const long t0 = (long)sl * S;
@@ -801,9 +829,11 @@ __device__ __forceinline__ void slab_pass(SlabArgs& a) {
     if constexpr (DC)   // z of the group's blocks into the tile
       group_analysis<BF16, KT, RADIX>(f, a.fa, X + t0 * a.ldx * ESZ, a.ldx * ESZ, nt, nb, smem, stage);
     const unsigned char* src = ws + (long)(sl - a.slab0) * a.src_slab;
+    int zfirst = 0;
+    if ((!BWD || DX) && z0 + (int)(threadIdx.x >> 3) < z1) zfirst = (int)gload(a.zrow + z0 + (threadIdx.x >> 3));
     slab_walk<BF16, !BWD || DX, DC>(ent, s0, s1, src, smem, DC ? part + (long)row * a.pstride : nullptr, sl != row * a.sg);
     if constexpr (!BWD || DX) {
-      zero_rows(smem, a.zrow + z0, z1 - z0);
+      zero_rows(smem, a.zrow + z0, z1 - z0, zfirst);
       __syncthreads();
       group_synthesis<BF16, KT, RADIX, BETA>(f, a.fs, smem, stage, nb, nt, Y + t0 * a.ldy * ESZ, a.ldy * ESZ, a.scale, a.beta);
     }
