@@ -189,12 +189,12 @@ struct SlabStream {
   const int* zptr;              // [groups + 1] into zrow
   const unsigned short* zrow;   // rows of the group without entries
   int steps;
-  int nb, ngroups;              // blocks per group, groups of the destination side
+  int nb, ngroups;              // blocks (multi-stage frames: rows) per group, groups of the destination side
 };
 struct SlabPlanDev {
   int enabled = 0;
   SlabStream fwd{}, bwd{};
-  unsigned char* pool = nullptr;   // slabs of one side
+  unsigned char* pool = nullptr;   // slabs of one side (of both where a frame is multi-stage)
   size_t pool_bytes = 0;
   uint2* ent = nullptr;            // [batch][ent_adapter]: entry words with a call's coefficients
   long ent_adapter = 0;
@@ -210,10 +210,15 @@ inline int slab_group_blocks(const FrameDev& f, int64_t units) {
   const int nb = rows / f.W;
   return nb < 1 ? 1 : nb < f.nblk ? nb : f.nblk;
 }
-// Frames the slab kernels take: blocks applied directly or in one radix-4 stage.
+// The same for blocks applied in several stages, whose rows are gathered without a tile (rows).  The
+// walks of few groups are spread further.
+inline int slab_ms_group_rows(int64_t units) { return units <= 512 ? 64 : 256; }
+// Frames whose groups pass through an LDS tile: blocks applied directly or in one radix-4 stage.
 inline bool slab_frame(const FrameDev& f) {
   return (f.radix == 1 && f.nst == 0 && f.W <= 128) || (f.radix == 4 && f.nst == 1 && f.W2 <= 128);
 }
+// Frames in several stages: both sides' coefficients pass through the workspace (slab_ms.hip).
+inline bool slab_ms_frame(const FrameDev& f) { return f.nst >= 2; }
 
 // One adapter's view of its plan inside a plan group (ff_plan_group): the tables and the
 // workspace (batch slot 0 of the plan's own) that the group kernels read per adapter.

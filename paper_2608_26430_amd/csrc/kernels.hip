@@ -425,8 +425,7 @@ void record(hipEvent_t ev, hipStream_t s) {
 hipError_t configure_kernels() {
   static hipError_t once = [] {
     hipError_t e = hipSuccess;
-    for (const hipError_t r : {gen::configure_fwd_bf16(), gen::configure_fwd_f32(), gen::configure_bwd_bf16(),
-                               gen::configure_bwd_f32(), configure_slab()})
+    for (const hipError_t r : {gen::configure_fwd_f32(), gen::configure_bwd_f32(), configure_slab()})
       if (r != hipSuccess) e = r;
     return e;
   }();
@@ -478,6 +477,7 @@ hipError_t launch_fwd(const ff_plan* p, int bf16, int count, int T, ActPtrs X, i
   if (bf16 && p->fast.enabled) return launch_fwd128(p, count, T, X, ldx, c, cs, scale, beta, Y, ldy, c_saved, s);
   if (bf16 && p->slab.enabled)
     return launch_fwd_slab(p, bf16, count, T, X, ldx, c, cs, scale, beta, Y, ldy, s);
+  if (bf16) return hipErrorInvalidValue;   // (not reached: every other bf16 plan takes the slab kernels)
   FwdArgs a{};
   a.fin = p->fin->dev;
   a.fout = p->fout->dev;
@@ -511,7 +511,7 @@ hipError_t launch_fwd(const ff_plan* p, int bf16, int count, int T, ActPtrs X, i
   take_timing_events(&e0, &e1);
   record(e0, s);
   const size_t lds = p->gen_lds_bytes[bf16];
-  const hipError_t e = bf16 ? gen::launch_fwd_bf16(a, grid, lds, s) : gen::launch_fwd_f32(a, grid, lds, s);
+  const hipError_t e = gen::launch_fwd_f32(a, grid, lds, s);
   record(e1, s);
   return e != hipSuccess ? e : hipGetLastError();
 }
@@ -544,6 +544,7 @@ hipError_t launch_bwd(const ff_plan* p, int bf16, int count, int T, ActPtrs X, i
   if (bf16 && p->slab.enabled)
     return launch_bwd_slab(p, bf16, count, T, X, ldx, G, ldg, c, cs, scale, beta_dx, dX, lddx, want_dx, accumulate_dc,
                            dC, dCs, want_dc, s, ws);
+  if (bf16) return hipErrorInvalidValue;   // (not reached: every other bf16 plan takes the slab kernels)
   BwdArgs a{};
   a.fin = p->fin->dev;
   a.fout = p->fout->dev;
@@ -593,7 +594,7 @@ hipError_t launch_bwd(const ff_plan* p, int bf16, int count, int T, ActPtrs X, i
     const dim3 grid((unsigned)nwg, (unsigned)count);
     record(e0, s);
     const size_t lds = p->gen_lds_bytes[bf16];
-    const hipError_t eb = bf16 ? gen::launch_bwd_bf16(a, grid, lds, s) : gen::launch_bwd_f32(a, grid, lds, s);
+    const hipError_t eb = gen::launch_bwd_f32(a, grid, lds, s);
     record(e1, s);
     if (eb != hipSuccess) return eb;
     const hipError_t e = hipGetLastError();
@@ -612,6 +613,7 @@ hipError_t launch_fwd_group(const ff_plan_group* g, int bf16, int T, const int* 
   if (bf16 && p->fast.enabled) return launch_fwd128_group(g, T, tokens, X, ldx, cs, scale, beta, Y, ldy, s);
   if (bf16 && p->slab.enabled)
     return launch_fwd_group_slab(g, bf16, T, tokens, X, ldx, cs, scale, beta, Y, ldy, s);
+  if (bf16) return hipErrorInvalidValue;   // (not reached: every other bf16 plan takes the slab kernels)
   const unsigned count = (unsigned)g->count;
   FwdArgs a{};
   a.fin = p->fin->dev;
@@ -642,7 +644,7 @@ hipError_t launch_fwd_group(const ff_plan_group* g, int bf16, int T, const int* 
   take_timing_events(&e0, &e1);
   record(e0, s);
   const size_t lds = p->gen_lds_bytes[bf16];
-  const hipError_t e = bf16 ? gen::launch_fwd_bf16(a, grid, lds, s) : gen::launch_fwd_f32(a, grid, lds, s);
+  const hipError_t e = gen::launch_fwd_f32(a, grid, lds, s);
   record(e1, s);
   return e != hipSuccess ? e : hipGetLastError();
 }
@@ -658,6 +660,7 @@ hipError_t launch_bwd_group(const ff_plan_group* g, int bf16, int T, const int* 
   if (bf16 && p->slab.enabled)
     return launch_bwd_group_slab(g, bf16, T, tokens, X, ldx, G, ldg, cs, scale, beta_dx, dX, lddx, want_dx,
                                  accumulate_dc, dCs, want_dc, s);
+  if (bf16) return hipErrorInvalidValue;   // (not reached: every other bf16 plan takes the slab kernels)
   const unsigned count = (unsigned)g->count;
   BwdArgs a{};
   a.fin = p->fin->dev;
@@ -694,8 +697,7 @@ hipError_t launch_bwd_group(const ff_plan_group* g, int bf16, int T, const int* 
   record(e0, s);
   if (nwg > 0) {   // (no tokens: the reduction below writes zeros)
     const size_t lds = p->gen_lds_bytes[bf16];
-    const hipError_t eb = bf16 ? gen::launch_bwd_bf16(a, dim3((unsigned)nwg, count), lds, s)
-                               : gen::launch_bwd_f32(a, dim3((unsigned)nwg, count), lds, s);
+    const hipError_t eb = gen::launch_bwd_f32(a, dim3((unsigned)nwg, count), lds, s);
     if (eb != hipSuccess) return eb;
   }
   record(e1, s);

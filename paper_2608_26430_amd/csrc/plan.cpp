@@ -283,13 +283,15 @@ template <class Src>
 SlabStreamHost build_slab_stream(const std::vector<std::vector<int>>& lists, const ff::FrameDev& dst, int64_t slabs,
                                  Src src, uint32_t zero_src) {
   SlabStreamHost h;
-  h.nb = ff::slab_group_blocks(dst, slabs * ((int64_t)dst.nblk * dst.W + 127) / 128);
-  h.ngroups = (dst.nblk + h.nb - 1) / h.nb;
+  const int64_t units = slabs * ((int64_t)dst.nblk * dst.W + 127) / 128, P = (int64_t)dst.nblk * dst.W;
+  const bool ms = ff::slab_ms_frame(dst);
+  h.nb = ms ? ff::slab_ms_group_rows(units) : ff::slab_group_blocks(dst, units);
+  const int64_t per = ms ? h.nb : (int64_t)h.nb * dst.W;   // rows of a group
+  h.ngroups = (int)((P + per - 1) / per);
   h.zptr.push_back(0);
   for (int g = 0; g < h.ngroups; ++g) {
-    const int64_t p0 = (int64_t)g * h.nb * dst.W, p1 = std::min<int64_t>(p0 + (int64_t)h.nb * dst.W,
-                                                                         (int64_t)dst.nblk * dst.W);
-    const uint32_t dump = (uint32_t)(h.nb * dst.W);   // tile row of lanes that hold no row
+    const int64_t p0 = g * per, p1 = std::min(p0 + per, P);
+    const uint32_t dump = (uint32_t)per;   // the row of lanes that hold none
     std::vector<int> rows;
     for (int64_t r = p0; r < p1; ++r) {
       if (lists[r].empty())
@@ -504,15 +506,17 @@ extern "C" ff_status ff_plan_create(const ff_frame* f_in, const ff_frame* f_out,
     }
   }
   // the slab kernels' streams (bf16 calls): rows of C into output positions, columns into input ones
-  const bool slab = ff::slab_frame(FI) && ff::slab_frame(FO) && !f_in->lifted && !f_out->lifted &&
-                    n < (int64_t)ff::kSlabSrcMask && m < (int64_t)ff::kSlabSrcMask;
+  const bool slab_ms = ff::slab_ms_frame(FI) || ff::slab_ms_frame(FO);
+  const bool slab = (ff::slab_frame(FI) || ff::slab_ms_frame(FI)) && (ff::slab_frame(FO) || ff::slab_ms_frame(FO)) &&
+                    !f_in->lifted && !f_out->lifted && n < (int64_t)ff::kSlabSrcMask && m < (int64_t)ff::kSlabSrcMask;
   SlabStreamHost sfwd, sbwd;
   if (slab) {
-    // position of a coefficient: whole blocks in order, a factored block's four columns in turn
+    // position of a coefficient: whole blocks in order, a factored block's columns in turn
     auto position = [](const ff::FrameDev& f, const Loc& l) {
       if (f.radix == 1) return l.blk * f.W + l.local;
-      const int i = l.local >> 1;
-      return l.blk * f.W + (i & 3) * f.W2 + 2 * (i >> 2) + (l.local & 1);
+      int i = l.local >> 1, col = 0;
+      for (int t = 0; t < f.nst; ++t, i >>= 2) col = 4 * col + (i & 3);
+      return l.blk * f.W + col * f.W2 + 2 * i + (l.local & 1);
     };
     auto by_position = [&](const std::vector<std::vector<int>>& by, const ff::FrameDev& f, int64_t rho, auto other) {
       std::vector<std::vector<int>> out(by.size());
@@ -710,7 +714,8 @@ extern "C" ff_status ff_plan_create(const ff_frame* f_in, const ff_frame* f_out,
     slab_rows = (int)std::max<int64_t>(1, std::min<int64_t>({nslabs, (int64_t)ff::kSlabMaxRows,
                                                              (int64_t)(ff::kSlabPartialBytes / row_bytes)}));
     partial_elems = std::max(partial_elems, (size_t)max_batch * (size_t)slab_rows * (size_t)sbwd.steps * 16);
-    const size_t one = (size_t)(std::max(n, m) + 1) * ff::kSlabRowBytes;
+    // (a call through a multi-stage destination keeps both sides' slabs)
+    const size_t one = (size_t)(slab_ms ? n + m + 2 : std::max(n, m) + 1) * ff::kSlabRowBytes;
     const size_t cap = std::max<size_t>(ff::kSlabPoolBytes / one, 1);
     slab_pool = one * (size_t)std::min<int64_t>((int64_t)cap, nslabs * max_batch);
     slab_ent = std::max(sfwd.word.size(), sbwd.word.size());

@@ -54,6 +54,8 @@ hipError_t launch_analysis(const Side& side, const SlabStream& st, int bf16, int
                            const float* c, const float* const* cs, const SlabDesc* group, const int* tokens, int bwd,
                            int max_ent, hipStream_t s) {
   const FrameDev& f = *side.f;
+  const bool ms = slab_ms_frame(f);
+  const int threads = ms ? kMsThreads : kSlabThreads;
   AnaArgs a{};
   a.f = f;
   a.frag = f.wa16;
@@ -65,15 +67,6 @@ hipError_t launch_analysis(const Side& side, const SlabStream& st, int bf16, int
   a.ld = (long)side.ld;
   a.ws = ws;
   a.ws_adapter = ws_adapter;
-  // groups of at most 128 rows (wider ones leave fewer workgroups to hide the latencies), several per
-  // workgroup where there is work enough
-  a.nb = slab_group_blocks(f, std::min<int64_t>(2048, (int64_t)nslab * count * (((int64_t)f.nblk * f.W + 127) / 128)));
-  a.ngroups = (f.nblk + a.nb - 1) / a.nb;
-  a.gpw = (int)std::max<long>(1, std::min<long>(4, (long)nslab * a.ngroups * count / 2048));
-  a.runs = (a.ngroups + a.gpw - 1) / a.gpw;
-  a.nwork = (int)pad8((long)nslab * a.runs);
-  const Lds l = lds_layout(f, a.nb, bf16);
-  a.stage_off = l.stage;
   a.word = st.word;
   a.coef = st.coef;
   a.nent = entries ? (group ? max_ent : 16 * (st.steps + kSlabPadSteps)) : 0;
@@ -84,7 +77,20 @@ hipError_t launch_analysis(const Side& side, const SlabStream& st, int bf16, int
   a.group = group;
   a.tokens = tokens;
   a.bwd = bwd;
-  const unsigned nprep = pad8((a.nent + kSlabThreads - 1) / kSlabThreads);
+  const unsigned nprep = pad8((a.nent + threads - 1) / threads);
+  if (ms) {
+    a.nwork = (int)pad8((long)nslab * (slab_tokens(bf16) / kMsTok) * f.nblk);
+    return launch_ms_analysis(a, dim3((unsigned)a.nwork + nprep, (unsigned)count), s);
+  }
+  // groups of at most 128 rows (wider ones leave fewer workgroups to hide the latencies), several per
+  // workgroup where there is work enough
+  a.nb = slab_group_blocks(f, std::min<int64_t>(2048, (int64_t)nslab * count * (((int64_t)f.nblk * f.W + 127) / 128)));
+  a.ngroups = (f.nblk + a.nb - 1) / a.nb;
+  a.gpw = (int)std::max<long>(1, std::min<long>(4, (long)nslab * a.ngroups * count / 2048));
+  a.runs = (a.ngroups + a.gpw - 1) / a.gpw;
+  a.nwork = (int)pad8((long)nslab * a.runs);
+  const Lds l = lds_layout(f, a.nb, bf16);
+  a.stage_off = l.stage;
   return kernels_for(f).analysis(a, dim3((unsigned)a.nwork + nprep, (unsigned)count), l.bytes, s);
 }
 
@@ -102,7 +108,7 @@ Split split_call(int count, int nslab, size_t pool_bytes, size_t slab_bytes) {
 // Arguments common to both directions; the work items and LDS of groups of at most nb blocks.
 struct Launch {
   unsigned grid;
-  size_t lds;
+  size_t lds;   // (0: multi-stage)
 };
 Launch pass_args(SlabArgs& a, const FrameDev& dst, const FrameDev& src, const SlabStream& st, int bf16, int T, int slab0,
                  int nslab, int sg, int nb, int ngroups) {
@@ -120,9 +126,44 @@ Launch pass_args(SlabArgs& a, const FrameDev& dst, const FrameDev& src, const Sl
   a.wstep = st.wstep;
   a.zptr = st.zptr;
   a.zrow = st.zrow;
+  const unsigned grid = pad8((long)ngroups * a.nruns);
+  if (slab_ms_frame(dst)) return {grid, 0};
   const Lds l = lds_layout(dst, nb, bf16);
   a.stage_off = l.stage;
-  return {pad8((long)ngroups * a.nruns), l.bytes};
+  return {grid, l.bytes};
+}
+
+// Second pass of `count` adapters: a multi-stage destination is gathered into the workspace and then
+// synthesised.  A backward pass writes dX if dx and dC partial rows if dc.
+hipError_t launch_pass(const SlabArgs& a, const Launch& l, bool bwd, bool dx, bool dc, int count, hipStream_t s) {
+  const dim3 grid(l.grid, (unsigned)count);
+  if (!slab_ms_frame(a.f))
+    return bwd ? kernels_for(a.f).bwd(a, dx, dc, grid, l.lds, s) : kernels_for(a.f).fwd(a, grid, l.lds, s);
+  const hipError_t e = launch_ms_pass(a, bwd, dx, dc, grid, s);
+  if (e != hipSuccess || !dx) return e;
+  MsOutArgs o{};
+  o.f = a.f;
+  o.T = a.T;
+  o.slab0 = a.slab0;
+  o.nslab = a.nslab;
+  o.nwork = (int)pad8((long)a.nslab * (SlabT<true>::S / kMsTok) * a.f.nblk);
+  o.ws = a.wd;
+  o.ws_adapter = a.ws_adapter;
+  o.Y = a.Y;
+  o.Ys = a.Ys;
+  o.ldy = a.ldy;
+  o.scale = a.scale;
+  o.beta = a.beta;
+  o.group = a.group;
+  o.tokens = a.tokens;
+  return launch_ms_synthesis(o, dim3((unsigned)o.nwork, (unsigned)count), s);
+}
+
+// Bytes of one slab of a side.
+size_t side_bytes(const FrameDev& f) { return ((size_t)f.nblk * f.W + 1) * kSlabRowBytes; }
+// Bytes a call keeps per slab: the source side's, and a multi-stage destination's.
+size_t call_bytes(const FrameDev& src, const FrameDev& dst) {
+  return side_bytes(src) + (slab_ms_frame(dst) ? side_bytes(dst) : 0);
 }
 
 }  // namespace
@@ -133,7 +174,8 @@ hipError_t configure_slab() {
     const hipError_t r = l->configure();
     if (r != hipSuccess) e = r;
   }
-  return e;
+  const hipError_t r = configure_ms();
+  return r != hipSuccess ? r : e;
 }
 
 hipError_t launch_fwd_slab(const ff_plan* p, int bf16, int count, int T, ActPtrs X, int64_t ldx, const float* c,
@@ -144,7 +186,7 @@ hipError_t launch_fwd_slab(const ff_plan* p, int bf16, int count, int T, ActPtrs
   if (nslab == 0) return hipSuccess;
   const FrameDev &fi = p->fin->dev, &fo = p->fout->dev;
   const SlabStream& st = p->slab.fwd;
-  const size_t slab_bytes = ((size_t)fi.nblk * fi.W + 1) * kSlabRowBytes;
+  const size_t slab_bytes = call_bytes(fi, fo);
   const Split sp = split_call(count, nslab, p->slab.pool_bytes, slab_bytes);
   const long ws_adapter = (long)slab_bytes * sp.slabs;
   record(e0, s);
@@ -158,6 +200,7 @@ hipError_t launch_fwd_slab(const ff_plan* p, int bf16, int count, int T, ActPtrs
       SlabArgs a{};
       const Launch l = pass_args(a, fo, fi, st, bf16, T, s0, ns, 1, st.nb, st.ngroups);
       a.ws = p->slab.pool;
+      a.wd = p->slab.pool + (size_t)sp.slabs * side_bytes(fi);
       a.ws_adapter = ws_adapter;
       a.ent = ent;
       a.ent_adapter = p->slab.ent_adapter;
@@ -166,7 +209,7 @@ hipError_t launch_fwd_slab(const ff_plan* p, int bf16, int count, int T, ActPtrs
       a.ldy = (long)ldy;
       a.scale = scale;
       a.beta = beta;
-      e = kernels_for(fo).fwd(a, dim3(l.grid, (unsigned)na), l.lds, s);
+      e = launch_pass(a, l, false, true, false, na, s);
       if (e != hipSuccess) return e;
     }
   record(e1, s);
@@ -184,7 +227,7 @@ hipError_t launch_bwd_slab(const ff_plan* p, int bf16, int count, int T, ActPtrs
   const SlabStream& st = p->slab.bwd;
   int sg = 1, nrows = 0;
   partial_rows(T, S, p->slab.rows, &sg, &nrows);
-  const size_t slab_bytes = ((size_t)fo.nblk * fo.W + 1) * kSlabRowBytes;
+  const size_t slab_bytes = call_bytes(fo, fi);
   const long pstride = 16L * st.steps;
   unsigned char* pool = p->slab.pool;
   size_t pool_bytes = p->slab.pool_bytes;
@@ -213,9 +256,16 @@ hipError_t launch_bwd_slab(const ff_plan* p, int bf16, int count, int T, ActPtrs
       hipError_t e = launch_analysis({&fo, G, ldg}, st, bf16, na, a0, T, s0, ns, pool, ws_adapter, ent, p->slab.ent_adapter,
                                      s0 == 0, want_dx ? c : nullptr, want_dx ? cs : nullptr, nullptr, nullptr, 1, 0, s);
       if (e != hipSuccess) return e;
+      unsigned char* wd = pool + (size_t)sp.slabs * side_bytes(fo);
+      if (want_dc && slab_ms_frame(fi)) {
+        e = launch_analysis({&fi, X, ldx}, st, bf16, na, a0, T, s0, ns, wd, ws_adapter, nullptr, 0, false, nullptr, nullptr,
+                            nullptr, nullptr, 1, 0, s);
+        if (e != hipSuccess) return e;
+      }
       SlabArgs a{};
       const Launch l = pass_args(a, fi, fo, st, bf16, T, s0, ns, sg, st.nb, st.ngroups);
       a.ws = pool;
+      a.wd = wd;
       a.ws_adapter = ws_adapter;
       a.ent = ent;
       a.ent_adapter = p->slab.ent_adapter;
@@ -230,7 +280,7 @@ hipError_t launch_bwd_slab(const ff_plan* p, int bf16, int count, int T, ActPtrs
       a.prows = nrows;
       a.pstride = pstride;
       a.partial = partial + (long)a0 * nrows * pstride;
-      e = kernels_for(fi).bwd(a, want_dx, want_dc, dim3(l.grid, (unsigned)na), l.lds, s);
+      e = launch_pass(a, l, true, want_dx, want_dc, na, s);
       if (e != hipSuccess) return e;
     }
   record(e1, s);
@@ -299,7 +349,7 @@ hipError_t launch_fwd_group_slab(const ff_plan_group* g, int bf16, int T, const 
   if (nslab == 0) return hipSuccess;
   const FrameDev &fi = p->fin->dev, &fo = p->fout->dev;
   const SlabStream& st = p->slab.fwd;
-  const size_t slab_bytes = ((size_t)fi.nblk * fi.W + 1) * kSlabRowBytes;
+  const size_t slab_bytes = call_bytes(fi, fo);
   const Split sp = split_call(1, nslab, g->slab_pool, slab_bytes);   // every adapter in its plan's own pool
   record(e0, s);
   for (int s0 = 0; s0 < nslab; s0 += sp.slabs) {
@@ -309,13 +359,14 @@ hipError_t launch_fwd_group_slab(const ff_plan_group* g, int bf16, int T, const 
     if (e != hipSuccess) return e;
     SlabArgs a{};
     const Launch l = pass_args(a, fo, fi, st, bf16, T, s0, ns, 1, g->slab_nb_fwd, g->slab_groups_fwd);
+    a.ws_adapter = (long)((size_t)sp.slabs * side_bytes(fi));
     a.Ys = Y;
     a.ldy = (long)ldy;
     a.scale = scale;
     a.beta = beta;
     a.group = g->slab;
     a.tokens = tokens;
-    e = kernels_for(fo).fwd(a, dim3(l.grid, (unsigned)count), l.lds, s);
+    e = launch_pass(a, l, false, true, false, count, s);
     if (e != hipSuccess) return e;
   }
   record(e1, s);
@@ -334,7 +385,7 @@ hipError_t launch_bwd_group_slab(const ff_plan_group* g, int bf16, int T, const 
   const SlabStream& st = p->slab.bwd;
   int sg = 1, nrows = 0;
   partial_rows(T, S, g->slab_rows, &sg, &nrows);
-  const size_t slab_bytes = ((size_t)fo.nblk * fo.W + 1) * kSlabRowBytes;
+  const size_t slab_bytes = call_bytes(fo, fi);
   const Split sp = split_call(1, std::max(nslab, 1), g->slab_pool, slab_bytes);
   record(e0, s);
   for (int s0 = 0; s0 < nslab; s0 += sp.slabs) {
@@ -342,8 +393,15 @@ hipError_t launch_bwd_group_slab(const ff_plan_group* g, int bf16, int T, const 
     hipError_t e = launch_analysis({&fo, {nullptr, G}, ldg}, st, bf16, count, 0, T, s0, ns, nullptr, 0, nullptr, 0, s0 == 0,
                                    nullptr, want_dx ? cs : nullptr, g->slab, tokens, 1, g->max_slab_bwd, s);
     if (e != hipSuccess) return e;
+    const long wd = (long)((size_t)sp.slabs * side_bytes(fo));   // in each adapter's pool
+    if (want_dc && slab_ms_frame(fi)) {
+      e = launch_analysis({&fi, {nullptr, X}, ldx}, st, bf16, count, 0, T, s0, ns, nullptr, wd, nullptr, 0, false, nullptr,
+                          nullptr, g->slab, tokens, 1, 0, s);
+      if (e != hipSuccess) return e;
+    }
     SlabArgs a{};
     const Launch l = pass_args(a, fi, fo, st, bf16, T, s0, ns, sg, g->slab_nb_bwd, g->slab_groups_bwd);
+    a.ws_adapter = wd;
     a.Xs = X;
     a.ldx = (long)ldx;
     a.Ys = dX;
@@ -352,7 +410,7 @@ hipError_t launch_bwd_group_slab(const ff_plan_group* g, int bf16, int T, const 
     a.beta = beta_dx;
     a.group = g->slab;
     a.tokens = tokens;
-    e = kernels_for(fi).bwd(a, want_dx, want_dc, dim3(l.grid, (unsigned)count), l.lds, s);
+    e = launch_pass(a, l, true, want_dx, want_dc, count, s);
     if (e != hipSuccess) return e;
   }
   record(e1, s);

@@ -369,7 +369,7 @@ struct AnaArgs {
   const void* const* Xs;
   long ld;
   unsigned char* ws;     // [adapter][slab][P + 1][128 bytes]
-  long ws_adapter;       // bytes
+  long ws_adapter;       // bytes between adapters (group calls: offset in each adapter's pool)
   int nb, ngroups;       // blocks per group (a workgroup stages a group at a time)
   int gpw, runs;         // groups per workgroup, workgroups per slab
   int stage_off;         // LDS offset of the stage (the tile is first)
@@ -387,6 +387,28 @@ struct AnaArgs {
   int bwd;               // group calls: which stream's entries
 };
 
+// Group calls: adapter bi's entries, stream and pool into `a`; returns the pool.
+__device__ __forceinline__ unsigned char* group_entries(AnaArgs& a, int bi) {
+  const SlabDesc* d = a.group + bi;
+  const SlabStream* st = a.bwd ? &d->bwd : &d->fwd;
+  a.word = sload(&st->word);
+  a.coef = sload(&st->coef);
+  if (a.nent) a.nent = 16 * (sload(&st->steps) + kSlabPadSteps);
+  a.ent = sload(&d->ent) - (long)bi * a.ent_adapter;
+  return sload(&d->ws);
+}
+
+// Entry j of adapter bi's stream with this call's coefficient.
+__device__ __forceinline__ void copy_entry(const AnaArgs& a, int bi, int j) {
+  if (j >= a.nent) return;
+  const float* cv = a.cs ? sload(a.cs + bi) : a.c;
+  const int k = gload(a.coef + j);
+  uint2 e;
+  e.x = gload(a.word + j);
+  e.y = cv && k >= 0 ? __float_as_uint(gload(cv + k)) : 0u;
+  gstore(a.ent + (long)bi * a.ent_adapter + j, e);
+}
+
 // Workgroups per CU that the widest blocks of a kernel leave LDS for (two also where factored blocks'
 // results wait in fp32), which bounds its registers.
 constexpr int slab_wgs(int KT, bool RADIX, bool BETA = false) { return RADIX && (KT >= 4 || BETA) ? 2 : 3; }
@@ -399,24 +421,11 @@ __global__ void __launch_bounds__(kSlabThreads, slab_wgs(KT, RADIX)) slab_analys
   unsigned char* ws = a.ws + (long)bi * a.ws_adapter;
   int T = a.T;
   if (a.group) {
-    const SlabDesc* d = a.group + bi;
-    const SlabStream* st = a.bwd ? &d->bwd : &d->fwd;
-    ws = sload(&d->ws);
-    a.word = sload(&st->word);
-    a.coef = sload(&st->coef);
-    if (a.nent) a.nent = 16 * (sload(&st->steps) + kSlabPadSteps);
-    a.ent = sload(&d->ent) - (long)bi * a.ent_adapter;
+    ws = group_entries(a, bi) + a.ws_adapter;
     T = adapter_tokens(a.tokens, a.T, bi);
   }
   if ((int)blockIdx.x >= a.nwork) {
-    const int j = ((int)blockIdx.x - a.nwork) * kSlabThreads + (int)threadIdx.x;
-    if (j >= a.nent) return;
-    const float* cv = a.cs ? sload(a.cs + bi) : a.c;
-    const int k = gload(a.coef + j);
-    uint2 e;
-    e.x = gload(a.word + j);
-    e.y = cv && k >= 0 ? __float_as_uint(gload(cv + k)) : 0u;
-    gstore(a.ent + (long)bi * a.ent_adapter + j, e);
+    copy_entry(a, bi, ((int)blockIdx.x - a.nwork) * kSlabThreads + (int)threadIdx.x);
     return;
   }
   const FrameDev& f = a.f;
@@ -757,12 +766,13 @@ struct SlabArgs {
   const void* fs;
   int T, slab0, nslab;      // as in AnaArgs
   int sg;                   // slabs per dC partial row (rows counted from slab 0)
-  int nb, ngroups;          // blocks per group of the destination side (group calls: the adapter's own)
+  int nb, ngroups;          // as in SlabStream, of the destination side (group calls: the adapter's own)
   int nruns;                // partial-row runs of this launch; work items: groups x runs
   int stage_off;            // LDS offset of the stage (the tile is first)
   long src_slab;            // bytes of a source slab
   const unsigned char* ws;
-  long ws_adapter;
+  long ws_adapter;          // bytes between adapters (group calls: offset of wd in each adapter's pool)
+  unsigned char* wd;        // multi-stage frames: the destination slabs
   const uint2* ent;
   long ent_adapter;
   const int* wstep;         // [group][kSlabWaves + 1]
@@ -857,6 +867,26 @@ struct SlabLaunch {
   hipError_t (*bwd)(const SlabArgs&, bool dx, bool dc, dim3 grid, size_t lds, hipStream_t s);
   hipError_t (*configure)();
 };
+// Multi-stage frames (slab_ms.hip).
+constexpr int kMsThreads = 512, kMsWaves = kMsThreads / 64;
+constexpr int kMsTok = 16;   // tokens of a workgroup: one MFMA group
+struct MsOutArgs {
+  FrameDev f;
+  int T, slab0, nslab, nwork;
+  const unsigned char* ws;   // destination slabs
+  long ws_adapter;           // as in SlabArgs
+  void* Y;
+  void* const* Ys;
+  long ldy;
+  float scale, beta;
+  const SlabDesc* group;
+  const int* tokens;
+};
+hipError_t launch_ms_analysis(const AnaArgs& a, dim3 grid, hipStream_t s);
+hipError_t launch_ms_synthesis(const MsOutArgs& a, dim3 grid, hipStream_t s);
+hipError_t launch_ms_pass(const SlabArgs& a, bool bwd, bool dx, bool dc, dim3 grid, hipStream_t s);
+hipError_t configure_ms();
+
 const SlabLaunch& launch_bf16_direct();
 const SlabLaunch& launch_bf16_radix();
 
