@@ -1,7 +1,7 @@
 // Device code of the generic kernels (fwd_kernel, bwd_kernel) and their helpers, shared by the
 // translation units that instantiate them (gen_inst.hip, once per direction and kind of frame,
 // so that they compile in parallel), by kernels.hip and by the slab kernels (argument structs,
-// element helpers).  fp32 activations run here, and bf16 ones on frames in several radix-4 stages.
+// element helpers).  fp32 activations run here.
 #pragma once
 
 #include <algorithm>
@@ -322,13 +322,12 @@ __device__ __forceinline__ float2 cmulc(float2 a, float2 w) {
   return make_float2(fmaf(a.x, w.x, a.y * w.y), fmaf(a.y, w.x, -a.x * w.y));
 }
 
-// x / d for 0 <= x < 2^24 and 0 < d, with inv = 1 / d in fp32: the product is within one of the
-// quotient, which the two corrections make exact.
+// x / d for 0 <= x <= 2^21 and 0 < d <= 2^14, with inv = 1 / d in fp32: (x + 1/2) / d is at least
+// 1 / 2d from a whole number, more than the rounding of inv and of the product can move it.  (No
+// multiplication of whole numbers, whose 32-bit form runs at a quarter of the rate.)
 __device__ __forceinline__ int div_small(int x, int d, float inv) {
-  int q = (int)((float)x * inv);
-  q -= q * d > x;
-  q += (q + 1) * d <= x;
-  return q;
+  (void)d;
+  return (int)(((float)x + 0.5f) * inv);
 }
 
 // The twiddle factors of a single-stage factored frame, copied to LDS (the caller synchronizes).
@@ -450,15 +449,13 @@ __device__ __forceinline__ void radix4_synthesis(const FrameDev& f, const float2
 // frequency, lds_position), where the MFMA applies the dense DFT of size k2.  fp32 throughout; LDS
 // receives the activation type.  The synthesis runs the adjoints in reverse order.  A lane holds 32
 // of the 128 values of a three-stage residue, and four times the lanes are at work.
+// (wb: the lane's base twiddles)
 template <int S, int T, bool INV>
-__device__ __forceinline__ void msr_stage(float2 (&v)[1 << (2 * S - 2)], int bq, int k2,
+__device__ __forceinline__ void msr_stage(float2 (&v)[1 << (2 * S - 2)], const float2 (&wb)[3], int k2,
                                           const float2* __restrict__ twk) {
   constexpr int NL = 1 << (2 * S - 2);
   constexpr int st = 1 << (2 * (S - T) - 2);   // stride of digit a_T in m (T < S)
   constexpr int tws = 1 << (2 * (T - 1));      // w_{K_{T-1}} = w_k^(4^(T-1))
-  float2 wb[3];
-#pragma unroll
-  for (int a = 1; a < 4; ++a) wb[a - 1] = gload(twk + a * bq * tws);
 #pragma unroll
   for (int hi = 0; hi < NL / (4 * st); ++hi)
 #pragma unroll
@@ -491,14 +488,19 @@ __device__ __forceinline__ void msr_stage(float2 (&v)[1 << (2 * S - 2)], int bq,
     }
 }
 
+template <int S, int T, bool INV>
+__device__ __forceinline__ void msr_stage(float2 (&v)[1 << (2 * S - 2)], int bq, int k2,
+                                          const float2* __restrict__ twk) {
+  float2 wb[3];
+#pragma unroll
+  for (int a = 1; a < 4; ++a) wb[a - 1] = gload(twk + a * bq * (1 << (2 * (T - 1))));
+  msr_stage<S, T, INV>(v, wb, k2, twk);
+}
+
 // Stage S, local after the quad transpose: groups v[4 g .. 4 g + 3] over the lowest digit (n = b).
 template <int S, bool INV>
-__device__ __forceinline__ void msr_last_stage(float2 (&v)[1 << (2 * S - 2)], int b, const float2* __restrict__ twk) {
+__device__ __forceinline__ void msr_last_stage(float2 (&v)[1 << (2 * S - 2)], const float2 (&w)[3]) {
   constexpr int NL = 1 << (2 * S - 2);
-  constexpr int tws = 1 << (2 * (S - 1));
-  float2 w[3];
-#pragma unroll
-  for (int a = 1; a < 4; ++a) w[a - 1] = gload(twk + a * b * tws);
 #pragma unroll
   for (int g = 0; g < NL / 4; ++g) {
     float2* x = v + 4 * g;
@@ -517,6 +519,14 @@ __device__ __forceinline__ void msr_last_stage(float2 (&v)[1 << (2 * S - 2)], in
       x[3] = make_float2(d02.x + d13.y, d02.y - d13.x);
     }
   }
+}
+
+template <int S, bool INV>
+__device__ __forceinline__ void msr_last_stage(float2 (&v)[1 << (2 * S - 2)], int b, const float2* __restrict__ twk) {
+  float2 w[3];
+#pragma unroll
+  for (int a = 1; a < 4; ++a) w[a - 1] = gload(twk + a * b * (1 << (2 * (S - 1))));
+  msr_last_stage<S, INV>(v, w);
 }
 
 // One component of a register exchanged with lane q ^ D of the quad (DPP quad permutation).

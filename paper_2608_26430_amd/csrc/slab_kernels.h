@@ -79,8 +79,8 @@ __device__ __forceinline__ void stage_load(const unsigned char* src, long ld, in
     int at[kU];
 #pragma unroll
     for (int u = 0; u < kU; ++u) {
-      const int i = min(i0 + u * kSlabThreads, n - 1), t = div_small(i, cb, inv), c = i - t * cb;
-      at[u] = t * sb + 16 * c;
+      const int i = min(i0 + u * kSlabThreads, n - 1), t = div_small(i, cb, inv), c = i - __mul24(t, cb);
+      at[u] = __mul24(t, sb) + 16 * c;
       v[u] = gload(reinterpret_cast<const u32x4v*>(src + (long)min(t, nt - 1) * ld + 16 * c));
       if (nt < S && t >= nt) v[u] = u32x4v{0u, 0u, 0u, 0u};
     }
@@ -94,9 +94,9 @@ __device__ __forceinline__ void stage_store(const unsigned char* stage, int nt, 
   const int tid = phase_tid(), sb = stage_stride(cb), n = nt * cb;
   const float inv = 1.f / (float)cb;
   for (int i = tid; i < n; i += kSlabThreads) {
-    const int t = div_small(i, cb, inv), c = i - t * cb;
+    const int t = div_small(i, cb, inv), c = i - __mul24(t, cb);
     gstore(reinterpret_cast<u32x4v*>(dst + (long)t * ld + 16 * c),
-           *reinterpret_cast<const u32x4v*>(stage + t * sb + 16 * c));
+           *reinterpret_cast<const u32x4v*>(stage + __mul24(t, sb) + 16 * c));
   }
 }
 

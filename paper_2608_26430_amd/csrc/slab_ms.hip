@@ -14,7 +14,9 @@
 // What bounded the kernels this replaces (whole tokens of both sides in LDS, 9 tokens a tile): their
 // token rows were read and written in 4-byte words of neighbouring lanes 128 bytes apart, one cache
 // access each (2048 per 4096-wide token and pass).  4096 -> 4096 wide, rho = 2, 4096 tokens: a
-// training step 280 -> 175 us; 1024 wide: 74 -> 68 us.
+// training step 280 -> 163 us; 1024 wide: 74 -> 62 us.  Vector instructions bound what is left: the stages of
+// 16 tokens 4096 wide are 4 x 640 of them per wave, 9 of an analysis's 25 us (27.5 with the rows loaded
+// before the stages and 32-bit integer products, of a quarter of the rate, in the addresses).
 #include "slab_kernels.h"
 
 namespace ff {
@@ -36,38 +38,74 @@ struct MsTile {
   }
 };
 
-// The radix-4 stages of every (token, b) in place.
+// Base twiddles of the stages in LDS after the regions: of stage T < S for a = 1..3 and bq < 4 k2, then of
+// stage S for a = 1..3 and b < k2.  (From memory, the waits for them would be waits for the token rows
+// in flight.)
+template <int S>
+__device__ __host__ constexpr int ms_twiddles(int k2) {
+  return 3 * k2 * (4 * (S - 1) + 1);
+}
+template <int S>
+struct Twiddles {
+  static constexpr int kU = 2;   // (at most 960 factors)
+  float2 w[kU];
+  __device__ __forceinline__ void fetch(const FrameDev& f) {
+    const int k2 = f.k2, n = ms_twiddles<S>(k2), per = 12 * k2;
+    const float inv = 1.f / (float)k2;
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+      const int i = min(phase_tid() + u * kMsThreads, n - 1);
+      const int T = (i >= per) + (S > 2 && i >= 2 * per), r = i - T * per;
+      const int a = div_small(r, k2, inv) >> (T == S - 1 ? 0 : 2), m = T == S - 1 ? k2 : 4 * k2;
+      w[u] = gload(f.twk + (a + 1) * (r - a * m) * (1 << (2 * T)));
+    }
+  }
+  __device__ __forceinline__ void put(const FrameDev& f, float2* tw) const {
+    const int n = ms_twiddles<S>(f.k2);
+#pragma unroll
+    for (int u = 0; u < kU; ++u) tw[min(phase_tid() + u * kMsThreads, n - 1)] = w[u];
+  }
+};
+
+// The radix-4 stages of every b of nt tokens from t0 on, in place.
 template <int S, bool INV, bool BETA>
-__device__ __forceinline__ void ms_stages(const FrameDev& f, unsigned char* lds, int nt, float s, float beta,
-                                          const unsigned char* old, long ld) {
+__device__ __forceinline__ void ms_stages(const FrameDev& f, unsigned char* lds, const float2* tw, int t0, int nt, float s,
+                                          float beta, const unsigned char* old, long ld) {
   constexpr int NL = 1 << (2 * S - 2);
   const int k2 = f.k2, TS = ms_token_stride(k2), R = ms_region(k2);
   const float inv = 1.f / (float)k2;
   const int n = 4 * nt * k2;   // whole quads
   for (int i = phase_tid(); i < n; i += kMsThreads) {
-    const int q = i & 3, it = i >> 2, t = div_small(it, k2, inv), b = it - t * k2, bq = b + k2 * q;
-    unsigned char* p = lds + t * TS + 4 * b;
-    float2 v[NL];
+    const int q = i & 3, it = i >> 2, tl = div_small(it, k2, inv), t = t0 + tl, b = it - __mul24(tl, k2);
+    const int bq = b + __mul24(k2, q);
+    unsigned char* p = lds + __mul24(t, TS) + 4 * b;
+    float2 v[NL], w1[3], w2[3], wl[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      w1[a] = tw[4 * k2 * a + bq];
+      if constexpr (S >= 3) w2[a] = tw[4 * k2 * (3 + a) + bq];
+      wl[a] = tw[12 * k2 * (S - 1) + k2 * a + b];
+    }
     if constexpr (!INV) {
 #pragma unroll
-      for (int m = 0; m < NL; ++m) v[m] = ld2<true>(reinterpret_cast<const u16*>(p + (4 * m + q) * R));
-      msr_stage<S, 1, false>(v, bq, k2, f.twk);
-      if constexpr (S >= 3) msr_stage<S, 2, false>(v, bq, k2, f.twk);
+      for (int m = 0; m < NL; ++m) v[m] = ld2<true>(reinterpret_cast<const u16*>(p + __mul24(q, R) + 4 * m * R));
+      msr_stage<S, 1, false>(v, w1, k2, f.twk);
+      if constexpr (S >= 3) msr_stage<S, 2, false>(v, w2, k2, f.twk);
       quad_transpose(v, q);
-      msr_last_stage<S, false>(v, b, f.twk);
+      msr_last_stage<S, false>(v, wl);
 #pragma unroll
       for (int g = 0; g < NL / 4; ++g)
 #pragma unroll
-        for (int a = 0; a < 4; ++a) st2<true>(reinterpret_cast<u16*>(p + (16 * g + 4 * q + a) * R), v[4 * g + a]);
+        for (int a = 0; a < 4; ++a) st2<true>(reinterpret_cast<u16*>(p + __mul24(4 * q, R) + (16 * g + a) * R), v[4 * g + a]);
     } else {
 #pragma unroll
       for (int g = 0; g < NL / 4; ++g)
 #pragma unroll
-        for (int a = 0; a < 4; ++a) v[4 * g + a] = ld2<true>(reinterpret_cast<const u16*>(p + (16 * g + 4 * q + a) * R));
-      msr_last_stage<S, true>(v, b, f.twk);
+        for (int a = 0; a < 4; ++a) v[4 * g + a] = ld2<true>(reinterpret_cast<const u16*>(p + __mul24(4 * q, R) + (16 * g + a) * R));
+      msr_last_stage<S, true>(v, wl);
       quad_transpose(v, q);
-      if constexpr (S >= 3) msr_stage<S, 2, true>(v, bq, k2, f.twk);
-      msr_stage<S, 1, true>(v, bq, k2, f.twk);
+      if constexpr (S >= 3) msr_stage<S, 2, true>(v, w2, k2, f.twk);
+      msr_stage<S, 1, true>(v, w1, k2, f.twk);
 #pragma unroll
       for (int m = 0; m < NL; ++m) {
         float2 o = make_float2(s * v[m].x, s * v[m].y);
@@ -76,11 +114,56 @@ __device__ __forceinline__ void ms_stages(const FrameDev& f, unsigned char* lds,
           o.x = fmaf(beta, y.x, o.x);
           o.y = fmaf(beta, y.y, o.y);
         }
-        st2<true>(reinterpret_cast<u16*>(p + (4 * m + q) * R), o);
+        st2<true>(reinterpret_cast<u16*>(p + __mul24(q, R) + 4 * m * R), o);
       }
     }
   }
 }
+
+// A workgroup's token rows are moved in kMsRuns runs of kMsRun tokens (whole cache lines), so that one run's
+// transfer goes on during another's stages.
+constexpr int kMsRuns = 4, kMsRun = kMsTok / kMsRuns;
+// Two waves take a token of a run, neighbouring lanes neighbouring pieces.
+template <int S>
+struct MsRows {
+  static constexpr int PT = S == 3 ? 4 : 2;   // 16-byte pieces of a thread: blocks up to 4096, 2048 wide
+  bool whole;                                 // k2 a multiple of four: a piece lies in one column
+  int t, c[PT];                               // token of the run; piece (past the row: its last again)
+  int at[PT], k2, R, b[PT];                   // its place in the token's LDS, first b
+  int run;                                    // LDS from run to run
+  __device__ __forceinline__ explicit MsRows(const FrameDev& f)
+      : whole(f.k2 % 4 == 0), t(__builtin_amdgcn_readfirstlane(threadIdx.x >> 7)), k2(f.k2), R(ms_region(f.k2)),
+        run(kMsRun * ms_token_stride(f.k2)) {
+    const int cb = f.W / 8;
+    const float inv = 1.f / (float)k2;
+#pragma unroll
+    for (int u = 0; u < PT; ++u) {
+      c[u] = min((phase_tid() & 127) + 128 * u, cb - 1);
+      const int j = div_small(4 * c[u], k2, inv);
+      b[u] = 4 * c[u] - __mul24(j, k2);
+      at[u] = __mul24(j, R) + 4 * b[u] + t * ms_token_stride(k2);
+    }
+  }
+  // piece u of run r
+  __device__ __forceinline__ void put(unsigned char* lds, int r, int u, u32x4v v) const {
+    unsigned char* p = lds + r * run + at[u];
+    if (whole) {   // uniform
+      *reinterpret_cast<u32x4v*>(p) = v;
+      return;
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e)   // (a column's end: on to the next one's start)
+      *reinterpret_cast<unsigned*>(p + 4 * e + (b[u] + e >= k2 ? R - 4 * k2 : 0)) = v[e];
+  }
+  __device__ __forceinline__ u32x4v get(const unsigned char* lds, int r, int u) const {
+    const unsigned char* p = lds + r * run + at[u];
+    if (whole) return *reinterpret_cast<const u32x4v*>(p);
+    u32x4v v;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = *reinterpret_cast<const unsigned*>(p + 4 * e + (b[u] + e >= k2 ? R - 4 * k2 : 0));
+    return v;
+  }
+};
 
 template <int S, int MT, int KT>
 __global__ void __launch_bounds__(kMsThreads, 2) ms_analysis(AnaArgs a) {
@@ -114,54 +197,43 @@ __global__ void __launch_bounds__(kMsThreads, 2) ms_analysis(AnaArgs a) {
       gstore(reinterpret_cast<u32x4v*>(out + (long)(i >> 1) * kSlabRowBytes + 16 * (i & 1)), u32x4v{0u, 0u, 0u, 0u});
     return;
   }
-  {   // token rows, 16 bytes per lane; the windows' padding and the tokens past the end are zero
-    const unsigned char* X = reinterpret_cast<const unsigned char*>(a.Xs ? sload(a.Xs + bi) : a.X) +
-                             (t0 * a.ld + (long)tile.blk * f.W) * 2;
-    const int cb = f.W / 8;   // 16-byte chunks (4 complex coordinates) of a block's row
-    const float inv_cb = 1.f / (float)cb, inv_k2 = 1.f / (float)k2;
-    constexpr int kU = 4;
-    for (int i0 = tid; i0 < kMsTok * cb; i0 += kU * kMsThreads) {
-      u32x4v v[kU];
-#pragma unroll
-      for (int u = 0; u < kU; ++u) {
-        const int i = min(i0 + u * kMsThreads, kMsTok * cb - 1), t = div_small(i, cb, inv_cb), c = i - t * cb;
-        v[u] = gload(reinterpret_cast<const u32x4v*>(X + (long)min(t, nt - 1) * a.ld * 2 + 16 * c));
-        if (t >= nt) v[u] = u32x4v{0u, 0u, 0u, 0u};
-      }
-#pragma unroll
-      for (int u = 0; u < kU; ++u) {
-        const int i = i0 + u * kMsThreads;
-        if (i >= kMsTok * cb) break;
-        const int t = div_small(i, cb, inv_cb), nn = 4 * (i - t * cb);
-        int j = div_small(nn, k2, inv_k2), b = nn - j * k2;
-        unsigned char* p = smem + t * TS;
-        if (k2 % 4 == 0) {   // uniform: the chunk lies in one column
-          *reinterpret_cast<u32x4v*>(p + j * R + 4 * b) = v[u];
-        } else {
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            *reinterpret_cast<unsigned*>(p + j * R + 4 * b) = v[u][e];
-            if (++b == k2) b = 0, ++j;
-          }
-        }
-      }
-    }
-    if (k2 % 4 != 0) {
-      const int pad = 4 - k2 % 4;
-      for (int i = tid; i < ncol * kMsTok * pad; i += kMsThreads) {
-        const int jt = i / pad, e = i - jt * pad;
-        *reinterpret_cast<unsigned*>(smem + (jt >> 4) * R + (jt & 15) * TS + 4 * (k2 + e)) = 0u;
-      }
-    }
-  }
+  const unsigned char* X = reinterpret_cast<const unsigned char*>(a.Xs ? sload(a.Xs + bi) : a.X) +
+                           (t0 * a.ld + (long)tile.blk * f.W) * 2;
+  float2* tw = reinterpret_cast<float2*>(smem + ncol * R);
+  Twiddles<S> twid;
+  twid.fetch(f);
   // the wave's fragments, the same for all its columns
   bf16x8 fr[MT][KT];
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
     for (int ks = 0; ks < KT; ++ks) fr[mt][ks] = gload(reinterpret_cast<const bf16x8*>(f.fa16) + (mt * KT + ks) * 64 + lane);
-  __syncthreads();
-  ms_stages<S, false, false>(f, smem, kMsTok, 0.f, 0.f, nullptr, 0);
+  // every piece in flight at once, with no branch among the loads: the waits are then for the run at hand
+  // (tokens past the end: the last one's pieces, put down as zeros)
+  const MsRows<S> rows(f);
+  u32x4v v[kMsRuns][MsRows<S>::PT];
+#pragma unroll
+  for (int r = 0; r < kMsRuns; ++r)
+#pragma unroll
+    for (int u = 0; u < MsRows<S>::PT; ++u)
+      v[r][u] = gload(reinterpret_cast<const u32x4v*>(X + (long)min(kMsRun * r + rows.t, nt - 1) * a.ld * 2 + 16 * rows.c[u]));
+  __builtin_amdgcn_sched_barrier(0);
+  twid.put(f, tw);
+  if (k2 % 4 != 0) {   // the windows' padding
+    const int pad = 4 - k2 % 4;
+    for (int i = tid; i < ncol * kMsTok * pad; i += kMsThreads) {
+      const int jt = i / pad, e = i - jt * pad;
+      *reinterpret_cast<unsigned*>(smem + (jt >> 4) * R + (jt & 15) * TS + 4 * (k2 + e)) = 0u;
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < kMsRuns; ++r) {
+#pragma unroll
+    for (int u = 0; u < MsRows<S>::PT; ++u)
+      rows.put(smem, r, u, kMsRun * r + rows.t < nt ? v[r][u] : u32x4v{0u, 0u, 0u, 0u});
+    __syncthreads();
+    if (kMsRun * r < nt) ms_stages<S, false, false>(f, smem, tw, kMsRun * r, kMsRun, 0.f, 0.f, nullptr, 0);
+  }
   __syncthreads();
   const int nw = (W2 + 7) / 8;
   for (int j = wave; j < ncol; j += kMsWaves) {
@@ -209,34 +281,34 @@ __global__ void __launch_bounds__(kMsThreads, 2) ms_synthesis(MsOutArgs a) {
   unsigned char* Y = reinterpret_cast<unsigned char*>(a.Ys ? sload(a.Ys + bi) : a.Y) + (t0 * a.ldy + (long)tile.blk * f.W) * 2;
   const int tid = phase_tid(), lane = tid & 63, q = lane >> 4, L = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  {
-    const float inv = 1.f / (float)W2;
-    constexpr int kU = 4;
-    const int n = 2 * f.W;
-    for (int i0 = tid; i0 < n; i0 += kU * kMsThreads) {
-      u32x4v v[kU];
-#pragma unroll
-      for (int u = 0; u < kU; ++u) {
-        const int i = min(i0 + u * kMsThreads, n - 1);
-        v[u] = gload(reinterpret_cast<const u32x4v*>(in + (long)(i >> 1) * kSlabRowBytes + 16 * (i & 1)));
-      }
-#pragma unroll
-      for (int u = 0; u < kU; ++u) {
-        const int i = i0 + u * kMsThreads;
-        if (i >= n) break;
-        const int row = i >> 1, j = div_small(row, W2, inv);
-        *reinterpret_cast<u32x4v*>(smem + j * R + (row - j * W2) * 32 + 16 * (i & 1)) = v[u];
-      }
-    }
-  }
+  float2* tw = reinterpret_cast<float2*>(smem + ncol * R);
+  Twiddles<S> twid;
+  twid.fetch(f);
   bf16x8 fr[MT][KT];
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
     for (int ks = 0; ks < KT; ++ks) fr[mt][ks] = gload(reinterpret_cast<const bf16x8*>(f.ws16) + (mt * KT + ks) * 64 + lane);
-  __syncthreads();
-  for (int j = wave; j < ncol; j += kMsWaves) {
+  // a column is one wave's: its coefficients to LDS, two columns in flight, transformed and back as
+  // [token][k2 complex]
+  constexpr int kPC = (MT + 1) / 2;   // 16-byte pieces of a lane: a column's rows are two each
+  u32x4v cv[2][kPC];
+  auto fetch = [&](int j, u32x4v (&v)[kPC]) {
+#pragma unroll
+    for (int u = 0; u < kPC; ++u) {
+      const int i = min(lane + 64 * u, 2 * W2 - 1);
+      v[u] = gload(reinterpret_cast<const u32x4v*>(in + (long)(j * W2 + (i >> 1)) * kSlabRowBytes + 16 * (i & 1)));
+    }
+  };
+  auto column = [&](int j, u32x4v (&v)[kPC]) {
     unsigned char* reg = smem + j * R;
+#pragma unroll
+    for (int u = 0; u < kPC; ++u) {
+      const int i = min(lane + 64 * u, 2 * W2 - 1);
+      *reinterpret_cast<u32x4v*>(reg + (i >> 1) * 32 + 16 * (i & 1)) = v[u];
+    }
+    if (j + 2 * kMsWaves < ncol) fetch(j + 2 * kMsWaves, v);   // (uniform)
+    __asm__ volatile("" ::: "memory");   // (a wave's LDS operations execute in order)
     bf16x8 op[KT];
 #pragma unroll
     for (int ks = 0; ks < KT; ++ks) {   // token L at the 8 coefficients of its clamped window, by transposed reads
@@ -262,27 +334,27 @@ __global__ void __launch_bounds__(kMsThreads, 2) ms_synthesis(MsOutArgs a) {
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
       if (16 * mt + 4 * q < W2) *reinterpret_cast<uint2*>(reg + L * TS + (16 * mt + 4 * q) * 2) = Act<true>::pack4(acc[mt]);
+  };
+  fetch(wave, cv[0]);
+  fetch(wave + kMsWaves, cv[1]);
+  __builtin_amdgcn_sched_barrier(0);
+  twid.put(f, tw);
+  for (int j = wave; j < ncol; j += 2 * kMsWaves) {   // (ncol: 16 or 64)
+    column(j, cv[0]);
+    column(j + kMsWaves, cv[1]);
   }
   __syncthreads();
-  ms_stages<S, true, BETA>(f, smem, nt, a.scale, a.beta, Y, a.ldy * 2);
-  __syncthreads();
-  const int cb = f.W / 8;
-  const float inv_cb = 1.f / (float)cb, inv_k2 = 1.f / (float)k2;
-  for (int i = tid; i < nt * cb; i += kMsThreads) {
-    const int t = div_small(i, cb, inv_cb), c = i - t * cb, nn = 4 * c;
-    int j = div_small(nn, k2, inv_k2), b = nn - j * k2;
-    const unsigned char* p = smem + t * TS;
-    u32x4v v;
-    if (k2 % 4 == 0) {
-      v = *reinterpret_cast<const u32x4v*>(p + j * R + 4 * b);
-    } else {
+  const MsRows<S> rows(f);
+#pragma unroll 1
+  for (int r = 0; kMsRun * r < nt; ++r) {
+    ms_stages<S, true, BETA>(f, smem, tw, kMsRun * r, min(kMsRun, nt - kMsRun * r), a.scale, a.beta, Y, a.ldy * 2);
+    __syncthreads();
+    const int t = kMsRun * r + rows.t;
+    if (t < nt) {   // (uniform)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        v[e] = *reinterpret_cast<const unsigned*>(p + j * R + 4 * b);
-        if (++b == k2) b = 0, ++j;
-      }
+      for (int u = 0; u < MsRows<S>::PT; ++u)
+        gstore(reinterpret_cast<u32x4v*>(Y + (long)t * a.ldy * 2 + 16 * rows.c[u]), rows.get(smem, r, u));
     }
-    gstore(reinterpret_cast<u32x4v*>(Y + (long)t * a.ldy * 2 + 16 * c), v);
   }
 }
 
@@ -419,18 +491,23 @@ __global__ void __launch_bounds__(kSlabThreads, DC ? 2 : 3) ms_pass(SlabArgs a) 
   }
 }
 
-#define MS_SHAPES(S, X)                     \
-  switch (a.f.MT * 8 + a.f.KT) {            \
-    case 3 * 8 + 2: X(S, 3, 2); break;      \
-    case 4 * 8 + 2: X(S, 4, 2); break;      \
-    case 5 * 8 + 3: X(S, 5, 3); break;      \
-    case 6 * 8 + 3: X(S, 6, 3); break;      \
-    case 7 * 8 + 4: X(S, 7, 4); break;      \
-    case 8 * 8 + 4: X(S, 8, 4); break;      \
-    default: return hipErrorInvalidValue;   \
+// Output tiles and contraction steps of the DFTs of size k2: 17 to 64 points in two stages, to 32 in three.
+#define MS_SHAPES(X)                                    \
+  switch (a.f.nst * 64 + a.f.MT * 8 + a.f.KT) {         \
+    case 2 * 64 + 3 * 8 + 2: X(2, 3, 2); break;         \
+    case 2 * 64 + 4 * 8 + 2: X(2, 4, 2); break;         \
+    case 2 * 64 + 5 * 8 + 3: X(2, 5, 3); break;         \
+    case 2 * 64 + 6 * 8 + 3: X(2, 6, 3); break;         \
+    case 2 * 64 + 7 * 8 + 4: X(2, 7, 4); break;         \
+    case 2 * 64 + 8 * 8 + 4: X(2, 8, 4); break;         \
+    case 3 * 64 + 3 * 8 + 2: X(3, 3, 2); break;         \
+    case 3 * 64 + 4 * 8 + 2: X(3, 4, 2); break;         \
+    default: return hipErrorInvalidValue;               \
   }
 
-size_t ms_lds(const FrameDev& f) { return (size_t)f.ncol * ms_region(f.k2); }
+size_t ms_lds(const FrameDev& f) {
+  return (size_t)f.ncol * ms_region(f.k2) + (f.nst == 2 ? ms_twiddles<2>(f.k2) : ms_twiddles<3>(f.k2)) * sizeof(float2);
+}
 
 template <class K>
 hipError_t allow_lds(K* k) {
@@ -442,11 +519,7 @@ hipError_t allow_lds(K* k) {
 hipError_t launch_ms_analysis(const AnaArgs& a, dim3 grid, hipStream_t s) {
   const size_t lds = ms_lds(a.f);
 #define X(S, mt, kt) hipLaunchKernelGGL((ms_analysis<S, mt, kt>), grid, dim3(kMsThreads), lds, s, a)
-  if (a.f.nst == 2) {
-    MS_SHAPES(2, X)
-  } else {
-    MS_SHAPES(3, X)
-  }
+  MS_SHAPES(X)
 #undef X
   return hipGetLastError();
 }
@@ -458,11 +531,7 @@ hipError_t launch_ms_synthesis(const MsOutArgs& a, dim3 grid, hipStream_t s) {
     hipLaunchKernelGGL((ms_synthesis<S, mt, kt, true>), grid, dim3(kMsThreads), lds, s, a);            \
   else                                                                                                \
     hipLaunchKernelGGL((ms_synthesis<S, mt, kt, false>), grid, dim3(kMsThreads), lds, s, a)
-  if (a.f.nst == 2) {
-    MS_SHAPES(2, X)
-  } else {
-    MS_SHAPES(3, X)
-  }
+  MS_SHAPES(X)
 #undef X
   return hipGetLastError();
 }
@@ -485,9 +554,7 @@ hipError_t configure_ms() {
   for (const hipError_t r : {allow_lds(&ms_analysis<S, mt, kt>), allow_lds(&ms_synthesis<S, mt, kt, false>), \
                              allow_lds(&ms_synthesis<S, mt, kt, true>)})                              \
     if (r != hipSuccess) e = r;
-#define ALL(S) ONE(S, 3, 2) ONE(S, 4, 2) ONE(S, 5, 3) ONE(S, 6, 3) ONE(S, 7, 4) ONE(S, 8, 4)
-  ALL(2) ALL(3)
-#undef ALL
+  ONE(2, 3, 2) ONE(2, 4, 2) ONE(2, 5, 3) ONE(2, 6, 3) ONE(2, 7, 4) ONE(2, 8, 4) ONE(3, 3, 2) ONE(3, 4, 2)
 #undef ONE
   return e;
 }
