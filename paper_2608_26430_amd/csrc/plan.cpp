@@ -277,11 +277,24 @@ struct SlabStreamHost {
   int nb = 1, ngroups = 0;
 };
 
-// lists[pos]: entries of destination position pos; src(e): source position of entry e; zero_src: the
-// source slab's row of zeros.
-template <class Src>
-SlabStreamHost build_slab_stream(const std::vector<std::vector<int>>& lists, const ff::FrameDev& dst, int64_t slabs,
-                                 Src src, uint32_t zero_src) {
+// Entry e joins source position src[e] (below nsrc, the row of the source slab that holds zeros) and
+// destination position dst_pos[e].
+SlabStreamHost build_slab_stream(const std::vector<int>& src, int64_t nsrc, const std::vector<int>& dst_pos,
+                                 const ff::FrameDev& dst, int64_t slabs) {
+  // entries of each destination position in order of their source: two stable counting sorts
+  const int64_t ndst = (int64_t)dst.nblk * dst.W, nnz = (int64_t)src.size();
+  std::vector<int> by_src((size_t)nnz), list((size_t)nnz), ptr((size_t)std::max(nsrc, ndst) + 1, 0);
+  for (int64_t e = 0; e < nnz; ++e) ptr[(size_t)src[e] + 1]++;
+  for (int64_t i = 0; i < nsrc; ++i) ptr[i + 1] += ptr[i];
+  for (int64_t e = 0; e < nnz; ++e) by_src[(size_t)ptr[(size_t)src[e]]++] = (int)e;
+  ptr.assign((size_t)ndst + 1, 0);
+  for (int64_t e = 0; e < nnz; ++e) ptr[(size_t)dst_pos[e] + 1]++;
+  for (int64_t i = 0; i < ndst; ++i) ptr[i + 1] += ptr[i];
+  for (int e : by_src) list[(size_t)ptr[(size_t)dst_pos[e]]++] = e;
+  for (int64_t i = ndst; i > 0; --i) ptr[i] = ptr[i - 1];   // (the distribution moved each start to its end)
+  ptr[0] = 0;
+  auto size = [&](int64_t r) { return (int64_t)ptr[r + 1] - ptr[r]; };
+  const uint32_t zero_src = (uint32_t)nsrc;
   SlabStreamHost h;
   const int64_t units = slabs * ((int64_t)dst.nblk * dst.W + 127) / 128, P = (int64_t)dst.nblk * dst.W;
   const bool ms = ff::slab_ms_frame(dst);
@@ -294,13 +307,13 @@ SlabStreamHost build_slab_stream(const std::vector<std::vector<int>>& lists, con
     const uint32_t dump = (uint32_t)per;   // the row of lanes that hold none
     std::vector<int> rows;
     for (int64_t r = p0; r < p1; ++r) {
-      if (lists[r].empty())
+      if (size(r) == 0)
         h.zrow.push_back((unsigned short)(r - p0));
       else
         rows.push_back((int)r);
     }
     h.zptr.push_back((int)h.zrow.size());
-    std::stable_sort(rows.begin(), rows.end(), [&](int a, int b) { return lists[a].size() > lists[b].size(); });
+    std::stable_sort(rows.begin(), rows.end(), [&](int a, int b) { return size(a) > size(b); });
     // bundles of 16 rows, longest first, each to the wave with the fewest steps so far
     const int nbun = ((int)rows.size() + 15) / 16;
     std::vector<std::vector<int>> of_wave(ff::kSlabWaves);
@@ -308,7 +321,7 @@ SlabStreamHost build_slab_stream(const std::vector<std::vector<int>>& lists, con
     for (int b = 0; b < nbun; ++b) {
       const int w = (int)(std::min_element(load.begin(), load.end()) - load.begin());
       of_wave[w].push_back(b);
-      load[w] += (int64_t)lists[rows[16 * b]].size();
+      load[w] += size(rows[16 * b]);
     }
     for (int w = 0; w < ff::kSlabWaves; ++w) {
       h.wstep.push_back((int)h.steps);
@@ -318,19 +331,20 @@ SlabStreamHost build_slab_stream(const std::vector<std::vector<int>>& lists, con
       h.id.resize(h.word.size(), -1);
       int64_t k0 = 0;
       for (int b : of_wave[w]) {
-        const int64_t len = (int64_t)lists[rows[16 * b]].size();
-        for (int64_t k = 0; k < len; ++k)
-          for (int l = 0; l < 16; ++l) {
-            const bool real = 16 * b + l < (int)rows.size();
-            const int r = real ? rows[16 * b + l] : 0;
-            const int e = real && k < (int64_t)lists[r].size() ? lists[r][k] : -1;
-            const uint32_t d = real ? (uint32_t)(r - p0) : dump;
+        const int64_t len = size(rows[16 * b]);
+        for (int l = 0; l < 16; ++l) {
+          const bool real = 16 * b + l < (int)rows.size();
+          const int r = real ? rows[16 * b + l] : 0;
+          const int64_t have = real ? size(r) : 0;
+          const uint32_t d = (real ? (uint32_t)(r - p0) : dump) << ff::kSlabDstShift;
+          for (int64_t k = 0; k < len; ++k) {
+            const int e = k < have ? list[(size_t)(ptr[r] + k)] : -1;
             // batches of four steps: entry l of step k at 64 (k / 4) + 4 l + k % 4
             const size_t j = at + (size_t)((k0 + k) / 4 * 64 + 4 * l + (k0 + k) % 4);
-            h.word[j] = (e >= 0 ? (uint32_t)src(e) : zero_src) | d << ff::kSlabDstShift |
-                        (k == len - 1 ? (uint32_t)ff::kRowLast : 0u);
+            h.word[j] = (e >= 0 ? (uint32_t)src[(size_t)e] : zero_src) | d | (k == len - 1 ? (uint32_t)ff::kRowLast : 0u);
             h.id[j] = e;
           }
+        }
         k0 += len;
       }
       h.steps += len4;
@@ -518,20 +532,14 @@ extern "C" ff_status ff_plan_create(const ff_frame* f_in, const ff_frame* f_out,
       for (int t = 0; t < f.nst; ++t, i >>= 2) col = 4 * col + (i & 3);
       return l.blk * f.W + col * f.W2 + 2 * i + (l.local & 1);
     };
-    auto by_position = [&](const std::vector<std::vector<int>>& by, const ff::FrameDev& f, int64_t rho, auto other) {
-      std::vector<std::vector<int>> out(by.size());
-      for (int64_t c = 0; c < (int64_t)by.size(); ++c) {
-        std::vector<int> l = by[c];
-        std::stable_sort(l.begin(), l.end(), [&](int a, int b) { return other(a) < other(b); });
-        out[(size_t)position(f, locate(c, rho))] = std::move(l);
-      }
-      return out;
-    };
-    auto pos_in = [&](int e) { return position(FI, cloc[e]); };
-    auto pos_out = [&](int e) { return position(FO, rloc[e]); };
+    std::vector<int> pos_in((size_t)nnz), pos_out((size_t)nnz);
+    for (int64_t e = 0; e < nnz; ++e) {
+      pos_in[e] = position(FI, cloc[e]);
+      pos_out[e] = position(FO, rloc[e]);
+    }
     const int64_t slabs = (max_tokens + ff::kSlabRowBytes / 2 - 1) / (ff::kSlabRowBytes / 2) * max_batch;
-    sfwd = build_slab_stream(by_position(by_row, FO, f_out->rho, pos_in), FO, slabs, pos_in, (uint32_t)n);
-    sbwd = build_slab_stream(by_position(by_col, FI, f_in->rho, pos_out), FI, slabs, pos_out, (uint32_t)m);
+    sfwd = build_slab_stream(pos_in, n, pos_out, FO, slabs);
+    sbwd = build_slab_stream(pos_out, m, pos_in, FI, slabs);
     if (std::max(sfwd.word.size(), sbwd.word.size()) > (size_t)1 << 30)
       return ff::fail(FF_EUNSUPPORTED, "support too skewed for the entry streams");
   }
