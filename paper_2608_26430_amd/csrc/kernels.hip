@@ -474,9 +474,15 @@ hipError_t launch_dc_reduce(const float* partial, long nrows, int len, const int
 hipError_t launch_fwd(const ff_plan* p, int bf16, int count, int T, ActPtrs X, int64_t ldx, const float* c,
                       const float* const* cs, float scale, float beta, ActPtrs Y, int64_t ldy, float* c_saved,
                       hipStream_t s) {
-  if (bf16 && p->fast.enabled) return launch_fwd128(p, count, T, X, ldx, c, cs, scale, beta, Y, ldy, c_saved, s);
-  if (bf16 && p->slab.enabled)
-    return launch_fwd_slab(p, bf16, count, T, X, ldx, c, cs, scale, beta, Y, ldy, s);
+  const bool slab = p->slab.enabled && (!p->fast.enabled || fused_forward_slower(p->fin->dv, p->fout->dv, p->nnz,
+                                                                                 (int64_t)T * count));
+  if (bf16 && p->fast.enabled && !slab)
+    return launch_fwd128(p, count, T, X, ldx, c, cs, scale, beta, Y, ldy, c_saved, s);
+  if (bf16 && slab) {
+    const hipError_t e = launch_fwd_slab(p, bf16, count, T, X, ldx, c, cs, scale, beta, Y, ldy, s);
+    if (e != hipSuccess || !c_saved || !p->fast.enabled) return e;
+    return launch_fwd128(p, count, 0, X, ldx, c, cs, scale, beta, Y, ldy, c_saved, s);   // the copy alone
+  }
   if (bf16) return hipErrorInvalidValue;   // (not reached: every other bf16 plan takes the slab kernels)
   FwdArgs a{};
   a.fin = p->fin->dev;
