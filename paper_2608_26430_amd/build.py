@@ -24,9 +24,9 @@ SOURCES = [("capi.cpp", "capi.cpp.o", []), ("framegen.cpp", "framegen.cpp.o", []
            ("slab_ms.hip", "slab_ms.hip.o", [])] + [
     ("slab_inst.hip", f"slab_bf16_{r}.o", ["-DSLAB_BF16=1", f"-DSLAB_RADIX={int(r == 'radix')}"])
     for r in ("direct", "radix")] + [
-    ("gen_inst.hip", f"gen_{d}_f32{'_ms' if ms else ''}.o",
-     [f"-DGEN_BWD={int(d == 'bwd')}", f"-DGEN_MS={ms}"])
-    for d in ("bwd", "fwd") for ms in (0, 1)]
+    ("gen_inst.hip", f"gen_{d}_{t}{'_ms' if ms else ''}.o",
+     [f"-DGEN_BWD={int(d == 'bwd')}", f"-DGEN_BF16={int(t == 'bf16')}", f"-DGEN_MS={ms}"])
+    for d in ("bwd", "fwd") for t, ms in (("bf16", 1), ("f32", 0), ("f32", 1))]
 
 ARCH = "gfx950"
 COMMON = [

@@ -365,6 +365,10 @@ namespace ff {
 
 // Error reporting (capi.cpp): remember a message for ff_last_error and return s.
 ff_status fail(ff_status s, const char* fmt, ...);
+// Whether a bf16 call of at most `tokens` tokens (all adapters; `most` of one) on a plan without the fused
+// kernels runs in the slab kernels (else in the generic ones).
+bool slab_forward(const ff_plan* p, int64_t tokens, int64_t most);
+bool slab_backward(const ff_plan* p, int64_t tokens);
 void clear_error();
 
 // One-shot kernel timing events armed by ff_time_next_kernel.

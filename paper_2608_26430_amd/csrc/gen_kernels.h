@@ -1,7 +1,7 @@
 // Device code of the generic kernels (fwd_kernel, bwd_kernel) and their helpers, shared by the
-// translation units that instantiate them (gen_inst.hip, once per direction and kind of frame,
+// translation units that instantiate them (gen_inst.hip, once per direction and activation type,
 // so that they compile in parallel), by kernels.hip and by the slab kernels (argument structs,
-// element helpers).  fp32 activations run here.
+// element helpers).  fp32 activations run here, and short bf16 calls.
 #pragma once
 
 #include <algorithm>
@@ -1107,11 +1107,15 @@ __global__ void __launch_bounds__(kFusedThreads) bwd_kernel(BwdArgs a) {
 }
 
 
-// Launch fwd_kernel / bwd_kernel on fp32 activations (gen_inst.hip); CHUNKED is a.nch > 1.
+// Launch fwd_kernel / bwd_kernel for one activation type (gen_inst.hip); CHUNKED is a.nch > 1.
+hipError_t launch_fwd_bf16(const FwdArgs& a, dim3 grid, size_t lds, hipStream_t s);
 hipError_t launch_fwd_f32(const FwdArgs& a, dim3 grid, size_t lds, hipStream_t s);
+hipError_t launch_bwd_bf16(const BwdArgs& a, dim3 grid, size_t lds, hipStream_t s);
 hipError_t launch_bwd_f32(const BwdArgs& a, dim3 grid, size_t lds, hipStream_t s);
 // Allow them the largest dynamic LDS allocation (once per process).
+hipError_t configure_fwd_bf16();
 hipError_t configure_fwd_f32();
+hipError_t configure_bwd_bf16();
 hipError_t configure_bwd_f32();
 
 }  // namespace gen

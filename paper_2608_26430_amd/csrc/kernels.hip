@@ -425,7 +425,8 @@ void record(hipEvent_t ev, hipStream_t s) {
 hipError_t configure_kernels() {
   static hipError_t once = [] {
     hipError_t e = hipSuccess;
-    for (const hipError_t r : {gen::configure_fwd_f32(), gen::configure_bwd_f32(), configure_slab()})
+    for (const hipError_t r : {gen::configure_fwd_bf16(), gen::configure_fwd_f32(), gen::configure_bwd_bf16(),
+                               gen::configure_bwd_f32(), configure_slab()})
       if (r != hipSuccess) e = r;
     return e;
   }();
@@ -471,11 +472,45 @@ hipError_t launch_dc_reduce(const float* partial, long nrows, int len, const int
   return hipGetLastError();
 }
 
+// The generic kernels are one launch whose workgroups keep both sides of a few tokens in LDS and walk the
+// whole support; the slab kernels are two or three, which spread the walk but each take their latency.
+//
+// Several stages (one block per side, so few workgroups per slab): the generic kernels up to about one
+// round of tiles on the chip.  Forward / backward, generic -> slab: 4096 wide (5,000 entries) 16 tokens
+// 17/32 -> 39/60 us, 1536 34/72 -> 46/70, 2048 47/86 -> 48/73, 4096 91/161 -> 58/89; 1024 wide (1,000)
+// 16 tokens 9/20 -> 18/28, 2048 15/30 -> 20/32, 4096 23/43 -> 22/35, 8192 39/80 -> 34/52.
+static int64_t ms_tokens(const ff_plan* p, double most, double per) {
+  return (int64_t)(most + per * 2 / (double)(p->fin->dv + p->fout->dv));
+}
+static bool multistage(const ff_plan* p) { return slab_ms_frame(p->fin->dev) || slab_ms_frame(p->fout->dev); }
+bool slab_backward(const ff_plan* p, int64_t tokens) {
+  if (!p->slab.enabled) return false;
+  // other frames: always quicker there (256 -> 512 wide, 1 token: 15 -> 13 us; 2880 -> 2880: 29 -> 25)
+  return p->gen_nch > 1 || !multistage(p) || tokens > ms_tokens(p, 1400, 0.9e6);
+}
+// Other frames, forward, by both sides' times in microseconds (generic -> slab): 256 -> 512 wide with 700
+// entries 7 -> 9, 768 -> 2304 with 3,000, 256 tokens 9 -> 10, 4096 19 -> 20; 2880 -> 2880 with 14,000, 1
+// token 14 -> 16, 64 tokens 20 -> 19; 512 -> 6912 with 27,000, 64 tokens 22 -> 12; 17 adapters 1152 -> 1664
+// with 1,935 of up to 418 tokens 18 -> 22.
+bool slab_forward(const ff_plan* p, int64_t tokens, int64_t most) {
+  if (!p->slab.enabled) return false;
+  if (p->gen_nch > 1) return true;
+  if (multistage(p)) return tokens > ms_tokens(p, 1800, 1.6e6);
+  const double w = (double)(p->fin->dv + p->fout->dv), e = (double)p->nnz, t = (double)tokens;
+  const bool factored = p->fin->dev.radix != 1 || p->fout->dev.radix != 1;
+  const double round = (double)std::min(8, p->gen_tile_tokens[1]) * p->gen_wgs;   // tokens in flight at once
+  const double generic = (5.5 + 7e-4 * w + 4e-4 * e) * (factored ? 1.3 : 1.0) * (most < 8 ? 0.7 : 1.0) *
+                         std::max(1.0, t / round);
+  const double slab = 9 + 4e-4 * w + e / (256.0 * p->slab.fwd.ngroups) + 8e-7 * w * t;
+  return generic + 0.3 > slab;
+}
+
 hipError_t launch_fwd(const ff_plan* p, int bf16, int count, int T, ActPtrs X, int64_t ldx, const float* c,
                       const float* const* cs, float scale, float beta, ActPtrs Y, int64_t ldy, float* c_saved,
                       hipStream_t s) {
-  const bool slab = p->slab.enabled && (!p->fast.enabled || fused_forward_slower(p->fin->dv, p->fout->dv, p->nnz,
-                                                                                 (int64_t)T * count));
+  const int64_t tokens = (int64_t)T * count;
+  const bool slab = p->fast.enabled ? p->slab.enabled && fused_forward_slower(p->fin->dv, p->fout->dv, p->nnz, tokens)
+                                    : slab_forward(p, tokens, T);
   if (bf16 && p->fast.enabled && !slab)
     return launch_fwd128(p, count, T, X, ldx, c, cs, scale, beta, Y, ldy, c_saved, s);
   if (bf16 && slab) {
@@ -483,7 +518,6 @@ hipError_t launch_fwd(const ff_plan* p, int bf16, int count, int T, ActPtrs X, i
     if (e != hipSuccess || !c_saved || !p->fast.enabled) return e;
     return launch_fwd128(p, count, 0, X, ldx, c, cs, scale, beta, Y, ldy, c_saved, s);   // the copy alone
   }
-  if (bf16) return hipErrorInvalidValue;   // (not reached: every other bf16 plan takes the slab kernels)
   FwdArgs a{};
   a.fin = p->fin->dev;
   a.fout = p->fout->dev;
@@ -517,7 +551,7 @@ hipError_t launch_fwd(const ff_plan* p, int bf16, int count, int T, ActPtrs X, i
   take_timing_events(&e0, &e1);
   record(e0, s);
   const size_t lds = p->gen_lds_bytes[bf16];
-  const hipError_t e = gen::launch_fwd_f32(a, grid, lds, s);
+  const hipError_t e = bf16 ? gen::launch_fwd_bf16(a, grid, lds, s) : gen::launch_fwd_f32(a, grid, lds, s);
   record(e1, s);
   return e != hipSuccess ? e : hipGetLastError();
 }
@@ -547,10 +581,9 @@ hipError_t launch_bwd(const ff_plan* p, int bf16, int count, int T, ActPtrs X, i
     return launch_bwd128(p, count, T, X, ldx, G, ldg, c, cs, scale, beta_dx, dX, lddx, want_dx, accumulate_dc, dC, dCs,
                          want_dc, c_saved, s, ws);
   if (ws && count != 1) return hipErrorInvalidValue;   // a caller's scratch serves one adapter
-  if (bf16 && p->slab.enabled)
+  if (bf16 && slab_backward(p, (int64_t)T * count))
     return launch_bwd_slab(p, bf16, count, T, X, ldx, G, ldg, c, cs, scale, beta_dx, dX, lddx, want_dx, accumulate_dc,
                            dC, dCs, want_dc, s, ws);
-  if (bf16) return hipErrorInvalidValue;   // (not reached: every other bf16 plan takes the slab kernels)
   BwdArgs a{};
   a.fin = p->fin->dev;
   a.fout = p->fout->dev;
@@ -600,7 +633,7 @@ hipError_t launch_bwd(const ff_plan* p, int bf16, int count, int T, ActPtrs X, i
     const dim3 grid((unsigned)nwg, (unsigned)count);
     record(e0, s);
     const size_t lds = p->gen_lds_bytes[bf16];
-    const hipError_t eb = gen::launch_bwd_f32(a, grid, lds, s);
+    const hipError_t eb = bf16 ? gen::launch_bwd_bf16(a, grid, lds, s) : gen::launch_bwd_f32(a, grid, lds, s);
     record(e1, s);
     if (eb != hipSuccess) return eb;
     const hipError_t e = hipGetLastError();
@@ -617,9 +650,9 @@ hipError_t launch_fwd_group(const ff_plan_group* g, int bf16, int T, const int* 
                             hipStream_t s) {
   const ff_plan* p = g->ref;
   if (bf16 && p->fast.enabled) return launch_fwd128_group(g, T, tokens, X, ldx, cs, scale, beta, Y, ldy, s);
-  if (bf16 && p->slab.enabled)
+  // (per-adapter token counts are on the device: half of the most, on average)
+  if (bf16 && slab_forward(p, (int64_t)T * g->count / (tokens ? 2 : 1), T))
     return launch_fwd_group_slab(g, bf16, T, tokens, X, ldx, cs, scale, beta, Y, ldy, s);
-  if (bf16) return hipErrorInvalidValue;   // (not reached: every other bf16 plan takes the slab kernels)
   const unsigned count = (unsigned)g->count;
   FwdArgs a{};
   a.fin = p->fin->dev;
@@ -650,7 +683,7 @@ hipError_t launch_fwd_group(const ff_plan_group* g, int bf16, int T, const int* 
   take_timing_events(&e0, &e1);
   record(e0, s);
   const size_t lds = p->gen_lds_bytes[bf16];
-  const hipError_t e = gen::launch_fwd_f32(a, grid, lds, s);
+  const hipError_t e = bf16 ? gen::launch_fwd_bf16(a, grid, lds, s) : gen::launch_fwd_f32(a, grid, lds, s);
   record(e1, s);
   return e != hipSuccess ? e : hipGetLastError();
 }
@@ -663,10 +696,9 @@ hipError_t launch_bwd_group(const ff_plan_group* g, int bf16, int T, const int* 
   if (bf16 && p->fast.enabled)
     return launch_bwd128_group(g, T, tokens, X, ldx, G, ldg, cs, scale, beta_dx, dX, lddx, want_dx, accumulate_dc,
                                dCs, want_dc, s);
-  if (bf16 && p->slab.enabled)
+  if (bf16 && slab_backward(p, (int64_t)T * g->count / (tokens ? 2 : 1)))
     return launch_bwd_group_slab(g, bf16, T, tokens, X, ldx, G, ldg, cs, scale, beta_dx, dX, lddx, want_dx,
                                  accumulate_dc, dCs, want_dc, s);
-  if (bf16) return hipErrorInvalidValue;   // (not reached: every other bf16 plan takes the slab kernels)
   const unsigned count = (unsigned)g->count;
   BwdArgs a{};
   a.fin = p->fin->dev;
@@ -703,7 +735,8 @@ hipError_t launch_bwd_group(const ff_plan_group* g, int bf16, int T, const int* 
   record(e0, s);
   if (nwg > 0) {   // (no tokens: the reduction below writes zeros)
     const size_t lds = p->gen_lds_bytes[bf16];
-    const hipError_t eb = gen::launch_bwd_f32(a, dim3((unsigned)nwg, count), lds, s);
+    const hipError_t eb = bf16 ? gen::launch_bwd_bf16(a, dim3((unsigned)nwg, count), lds, s)
+                               : gen::launch_bwd_f32(a, dim3((unsigned)nwg, count), lds, s);
     if (eb != hipSuccess) return eb;
   }
   record(e1, s);

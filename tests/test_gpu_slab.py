@@ -1,0 +1,128 @@
+"""The slab kernels (bf16: source side -> coefficient-major workspace -> destination side) at the sizes where
+they can go wrong: token counts around a slab of 64 and a group of 16, blocks applied directly, in one
+radix-4 stage and in several, on either side, groups with a remainder, several slabs per dC partial row, and
+calls split over the workspace.  Supports are dense enough, or calls long enough, that the dispatch takes
+these kernels in both directions.  Element-wise bounds against the oracle as in the other parity tests."""
+import numpy as np
+import pytest
+
+from paper_2608_26430_amd import inputs
+from tests.parity_util import BwdBounds, FwdBounds, guarded, guards_intact, oracle_frame, plan_c, to_np, torch_act, user_dc, within
+
+torch = pytest.importorskip("torch")
+import paper_2608_26430_amd as ff  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def dev():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    torch.cuda.set_device(0)
+    return torch.device("cuda:0")
+
+
+def _ok(name, got, ref, bound):
+    ok, worst = within(got, ref, bound)
+    assert ok, f"{name}: element-wise bound exceeded (max err/bound {worst:.3g})"
+
+
+# (n, rho_in, m, rho_out, nnz, T): 32-wide blocks; 8-wide ones, 24 x 8 rows a remainder of 64-row groups;
+# 344-wide factored ones on both sides, and with direct ones on either; several stages: 4^2 x 17 and
+# 4^2 x 20 (two stages), 4^3 x 17 (three), beyond the generic kernels' token counts; 16500 tokens: two slabs
+# per dC partial row
+CASES = [(2048, 128, 2048, 128, 30000, t) for t in (1, 15, 63, 64, 65)] + [
+    (520, 130, 1032, 258, 30000, 81),
+    (2752, 16, 2752, 16, 30000, 70),
+    (2752, 16, 2048, 32, 40000, 129),
+    (2048, 32, 2752, 16, 40000, 17),
+    (544, 2, 544, 2, 700, 5009),
+    (640, 2, 640, 2, 900, 4449),
+    (2176, 2, 2176, 2, 3000, 2561),
+    (256, 16, 256, 16, 600, 16500),
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "n%d_m%d_nnz%d_T%d" % (c[0], c[2], c[4], c[5]))
+def test_slab_parity(dev, case):
+    n, rn, m, rm, nnz, T = case
+    k_in, k_out, s = n // rn, m // rm, 0.173
+    g = inputs.rng(n + 3 * m + T)
+    rows, cols = inputs.support(g, m, n, nnz)
+    vals = inputs.gaussian(g, (nnz,), std=0.02)
+    X, G = inputs.gaussian(g, (T, n), dtype="bf16"), inputs.gaussian(g, (T, m), dtype="bf16")
+    plan = ff.plan_create(ff.framegen(n, k_in, rn), ff.framegen(m, k_out, rm), rows, cols, max_tokens=T)
+    assert not plan.fast128
+    _, Xd = guarded(T, n, n + 8, "bf16", dev, X)
+    _, Gd = guarded(T, m, m + 16, "bf16", dev, G)
+    ybuf, Y = guarded(T, m, m + 8, "bf16", dev)
+    dxbuf, dX = guarded(T, n, n + 24, "bf16", dev)
+    c = plan_c(plan, vals, dev)
+    ff.adapter_fwd(plan, Xd, c, s, Y=Y)
+    Yb = ff.adapter_fwd(plan, Xd, c, s, Y=Y.clone(), beta=0.5)
+    _, dC = ff.adapter_bwd(plan, Xd, Gd, c, s, dX=dX, dC=torch.full((plan.coef_slots,), float("nan"), device=dev))
+    dXb, _ = ff.adapter_bwd(plan, Xd, Gd, c, s, dX=dX.clone(), beta_dx=-1.5, want_dc=False)
+    _, dC2 = ff.adapter_bwd(plan, Xd, Gd, c, s, want_dx=False)
+    torch.cuda.synchronize()
+    assert guards_intact(ybuf, T, m, m + 8, "bf16") and guards_intact(dxbuf, T, n, n + 24, "bf16")
+    P_in, P_out = oracle_frame(k_in, rn, n), oracle_frame(k_out, rm, m)
+    # rows are independent of one another: the edges of the calls' slabs and groups, and some between
+    t = np.unique(np.concatenate([np.arange(min(T, 20)), np.arange(max(0, T - 20), T),
+                                  np.clip([47, 48, 63, 64, 127, 128], 0, T - 1), inputs.rng(T).integers(0, T, 20)]))
+    fb = FwdBounds(P_in, P_out, rows, cols, vals, s, X[t], "bf16", k_in, k_out)
+    _ok("y", to_np(Y[t]), fb.y, fb.by)
+    _ok("y coef", fb.coef(to_np(Y[t])), fb.v, fb.bv)
+    fbb = FwdBounds(P_in, P_out, rows, cols, vals, s, X[t], "bf16", k_in, k_out, beta_y0=0.5 * to_np(Y[t]))
+    _ok("y beta", to_np(Yb[t]), fbb.y, fbb.by)
+    bt = BwdBounds(P_in, P_out, rows, cols, vals, s, X[t], G[t], "bf16", k_in, k_out)
+    _ok("dX", to_np(dX[t]), bt.dx, bt.bdx)
+    _ok("dX coef", bt.coef(to_np(dX[t])), bt.q, bt.bq)
+    bbb = BwdBounds(P_in, P_out, rows, cols, vals, s, X[t], G[t], "bf16", k_in, k_out, beta_dx0=-1.5 * to_np(dX[t]))
+    _ok("dX beta", to_np(dXb[t]), bbb.dx, bbb.bdx)
+    b = BwdBounds(P_in, P_out, rows, cols, vals, s, X, G, "bf16", k_in, k_out)
+    _ok("dC", user_dc(plan, dC), b.dc, b.bdc)
+    assert torch.equal(dC, dC2), "dC is not deterministic"
+
+
+@pytest.mark.parametrize("wide_in", [True, False], ids=["wide_input", "wide_output"])
+def test_slab_call_split_over_workspace(dev, wide_in):
+    """2400 tokens of a 28672-wide source side need more slabs than the workspace holds (36 of 64 tokens): rows
+    are bitwise those of calls on the two parts."""
+    wide, narrow, T = (28672, 224, 128), (256, 16, 16), 2400
+    (n, ki, rn), (m, ko, rm) = (wide, narrow) if wide_in else (narrow, wide)
+    g = inputs.rng(17)
+    rows, cols = inputs.support(g, m, n, 30000)
+    plan = ff.plan_create(ff.framegen(n, ki, rn), ff.framegen(m, ko, rm), rows, cols, max_tokens=T)
+    c = plan_c(plan, inputs.gaussian(g, (30000,), std=0.02), dev)
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(5)
+    X, G = (torch.randn((T, d), generator=gen, device=dev).bfloat16() for d in (n, m))
+    run = (lambda a, b: ff.adapter_fwd(plan, X[a:b], c, 0.3)) if wide_in else (
+        lambda a, b: ff.adapter_bwd(plan, X[a:b], G[a:b], c, 0.3)[0])
+    whole, parts = run(0, T), torch.cat([run(0, 1216), run(1216, T)])
+    torch.cuda.synchronize()
+    assert torch.isfinite(whole.float()).all() and torch.equal(whole, parts)
+
+
+@pytest.mark.parametrize("d,rho", [(1024, 64), (640, 2)], ids=["direct", "two_stages"])
+def test_slab_batch_split_over_workspace(dev, d, rho):
+    """Adapters that share a plan, together more slabs than the workspace holds: bitwise the calls one by one."""
+    T, count = 5120, 14
+    g = inputs.rng(23)
+    rows, cols = inputs.support(g, d, d, 9000)
+    f = ff.framegen(d, d // rho, rho)
+    plan = ff.plan_create(f, f, rows, cols, max_tokens=T, max_batch=count)
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(6)
+    X, G = (torch.randn((count, T, d), generator=gen, device=dev).bfloat16() for _ in range(2))
+    c = [plan_c(plan, inputs.gaussian(g, (9000,), std=0.02), dev) for _ in range(count)]
+    Y, dX = torch.zeros_like(X), torch.zeros_like(X)
+    dC = [torch.empty(plan.coef_slots, device=dev) for _ in range(count)]
+    ff.adapter_fwd_batched(plan, list(X), c, 0.3, list(Y))
+    ff.adapter_bwd_batched(plan, list(X), list(G), c, 0.3, list(dX), dC)
+    for i in range(count):
+        y = ff.adapter_fwd(plan, X[i], c[i], 0.3)
+        dx, dc = ff.adapter_bwd(plan, X[i], G[i], c[i], 0.3)
+        torch.cuda.synchronize()
+        assert torch.equal(y, Y[i]) and torch.equal(dx, dX[i]) and torch.equal(dc, dC[i])
