@@ -445,8 +445,8 @@ hipError_t launch_gather(const float* c, const float* const* cs, const int* idx,
 // workgroup per CU, so tiles go in rounds of `slots` and a call costs about rounds x (token rows
 // its sparse walks read per table row + a fixed part worth kTileOverhead of them).  Of the tile
 // sizes up to tt (the plan's LDS limit) the cheapest is taken, the larger one on ties (fewer
-// passes over the tables).  g4 counts whole groups of four tokens: the tiles that bf16 calls once took,
-// which still bound what ff_adapter_bwd_noalloc accepts.
+// passes over the tables).  g4 counts whole groups of four tokens (bf16 group calls, and what
+// ff_adapter_bwd_noalloc accepts).
 constexpr int kTileOverhead = 2;
 
 int call_tile_tokens(int tt, long T, int count, int slots, bool g4) {
@@ -522,7 +522,7 @@ hipError_t launch_fwd(const ff_plan* p, int bf16, int count, int T, ActPtrs X, i
   a.fin = p->fin->dev;
   a.fout = p->fout->dev;
   a.T = T;
-  a.tt = call_tile_tokens(p->gen_tile_tokens[bf16], T, count, p->gen_wgs, bf16 && p->gen_g4);
+  a.tt = call_tile_tokens(p->gen_tile_tokens[bf16], T, count, p->gen_wgs, false);
   a.ldt_in = p->gen_ldt_in[bf16];
   a.ldt_out = p->ldt_out[bf16];
   a.nch = p->gen_nch;
@@ -658,6 +658,8 @@ hipError_t launch_fwd_group(const ff_plan_group* g, int bf16, int T, const int* 
   a.fin = p->fin->dev;
   a.fout = p->fout->dev;
   a.T = T;
+  // (bf16 sizes by whole groups of four: 17 adapters 1152 -> 1664 wide of up to 418 tokens, 16 tokens a tile 18
+  // us, 14 31 us, 17 25 us)
   a.tt = call_tile_tokens(p->gen_tile_tokens[bf16], T, (int)count, p->gen_wgs, bf16 && p->gen_g4);
   a.ldt_in = p->gen_ldt_in[bf16];
   a.ldt_out = p->ldt_out[bf16];
