@@ -65,8 +65,7 @@ struct FrameDev {
   const float2* twk;
   // The same matrices for the slab kernels, whose contraction windows are clamped to the column:
   // lane (q, L) of step ks holds elements min(KS ks + VL q, W2 - VL) .. + VL - 1 (KS, VL as above),
-  // those below KS ks + VL q having zero weight (an earlier window holds them).  Frames in one
-  // radix-4 stage have one matrix per column a', [4][MT][KT][64], with the stage's twiddles folded in.
+  // those below KS ks + VL q having zero weight (an earlier window holds them).
   const void* wa16;
   const void* ws16;
 };

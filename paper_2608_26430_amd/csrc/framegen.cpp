@@ -532,8 +532,7 @@ extern "C" ff_status ff_framegen(int64_t d, int64_t k, int64_t rho, ff_frame** o
   const size_t n16 = (size_t)fd.MT * fd.KT * 64 * 8;     // bf16 elements per fragment set
   const size_t n32 = (size_t)fd.MT * fd.KT4 * 64 * 4;    // fp32 elements per fragment set
   std::vector<uint16_t> fa16(n16, 0), fs16(n16, 0);
-  const size_t nmat = nst == 1 ? 4 : 1;   // slab kernels: one matrix per radix-4 column
-  std::vector<uint16_t> wa16(nmat * n16, 0), ws16(nmat * n16, 0);
+  std::vector<uint16_t> wa16(n16, 0), ws16(n16, 0);
   std::vector<float> fa32(n32, 0.f), fs32(n32, 0.f), B32((size_t)(W * W));
   // analysis computes out[c] = sum_u B[u][c] in[u]  (matrix M_a[o][i] = B[i][o]);
   // synthesis computes out[u] = sum_c B[u][c] in[c] (matrix M_s[o][i] = B[o][i]).
@@ -546,22 +545,6 @@ extern "C" ff_status ff_framegen(int64_t d, int64_t k, int64_t rho, ff_frame** o
     if (o >= W2 || i >= W2) return 0.0;
     return factored ? M2[i * W2 + o] : B[o * W + i];
   };
-  // Matrix of radix-4 column a for the slab kernels, the stage's twiddle w = exp(2 pi i a b / k) folded
-  // in: analysis M_a diag(conj w) over the inputs b, synthesis diag(w) M_s over the outputs b.
-  auto wcos = [&](size_t a, int64_t b) { return a ? tw[2 * ((a - 1) * fd.k2 + b)] : 1.0; };
-  auto wsin = [&](size_t a, int64_t b) { return a ? tw[2 * ((a - 1) * fd.k2 + b) + 1] : 0.0; };
-  auto Mwa = [&](size_t a, int64_t o, int64_t i) {
-    if (o >= W2 || i >= W2 || a == 0) return Ma(o, i);
-    const int64_t b = i / 2;
-    const double re = Ma(o, 2 * b), im = Ma(o, 2 * b + 1);
-    return i % 2 ? re * wsin(a, b) + im * wcos(a, b) : re * wcos(a, b) - im * wsin(a, b);
-  };
-  auto Mws = [&](size_t a, int64_t o, int64_t i) {
-    if (o >= W2 || i >= W2 || a == 0) return Ms(o, i);
-    const int64_t b = o / 2;
-    const double re = Ms(2 * b, i), im = Ms(2 * b + 1, i);
-    return o % 2 ? re * wsin(a, b) + im * wcos(a, b) : re * wcos(a, b) - im * wsin(a, b);
-  };
   for (int mt = 0; mt < fd.MT; ++mt)
     for (int lane = 0; lane < 64; ++lane) {
       const int64_t o = 16 * mt + (lane & 15), q = lane >> 4;
@@ -573,9 +556,9 @@ extern "C" ff_status ff_framegen(int64_t d, int64_t k, int64_t rho, ff_frame** o
           fs16[idx] = bf16_rne((float)Ms(o, i));
           // clamped windows (the slab kernels): elements an earlier window holds get zero weight
           const int64_t base = 32 * ks + 8 * q, iw = std::max<int64_t>(0, std::min(base, W2 - 8)) + j;
-          for (size_t a = 0; a < nmat && iw >= base; ++a) {
-            wa16[a * n16 + idx] = bf16_rne((float)Mwa(a, o, iw));
-            ws16[a * n16 + idx] = bf16_rne((float)Mws(a, o, iw));
+          if (iw >= base) {
+            wa16[idx] = bf16_rne((float)Ma(o, iw));
+            ws16[idx] = bf16_rne((float)Ms(o, iw));
           }
         }
       for (int ks = 0; ks < fd.KT4; ++ks)
@@ -599,7 +582,7 @@ extern "C" ff_status ff_framegen(int64_t d, int64_t k, int64_t rho, ff_frame** o
   const size_t b16 = n16 * 2, b32 = n32 * 4, bB = B32.size() * 4, bT = tw32.size() * 4, bK = twk32.size() * 4;
   const size_t bU = up_src.size() * 4, bD = dn_v.size() * 4, bBt = Bt32.size() * 4;
   auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
-  const size_t total = 2 * up(b16) + 2 * up(nmat * b16) + 2 * up(b32) + up(bB) + up(bBt) + up(bT) + up(bK) + 2 * up(bU) + 2 * up(bD);
+  const size_t total = 4 * up(b16) + 2 * up(b32) + up(bB) + up(bBt) + up(bT) + up(bK) + 2 * up(bU) + 2 * up(bD);
   void* mem = nullptr;
   if (hipMalloc(&mem, total) != hipSuccess) {
     (void)hipGetLastError();
@@ -614,8 +597,8 @@ extern "C" ff_status ff_framegen(int64_t d, int64_t k, int64_t rho, ff_frame** o
   };
   fd.fa16 = put(fa16.data(), b16);
   fd.fs16 = put(fs16.data(), b16);
-  fd.wa16 = put(wa16.data(), nmat * b16);
-  fd.ws16 = put(ws16.data(), nmat * b16);
+  fd.wa16 = put(wa16.data(), b16);
+  fd.ws16 = put(ws16.data(), b16);
   fd.fa32 = put(fa32.data(), b32);
   fd.fs32 = put(fs32.data(), b32);
   fd.B32 = (const float*)put(B32.data(), bB);

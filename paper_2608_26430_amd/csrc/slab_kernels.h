@@ -199,10 +199,10 @@ __device__ __forceinline__ void analysis_direct(const FrameDev& f, const void* f
   }
 }
 
-// Factored blocks (one per group).  On the way into LDS the radix-4 stage's sums
-// Y_a'[c] = sum_a x[a k2 + c] (-i)^(a a') are formed in registers (the twiddles w^(-a' c) are folded
-// into the four matrices of `frag`); a token's column a' is nw windows of VL elements, 16 bytes
-// each, the last clamped to end with the column.
+// Factored blocks (one per group).  On the way into LDS the radix-4 stage
+// Y_a'[c] = w^(-a' c) sum_a x[a k2 + c] (-i)^(a a') is formed in registers, in fp32, twiddles
+// included; a token's column a' is nw windows of VL elements, 16 bytes each, the last clamped to end
+// with the column.  A thread keeps one window, whose twiddles it loads once, of every `per`-th token.
 __device__ __forceinline__ int radix_windows(int W2, int VL) { return (W2 + VL - 1) / VL; }
 __device__ __forceinline__ int radix_stride(int nw) { return (4 * nw | 1) * 16; }
 
@@ -211,16 +211,24 @@ __device__ __forceinline__ void radix_load(const FrameDev& f, const unsigned cha
                                            unsigned char* lds) {
   using T = SlabT<BF16>;
   constexpr int VL = T::TC, NC = VL / 2, S = T::S, kU = 3;
-  const int tid = phase_tid(), W2 = f.W2, nw = radix_windows(W2, VL), sb = radix_stride(nw), n = S * nw;
+  const int tid = phase_tid(), W2 = f.W2, nw = radix_windows(W2, VL), sb = radix_stride(nw);
   const float inv = 1.f / (float)nw;
-  for (int i0 = tid; i0 < n; i0 += kU * kSlabThreads) {
+  const int per = div_small(kSlabThreads, nw, inv), t0 = div_small(tid, nw, inv), w = tid - __mul24(t0, nw);
+  if (t0 >= per) return;
+  const int e0 = min(w * VL, W2 - VL);
+  float2 tw[3][NC];
+#pragma unroll
+  for (int a = 0; a < 3; ++a)
+#pragma unroll
+    for (int k = 0; k < NC; ++k) tw[a][k] = gload(f.tw + a * f.k2 + e0 / 2 + k);
+  src += e0 * T::ESZ;
+  lds += 16 * w;
+  for (int ts = t0; ts < S; ts += kU * per) {
     u32x4v x[kU][4];
-    int at[kU];
 #pragma unroll
     for (int u = 0; u < kU; ++u) {
-      const int i = min(i0 + u * kSlabThreads, n - 1), t = div_small(i, nw, inv), w = i - t * nw;
-      at[u] = t * sb + 16 * w;
-      const unsigned char* p = src + (long)min(t, nt - 1) * ld + min(w * VL, W2 - VL) * T::ESZ;
+      const int t = ts + u * per;
+      const unsigned char* p = src + (long)min(t, nt - 1) * ld;
 #pragma unroll
       for (int a = 0; a < 4; ++a) {   // (columns start at multiples of one complex coordinate)
         x[u][a] = u32x4v(*(const FF_GLOBAL u32x4a*)(p + a * W2 * T::ESZ));
@@ -229,7 +237,8 @@ __device__ __forceinline__ void radix_load(const FrameDev& f, const unsigned cha
     }
 #pragma unroll
     for (int u = 0; u < kU; ++u) {
-      if (i0 + u * kSlabThreads >= n) break;
+      const int t = ts + u * per;
+      if (t >= S) break;
       float y[4][VL];
 #pragma unroll
       for (int k = 0; k < NC; ++k) {
@@ -246,8 +255,9 @@ __device__ __forceinline__ void radix_load(const FrameDev& f, const unsigned cha
         }
         const float2 s02 = cadd(v[0], v[2]), d02 = csub(v[0], v[2]);
         const float2 s13 = cadd(v[1], v[3]), d13 = csub(v[1], v[3]);
-        const float2 o[4] = {cadd(s02, s13), make_float2(d02.x + d13.y, d02.y - d13.x), csub(s02, s13),
-                             make_float2(d02.x - d13.y, d02.y + d13.x)};
+        const float2 o[4] = {cadd(s02, s13), cmulc(make_float2(d02.x + d13.y, d02.y - d13.x), tw[0][k]),
+                             cmulc(csub(s02, s13), tw[1][k]),
+                             cmulc(make_float2(d02.x - d13.y, d02.y + d13.x), tw[2][k])};
 #pragma unroll
         for (int a = 0; a < 4; ++a) {
           y[a][2 * k] = o[a].x;
@@ -255,15 +265,9 @@ __device__ __forceinline__ void radix_load(const FrameDev& f, const unsigned cha
         }
       }
 #pragma unroll
-      for (int a = 0; a < 4; ++a) *reinterpret_cast<u32x4v*>(lds + at[u] + 16 * a * nw) = pack16<BF16>(y[a]);
+      for (int a = 0; a < 4; ++a) *reinterpret_cast<u32x4v*>(lds + t * sb + 16 * a * nw) = pack16<BF16>(y[a]);
     }
   }
-}
-
-template <class V, int KT>
-__device__ __forceinline__ void load_frags4(const void* frag, int MT, int mt, int lane, V (&fr)[4][KT]) {
-#pragma unroll
-  for (int a = 0; a < 4; ++a) load_frags<V, KT>(frag, a * MT + mt, lane, fr[a]);
 }
 
 // The DFTs of size k/4 of the four columns.  The tile takes the windows' LDS, so the results wait in
@@ -277,7 +281,7 @@ __device__ __forceinline__ void analysis_radix(const FrameDev& f, const void* fr
   const int lane = phase_tid() & 63, q = lane >> 4, L = lane & 15, W2 = f.W2, nw = radix_windows(W2, M::VL),
             sb = radix_stride(nw);
   const Items items(f.MT, 1);
-  V fr[4][KT];
+  V fr[KT];
   R out[NI][NTH][4];
   int have = -1;
 #pragma unroll
@@ -286,7 +290,7 @@ __device__ __forceinline__ void analysis_radix(const FrameDev& f, const void* fr
     if (it >= items.i1) break;   // uniform
     int mt, bl, th;
     items.get(it, mt, bl, th);
-    if (mt != have) load_frags4<V, KT>(frag, f.MT, mt, lane, fr);
+    if (mt != have) load_frags<V, KT>(frag, mt, lane, fr);
     have = mt;
     f32x4 acc[NTH][4];
 #pragma unroll
@@ -301,7 +305,7 @@ __device__ __forceinline__ void analysis_radix(const FrameDev& f, const void* fr
       for (int g = 0; g < NTH; ++g)
 #pragma unroll
         for (int a = 0; a < 4; ++a)
-          acc[g][a] = M::step(*reinterpret_cast<const V*>(p + 16 * g * sb + 16 * a * nw), fr[a][ks], acc[g][a]);
+          acc[g][a] = M::step(*reinterpret_cast<const V*>(p + 16 * g * sb + 16 * a * nw), fr[ks], acc[g][a]);
     }
 #pragma unroll
     for (int g = 0; g < NTH; ++g)
@@ -625,8 +629,8 @@ __device__ __forceinline__ typename Mfma<BF16>::V tile_operand(const unsigned ch
 // out = s P v (+ beta out) from the tile for one group of blocks of a slab, through the stage, where
 // the old values wait when BETA, so that each output is rounded once.  Work items as above (token
 // groups past the slab's tokens are left out).  Factored blocks: the DFT of size k/4 of the four
-// columns (with the twiddles) leaves each lane with two complex coordinates of all four, which the
-// radix-4 stage's sums combine in registers; their stage takes the tile's LDS, so the results wait in registers until
+// columns leaves each lane with two complex coordinates of all four, which the radix-4 stage, twiddles
+// included, combines in registers in fp32; their stage takes the tile's LDS, so the results wait in registers until
 // every wave has read the tile.
 template <bool BF16, int KT, bool RADIX, bool BETA>
 __device__ __forceinline__ void group_synthesis(const FrameDev& f, const void* frag, unsigned char* tile,
@@ -675,7 +679,8 @@ __device__ __forceinline__ void group_synthesis(const FrameDev& f, const void* f
     }
   } else {
     constexpr int NI = radix_items<BF16>(KT);
-    V fr[4][KT];
+    V fr[KT];
+    float2 tw[2][3];   // of the lane's two complex coordinates
     // results as stored, or in fp32 until the old values are added
     using O = typename std::conditional<BF16 && !BETA, unsigned, float2>::type;
     O out[NI][NTH][2][4];   // [item][token group][complex coordinate][a]
@@ -686,7 +691,13 @@ __device__ __forceinline__ void group_synthesis(const FrameDev& f, const void* f
       int mt, bl, th;
       items.get(it, mt, bl, th);
       if (16 * NTH * th >= nt) continue;   // uniform
-      if (mt != have) load_frags4<V, KT>(frag, f.MT, mt, lane, fr);
+      if (mt != have) {
+        load_frags<V, KT>(frag, mt, lane, fr);
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+          for (int a = 0; a < 3; ++a) tw[u][a] = gload(f.tw + a * f.k2 + min(8 * mt + 2 * q + u, f.k2 - 1));
+      }
       have = mt;
 #pragma unroll
       for (int g = 0; g < NTH; ++g) {
@@ -699,13 +710,16 @@ __device__ __forceinline__ void group_synthesis(const FrameDev& f, const void* f
           const int e = min(ks * M::KS + q * M::VL, W2 - M::VL);
 #pragma unroll
           for (int a = 0; a < 4; ++a)
-            acc[a] = M::step(fr[a][ks], tile_operand<BF16>(tile, a * W2 + e, NTH * th + g, L), acc[a]);
+            acc[a] = M::step(fr[ks], tile_operand<BF16>(tile, a * W2 + e, NTH * th + g, L), acc[a]);
         }
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
           float2 y[4];
 #pragma unroll
-          for (int a = 0; a < 4; ++a) y[a] = make_float2(acc[a][2 * u], acc[a][2 * u + 1]);
+          for (int a = 0; a < 4; ++a) {
+            y[a] = make_float2(acc[a][2 * u], acc[a][2 * u + 1]);
+            if (a > 0) y[a] = cmul(y[a], tw[u][a - 1]);
+          }
           const float2 s02 = cadd(y[0], y[2]), d02 = csub(y[0], y[2]), s13 = cadd(y[1], y[3]), d13 = csub(y[1], y[3]);
           float2 x[4];
           x[0] = cadd(s02, s13);

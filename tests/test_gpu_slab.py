@@ -126,3 +126,71 @@ def test_slab_batch_split_over_workspace(dev, d, rho):
         dx, dc = ff.adapter_bwd(plan, X[i], G[i], c[i], 0.3)
         torch.cuda.synchronize()
         assert torch.equal(y, Y[i]) and torch.equal(dx, dX[i]) and torch.equal(dc, dC[i])
+
+
+def _bf16(x):
+    return inputs.bf16_round(np.asarray(x, dtype=np.float32)).astype(np.float64)
+
+
+def _factored(k):
+    """The arithmetic of a factored frame's kernels, k = 4 k2: analysis and synthesis of one block.  The radix-4
+    stage and its twiddles are fp32 (here float64), its results are rounded to bf16 on the way into the DFT of
+    size k2, whose matrix is rounded to bf16; the synthesis rounds only its outputs."""
+    k2 = k // 4
+    ph = lambda x: np.exp(2j * np.pi * x)
+    lb = np.outer(np.arange(k2), np.arange(k2)) % k2 / k2
+    D = ph(-lb) / np.sqrt(k)
+    D = _bf16(D.real) + 1j * _bf16(D.imag)
+    w = np.stack([ph(a * np.arange(k2) / k) for a in range(4)])
+    R = ph(np.outer(np.arange(4), np.arange(4)) / 4)
+
+    def analysis(x):
+        y = np.conj(w) * (np.conj(R) @ (x[0::2] + 1j * x[1::2]).reshape(4, k2))
+        y = _bf16(y.real) + 1j * _bf16(y.imag)
+        z = (y @ D.T).T.reshape(-1)          # frequency a' + 4 l
+        return _bf16(np.stack([z.real, z.imag], 1).reshape(-1))
+
+    def synthesis(z):
+        y = (z[0::2] + 1j * z[1::2]).reshape(k2, 4).T @ np.conj(D)
+        x = (R @ (w * y)).reshape(-1)
+        return _bf16(np.stack([x.real, x.imag], 1).reshape(-1))
+
+    return analysis, synthesis
+
+
+@pytest.mark.parametrize("factored_input", [True, False], ids=["factored_input", "factored_output"])
+@pytest.mark.parametrize("k", [72, 128, 172, 196, 256])
+def test_factored_frames_keep_fp32_twiddles(dev, k, factored_input):
+    """The results of a factored frame are those of the arithmetic above, to a few roundings that fall the other
+    way (an fp32 sum of at most 512 terms is off by less than 2^-15, so about one value in 2^7 of those next to a
+    rounding boundary, 2^-8 apart, moves by 2^-8: 2^-8 sqrt(2^-7) = 3.5e-4 in the 2-norm at the very most).
+    Twiddles rounded to bf16 give 3e-3.  One token is not zero, so that dC is one product per entry."""
+    W, kd, T, t = 2 * k, 16, 640, 37
+    n, m = (W, 2 * kd) if factored_input else (2 * kd, W)
+    (ki, ko) = (k, kd) if factored_input else (kd, k)
+    f_in, f_out = ff.framegen(n, ki, 2), ff.framegen(m, ko, 2)
+    g = inputs.rng(k)
+    wide = np.arange(W)
+    narrow = g.permutation(np.resize(np.arange(2 * kd), W))
+    rows, cols = (narrow, wide) if factored_input else (wide, narrow)
+    vals = _bf16(inputs.gaussian(g, (W,)))
+    x, gr = inputs.gaussian(g, (1, n), dtype="bf16")[0], inputs.gaussian(g, (1, m), dtype="bf16")[0]
+    X, G = np.zeros((T, n), np.float32), np.zeros((T, m), np.float32)
+    X[t], G[t] = x, gr
+    plan = ff.plan_create(f_in, f_out, rows, cols, max_tokens=T)
+    Xd, Gd, c = torch_act(X, "bf16", dev), torch_act(G, "bf16", dev), plan_c(plan, vals, dev)
+    dX, dC = ff.adapter_bwd(plan, Xd, Gd, c, 1.0)
+    torch.cuda.synchronize()
+    analysis, synthesis = _factored(k)
+    P = oracle_frame(kd, 2, 2 * kd)
+    B = _bf16(P.toarray() if hasattr(P, "toarray") else P)
+    z = analysis(np.float64(x)) if factored_input else _bf16(B.T @ x)
+    u = _bf16(B.T @ gr) if factored_input else analysis(np.float64(gr))
+
+    def close(name, got, ref):
+        err = np.linalg.norm(got - ref) / np.linalg.norm(ref)
+        assert err < 3.5e-4, f"{name}: {err:.2e} from the kernels' arithmetic"
+
+    close("dC", user_dc(plan, dC), u[rows] * z[cols])
+    if factored_input:
+        close("dX", to_np(dX[t]), synthesis(_bf16(vals * u[rows])))
