@@ -283,7 +283,10 @@ ff_status ff_merge_delta(const ff_plan* p, const float* c_vals, float scale, int
  *       token counts (each clamped to [0, T]) so that requests of different
  *       lengths share a launch: adapter i then reads and writes only its first
  *       tokens[i] rows (dC sums over those rows; 0 rows give dC = 0).
- *   Results per adapter equal those of the single calls on its own plan.
+ *   Results per adapter equal those of the single calls on its own plan: bit for
+ *   bit on plans that report FF_Q_FAST128, and
+ *   elsewhere up to the rounding of the activation type, since the kernels that
+ *   take a bf16 call depend on its number of tokens there.
  */
 typedef struct ff_plan_group ff_plan_group;
 ff_status ff_plan_group_create(int64_t count, const ff_plan* const* plans, ff_plan_group** out);

@@ -219,22 +219,6 @@ inline bool slab_frame(const FrameDev& f) {
 // Frames in several stages: both sides' coefficients pass through the workspace (slab_ms.hip).
 inline bool slab_ms_frame(const FrameDev& f) { return f.nst >= 2; }
 
-// Whether a forward of `tokens` tokens (all adapters of the call) on 128-wide blocks is quicker in the slab
-// kernels than in the fused one, whose workgroups each walk the whole support for 8 tokens.  Microseconds,
-// fitted to calls of 1 to 1024 tokens (fused -> slab): 4096 -> 4096 with 10,000 entries, 1 token 23.6 ->
-// 10.4, 16 17.7 -> 10.6, 64 13.0 -> 11.4, 128 12.3 -> 11.8 (the fused kernel by this rule), 512 12.1 ->
-// 12.1; 40,000 entries, 512 tokens 22.0 -> 13.9; 4096 -> 8192 with 40,000, 1 token 78.2 -> 11.3, 512 27.0
-// -> 15.4; 1024 -> 1024 with 2,000, 16 tokens 5.9 -> 10.2 (fused).  Beyond 1024 tokens the slab
-// kernels' traffic takes the gain away (2048 tokens, 40,000 entries: 24.9 -> 28.0).
-constexpr int64_t kFusedRuleTokens = 1024;
-inline bool fused_forward_slower(int64_t n, int64_t m, int64_t nnz, int64_t tokens) {
-  if (tokens < 1 || tokens > kFusedRuleTokens) return false;
-  const double w = (double)(n + m), e = (double)nnz, t = (double)tokens;
-  const double fused = 3.5 + 4e-4 * w + 1e-3 * e * (0.38 + 10.4 / (t < 8 ? 8 : t));
-  const double slab = 10.5 + t * (8e-7 * w + 1e-7 * e);
-  return fused > slab + 0.5;
-}
-
 // One adapter's view of its plan inside a plan group (ff_plan_group): the tables and the
 // workspace (batch slot 0 of the plan's own) that the group kernels read per adapter.
 struct FastDesc {   // fused 128-wide kernels

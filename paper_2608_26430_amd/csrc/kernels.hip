@@ -508,16 +508,9 @@ bool slab_forward(const ff_plan* p, int64_t tokens, int64_t most) {
 hipError_t launch_fwd(const ff_plan* p, int bf16, int count, int T, ActPtrs X, int64_t ldx, const float* c,
                       const float* const* cs, float scale, float beta, ActPtrs Y, int64_t ldy, float* c_saved,
                       hipStream_t s) {
-  const int64_t tokens = (int64_t)T * count;
-  const bool slab = p->fast.enabled ? p->slab.enabled && fused_forward_slower(p->fin->dv, p->fout->dv, p->nnz, tokens)
-                                    : slab_forward(p, tokens, T);
-  if (bf16 && p->fast.enabled && !slab)
-    return launch_fwd128(p, count, T, X, ldx, c, cs, scale, beta, Y, ldy, c_saved, s);
-  if (bf16 && slab) {
-    const hipError_t e = launch_fwd_slab(p, bf16, count, T, X, ldx, c, cs, scale, beta, Y, ldy, s);
-    if (e != hipSuccess || !c_saved || !p->fast.enabled) return e;
-    return launch_fwd128(p, count, 0, X, ldx, c, cs, scale, beta, Y, ldy, c_saved, s);   // the copy alone
-  }
+  if (bf16 && p->fast.enabled) return launch_fwd128(p, count, T, X, ldx, c, cs, scale, beta, Y, ldy, c_saved, s);
+  if (bf16 && slab_forward(p, (int64_t)T * count, T))
+    return launch_fwd_slab(p, bf16, count, T, X, ldx, c, cs, scale, beta, Y, ldy, s);
   FwdArgs a{};
   a.fin = p->fin->dev;
   a.fout = p->fout->dev;

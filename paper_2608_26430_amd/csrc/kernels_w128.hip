@@ -621,11 +621,24 @@ __device__ __forceinline__ void analysis_phase(const Frag& F, const u16* rows, l
   wave_lds_fence();
 }
 
+// Whether the first T rows of X (n wide) and Y (m wide) share elements; rows of one matrix side by
+// side do not.
+__device__ __forceinline__ bool rows_overlap(const u16* X, long ldx, int n, const u16* Y, long ldy, int m, int T) {
+  const long d = Y - X;
+  if (d >= (T - 1) * ldx + n || -d >= (T - 1) * ldy + m) return false;
+  const bool beside = ldx == ldy && (d >= 0 ? d >= n && d + m <= ldx : -d >= m && -d + n <= ldx);
+  return !beside;
+}
+
 // The stream tables are separate restrict-qualified arguments: the kernel never writes them,
 // so their wave-uniform reads become scalar loads, which do not wait for vector stores.
-// GROUP: adapter blockIdx.y runs its own plan (a.group) on its own token count; such calls keep
-// no backward-ordered copy (the group backward writes its own).
-template <bool BETA, bool GROUP>
+// GROUP: adapter blockIdx.y runs its own plan (a.group) on its own token count.  SAVE: the
+// coefficients are also written in the backward's slot order (not in group calls, whose backward
+// writes its own copy).
+// gridDim.z workgroups share a tile: each analyses all of its tokens and takes every gridDim.z-th run
+// of kWaves output pairs (the arithmetic of an output does not depend on it).  Where Y overwrites X,
+// which the other workgroups still read, the first one does them all.
+template <bool BETA, bool GROUP, bool SAVE>
 __global__ void __launch_bounds__(kThreads, 2) fwd128(FastArgs a, const int4* __restrict__ pl,
                                                       const unsigned* __restrict__ fst,
                                                       const unsigned* __restrict__ em) {
@@ -647,17 +660,21 @@ __global__ void __launch_bounds__(kThreads, 2) fwd128(FastArgs a, const int4* __
   u16* Y = reinterpret_cast<u16*>(a.Ys ? a.Ys[bi] : a.Y) + (long)t0 * a.ldy;
   const float* cv = a.cs ? a.cs[bi] : a.c;
   const int npo = a.nblk_out / 2, lastp = npo - 1;
+  int split = (int)gridDim.z;
+  if (split > 1 && rows_overlap(X, a.ldx, a.nblk_in * kW, Y, a.ldy, a.nblk_out * kW, nt)) split = 1;
+  if ((int)blockIdx.z >= split) return;   // uniform
+  const int p0 = wave + kWaves * (int)blockIdx.z, pstep = kWaves * split;   // this wave's output pairs
 
   // This workgroup's share of the coefficient copy in the backward's slot order: coefficient
   // slots, then the backward's padding slots (zero).  Read first, written after the analysis;
   // every lane loads and stores (lanes past the share repeat its last item, an identical write).
-  const int nitem = GROUP ? 0 : a.nslot + a.nbpad;
-  const int per = (nitem + (int)gridDim.x - 1) / (int)gridDim.x;
-  const int j0 = (int)blockIdx.x * per, jn = min(nitem, j0 + per);
+  const int nitem = SAVE ? a.nslot + a.nbpad : 0, nshare = (int)gridDim.x * split;
+  const int per = (nitem + nshare - 1) / nshare;
+  const int j0 = ((int)blockIdx.z * (int)gridDim.x + (int)blockIdx.x) * per, jn = min(nitem, j0 + per);
   int spos = 0;
   float sval = 0.f;
   float* csave = nullptr;
-  if constexpr (!GROUP) {
+  if constexpr (SAVE) {
     const int js = max(min(j0 + (int)threadIdx.x, jn - 1), 0);
     const bool is_coef = js < a.nslot;
     const int pc = gld(a.pos)[min(js, a.nslot - 1)], pp = gld(a.bpad)[min(max(js - a.nslot, 0), a.nbpad - 1)];
@@ -673,8 +690,8 @@ __global__ void __launch_bounds__(kThreads, 2) fwd128(FastArgs a, const int4* __
   // first stream chunk of this wave's first output pair, in flight during the analysis; the
   // pair entries run one pair ahead of the chunks, so their scalar loads are never waited on
   // at a pair's start
-  int4 q = pl[min(wave, lastp)];
-  int4 qn = pl[min(wave + kWaves, lastp)];
+  int4 q = pl[min(p0, lastp)];
+  int4 qn = pl[min(p0 + pstep, lastp)];
   FwdChunk ch;
   fwd_load(fst, q.x, q.y, 0, cv, lane, ch);
   issue_point();
@@ -682,13 +699,14 @@ __global__ void __launch_bounds__(kThreads, 2) fwd128(FastArgs a, const int4* __
   Frag F;
   frag_stage(fr, reinterpret_cast<u32x4*>(smem), lane, F);
   analysis_phase(F, X, a.ldx, nt, a.nblk_in / 2, wave, lane, zL, tile);
-  if constexpr (!GROUP) gst(csave)[spos] = sval;
+  if constexpr (SAVE) gst(csave)[spos] = sval;
   __syncthreads();
 
   // One output pair: its chunk is in `cur`; the next pair's chunk is loaded into `nxt` first,
   // a whole pair ahead of its use.  The loop runs two pairs per iteration with the buffers'
   // roles swapped, so no chunk is ever copied between registers.
-  const int steps = (npo - wave + kWaves - 1) / kWaves;
+  const int steps = (npo - p0 + pstep - 1) / pstep;
+  int done = 0;
   // A pair's synthesis is stored at the start of the wave's next pair, after that pair's
   // stream loads: the loads do not queue behind the stores, and the MFMA results are waited
   // for a whole sparse phase later.
@@ -697,11 +715,11 @@ __global__ void __launch_bounds__(kThreads, 2) fwd128(FastArgs a, const int4* __
   // may not have been issued makes it wait for all of them).
   f32x4 acc[kMT];
   auto pair = [&](int p, FwdChunk& cur, FwdChunk& nxt, auto first) {
-    prio_by_progress((p - wave) / kWaves, steps);
+    prio_by_progress(done++, steps);
     fwd_load(fst, qn.x, qn.y, 0, cv, lane, nxt);
-    const int4 qnn = pl[min(p + 2 * kWaves, lastp)];
+    const int4 qnn = pl[min(p + 2 * pstep, lastp)];
     issue_point();
-    if constexpr (!decltype(first)::value) store_act<BETA>(Y, a.ldy, nt, 2 * (p - kWaves), lane, acc, a.beta, tile);
+    if constexpr (!decltype(first)::value) store_act<BETA>(Y, a.ldy, nt, 2 * (p - pstep), lane, acc, a.beta, tile);
     // v = C z for this pair into the tile
     const int off = q.x, len = q.y;
     zero_tile(tile, lane);
@@ -724,27 +742,27 @@ __global__ void __launch_bounds__(kThreads, 2) fwd128(FastArgs a, const int4* __
     qn = qnn;
   };
   FwdChunk ch2;
-  if (wave < npo) {
+  if (p0 < npo) {
     const std::true_type first;
     const std::false_type later;
-    int plast = wave;
-    pair(wave, ch, ch2, first);
-    if (wave + kWaves < npo) {
-      pair(wave + kWaves, ch2, ch, later);
-      plast = wave + kWaves;
+    int plast = p0;
+    pair(p0, ch, ch2, first);
+    if (p0 + pstep < npo) {
+      pair(p0 + pstep, ch2, ch, later);
+      plast = p0 + pstep;
     }
-    for (int p = wave + 2 * kWaves; p < npo; p += 2 * kWaves) {
+    for (int p = p0 + 2 * pstep; p < npo; p += 2 * pstep) {
       pair(p, ch, ch2, later);
       plast = p;
-      if (p + kWaves < npo) {
-        pair(p + kWaves, ch2, ch, later);
-        plast = p + kWaves;
+      if (p + pstep < npo) {
+        pair(p + pstep, ch2, ch, later);
+        plast = p + pstep;
       }
     }
     store_act<BETA>(Y, a.ldy, nt, 2 * plast, lane, acc, a.beta, tile);
   }
   // shares longer than one slot per thread (grids of few tiles)
-  if (!GROUP && per > kThreads)
+  if (SAVE && per > kThreads)
     for (int j = j0 + kThreads + (int)threadIdx.x; j < jn; j += kThreads) {
       if (j < a.nslot)
         gst(csave)[gld(a.pos)[j]] = gld(cv)[j];
@@ -1345,13 +1363,14 @@ hipError_t allow_lds(K* kernel) {
 hipError_t configure_fast128() {
   static hipError_t once = [] {
     hipError_t e = hipSuccess;
-    const hipError_t r[] = {allow_lds(&fwd128<false, false>),       allow_lds(&fwd128<true, false>),
+    const hipError_t r[] = {allow_lds(&fwd128<false, false, false>), allow_lds(&fwd128<true, false, false>),
+                            allow_lds(&fwd128<false, false, true>), allow_lds(&fwd128<true, false, true>),
                             allow_lds(&bwd128<true, true, false, false>), allow_lds(&bwd128<true, true, true, false>),
                             allow_lds(&bwd128<true, false, false, false>), allow_lds(&bwd128<true, false, true, false>),
                             allow_lds(&bwd128<false, true, false, false>), allow_lds(&bwd16<true, true, false, false>),
                             allow_lds(&bwd16<true, true, true, false>),   allow_lds(&bwd16<true, false, false, false>),
                             allow_lds(&bwd16<true, false, true, false>),  allow_lds(&bwd16<false, true, false, false>),
-                            allow_lds(&fwd128<false, true>),        allow_lds(&fwd128<true, true>),
+                            allow_lds(&fwd128<false, true, false>), allow_lds(&fwd128<true, true, false>),
                             allow_lds(&bwd128<true, true, false, true>), allow_lds(&bwd128<true, true, true, true>),
                             allow_lds(&bwd128<true, false, false, true>), allow_lds(&bwd128<true, false, true, true>),
                             allow_lds(&bwd128<false, true, false, true>), allow_lds(&bwd16<true, true, false, true>),
@@ -1381,13 +1400,26 @@ size_t fast16_lds_bytes(int nblk_out) {
   return b < frag ? frag : b;
 }
 
+// Workgroups per tile of a forward.  Few tiles leave CUs idle, and one workgroup's walk over its output
+// pairs is then the call, so the pairs are spread while there is a CU for every workgroup; no further,
+// since each analyses the whole tile.  Microseconds with 1 / 2 / 4 workgroups a tile, 4096 -> 4096 with
+// 10,000 entries: 16 tokens 10.9 / 8.0 / 6.3, 512 (64 tiles) 11.7 / 8.7 / 7.4, 1024 (128 tiles) 12.7 / 10.0 /
+// 10.6, 4096 (512 tiles) 20.7 / 27.3 / 36.4; 16 tenants of up to 128 tokens 16.1 / 14.5 / 19.7; 8192 -> 8192
+// with 40,000, 16 tokens 27.9 / 17.9 / 12.4 and with 8 workgroups 9.6.
+static unsigned fwd_split(const ff_plan* p, long tiles) {
+  const int most = (p->fout->dev.nblk / 2 + kWaves - 1) / kWaves;   // rounds of output pairs
+  for (int rounds = 1; rounds < most; ++rounds) {
+    const int split = (most + rounds - 1) / rounds;
+    if (tiles * split <= p->gen_wgs) return (unsigned)split;
+  }
+  return 1;
+}
+
 hipError_t launch_fwd128(const ff_plan* p, int count, int T, ActPtrs X, int64_t ldx, const float* c,
                          const float* const* cs, float scale, float beta, ActPtrs Y, int64_t ldy, float* c_saved,
                          hipStream_t s) {
   FastArgs a{};
-  // the backward-ordered coefficient copy goes to the caller's buffer, or to the plan's own
-  // copy, which every backward that is not handed a saved copy rewrites first
-  a.csave = c_saved ? c_saved : p->fast.coef_bwd;
+  a.csave = c_saved;
   a.pos = p->fast.bwd_pos;
   a.nslot = p->fast.coef_slots;
   a.bpad = p->fast.bwd_pad;
@@ -1407,7 +1439,8 @@ hipError_t launch_fwd128(const ff_plan* p, int count, int T, ActPtrs X, int64_t 
   a.cs = cs;
   a.scale = scale;
   a.beta = beta;
-  const dim3 grid((unsigned)((T + kTT - 1) / kTT), (unsigned)count);
+  const unsigned tiles = (unsigned)((T + kTT - 1) / kTT);
+  const dim3 grid(tiles, (unsigned)count, fwd_split(p, (long)tiles * count));
   const size_t lds = fast128_lds_bytes(a.nblk_in);
   hipEvent_t e0, e1;
   take_timing_events(&e0, &e1);
@@ -1419,12 +1452,10 @@ hipError_t launch_fwd128(const ff_plan* p, int count, int T, ActPtrs X, int64_t 
     return hipGetLastError();
   }
   rec(e0, s);
-  if (beta != 0.f)
-    hipLaunchKernelGGL((fwd128<true, false>), grid, dim3(kThreads), lds, s, a, p->fast.fwd_pl, p->fast.fwd_st,
-                       p->fast.fwd_em);
-  else
-    hipLaunchKernelGGL((fwd128<false, false>), grid, dim3(kThreads), lds, s, a, p->fast.fwd_pl, p->fast.fwd_st,
-                       p->fast.fwd_em);
+  const bool b = beta != 0.f;
+  hipLaunchKernelGGL((c_saved ? (b ? fwd128<true, false, true> : fwd128<false, false, true>)
+                              : (b ? fwd128<true, false, false> : fwd128<false, false, false>)),
+                     grid, dim3(kThreads), lds, s, a, p->fast.fwd_pl, p->fast.fwd_st, p->fast.fwd_em);
   rec(e1, s);
   return hipGetLastError();
 }
@@ -1558,15 +1589,15 @@ hipError_t launch_fwd128_group(const ff_plan_group* g, int T, const int* tokens,
   a.beta = beta;
   a.group = g->fast;
   a.tokens = tokens;
-  const dim3 grid((unsigned)((T + kTT - 1) / kTT), (unsigned)g->count);
+  const unsigned tiles = (unsigned)((T + kTT - 1) / kTT);
+  // (per-adapter token counts are on the device: half of the most, on average)
+  const dim3 grid(tiles, (unsigned)g->count, fwd_split(p, (long)tiles * g->count / (tokens ? 2 : 1)));
   const size_t lds = fast128_lds_bytes(a.nblk_in);
   hipEvent_t e0, e1;
   take_timing_events(&e0, &e1);
   rec(e0, s);
-  if (beta != 0.f)
-    hipLaunchKernelGGL((fwd128<true, true>), grid, dim3(kThreads), lds, s, a, nullptr, nullptr, nullptr);
-  else
-    hipLaunchKernelGGL((fwd128<false, true>), grid, dim3(kThreads), lds, s, a, nullptr, nullptr, nullptr);
+  hipLaunchKernelGGL((beta != 0.f ? fwd128<true, true, false> : fwd128<false, true, false>), grid, dim3(kThreads), lds, s,
+                     a, nullptr, nullptr, nullptr);
   rec(e1, s);
   return hipGetLastError();
 }

@@ -120,6 +120,38 @@ def test_group_mixes_fused_backward_tile_sizes(dev):
         assert torch.equal(rc, dC[i])
 
 
+def test_fused_results_do_not_depend_on_the_call(dev):
+    """4096 wide with 10,000 entries: a group's forward, a batched one and a single call of any length give a
+    token the same bits, also where few tokens spread a tile over several workgroups, and where Y overwrites X."""
+    n, nnz, T, s = 4096, 10_000, 300, 0.4
+    f = ff.framegen(n, 64, 64)
+    g = inputs.rng(12)
+    rows, cols = inputs.support(g, n, n, nnz)
+    plan, alone = (ff.plan_create(f, f, rows, cols, max_tokens=T, max_batch=3) for _ in range(2))
+    other = ff.plan_create(f, f, *inputs.support(g, n, n, nnz), max_tokens=T)
+    c = torch.from_numpy(alone.to_plan(inputs.gaussian(g, (nnz,), std=0.02))).to(dev)
+    c2 = torch.from_numpy(other.to_plan(inputs.gaussian(g, (nnz,), std=0.02))).to(dev)
+    X = torch_act(inputs.gaussian(g, (T, n), dtype="bf16"), "bf16", dev)
+    whole = ff.adapter_fwd(alone, X, c, s)
+    group = ff.plan_group([plan, other])
+    for t in (1, 8, 17, 64, 130):
+        assert torch.equal(ff.adapter_fwd(alone, X[:t], c, s), whole[:t]), f"{t} tokens"
+        assert torch.equal(ff.adapter_fwd(alone, X[:t], c, s, save=alone.new_saved()), whole[:t]), f"{t} tokens, saved"
+        Y = [torch.zeros((2 * t, n), dtype=torch.bfloat16, device=dev) for _ in range(2)]
+        Xs = [X[:2 * t], X[:2 * t]]
+        tokens = torch.tensor([t, 2 * t], dtype=torch.int32, device=dev)
+        ff.adapter_fwd_group(group, Xs, [c, c2], s, Y, tokens=tokens)
+        assert torch.equal(Y[0][:t], whole[:t]) and not Y[0][t:].any(), f"group, {t} tokens"
+        Yb = [torch.empty((t, n), dtype=torch.bfloat16, device=dev) for _ in range(3)]
+        ff.adapter_fwd_batched(alone, [X[:t]] * 3, [c] * 3, s, Yb)
+        assert all(torch.equal(y, whole[:t]) for y in Yb), f"batched, {t} tokens"
+        same = X[:t].clone()
+        assert torch.equal(ff.adapter_fwd(alone, same, c, s, Y=same), whole[:t]), f"in place, {t} tokens"
+        side = torch.zeros((t, 2 * n), dtype=torch.bfloat16, device=dev)   # both halves of one matrix
+        side[:, :n] = X[:t]
+        assert torch.equal(ff.adapter_fwd(alone, side[:, :n], c, s, Y=side[:, n:]), whole[:t]), f"side by side, {t}"
+
+
 def test_group_rejects_mismatched_plans(dev):
     f16, f32_ = ff.framegen(256, 16, 16), ff.framegen(512, 16, 32)
     r, c = inputs.support(inputs.rng(1), 256, 256, 300)
