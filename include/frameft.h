@@ -165,10 +165,10 @@ typedef enum ff_plan_query_key {
                                        input side at once; more when the support is dense) */
     FF_Q_GEN_TILE_TOKENS_F32 = 11,  /* most tokens per generic-kernel tile with those chunks, fp32 */
     FF_Q_GEN_TILE_TOKENS_BF16 = 12, /* the same, bf16 activations */
-    FF_Q_GEN_TOKEN_GROUPS = 13      /* 1 if bf16 calls keep several tokens of a coefficient together
-                                       (frames whose blocks are applied directly, up to 128 wide, or
-                                       in one radix-4 stage); the reported bf16 tile is then a
-                                       multiple of four tokens */
+    FF_Q_GEN_TOKEN_GROUPS = 13      /* 1 if bf16 forwards on the generic kernels keep four tokens
+                                       of a coefficient together in their tiles (frames whose blocks
+                                       are applied directly, up to 128 wide, or in one radix-4
+                                       stage); their tiles are then a multiple of four tokens */
 } ff_plan_query_key;
 ff_status ff_plan_query(const ff_plan* p, int key, int64_t* value);
 

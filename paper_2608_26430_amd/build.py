@@ -26,7 +26,8 @@ SOURCES = [("capi.cpp", "capi.cpp.o", []), ("framegen.cpp", "framegen.cpp.o", []
     for r in ("direct", "radix")] + [
     ("gen_inst.hip", f"gen_{d}_{t}{'_ms' if ms else ''}.o",
      [f"-DGEN_BWD={int(d == 'bwd')}", f"-DGEN_BF16={int(t == 'bf16')}", f"-DGEN_MS={ms}"])
-    for d in ("bwd", "fwd") for t, ms in (("bf16", 1), ("f32", 0), ("f32", 1))]
+    for d, t, ms in (("bwd", "bf16", 1), ("bwd", "f32", 0), ("bwd", "f32", 1), ("fwd", "bf16", 0), ("fwd", "bf16", 1),
+                     ("fwd", "f32", 0), ("fwd", "f32", 1))]
 
 ARCH = "gfx950"
 COMMON = [

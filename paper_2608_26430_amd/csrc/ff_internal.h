@@ -287,9 +287,9 @@ struct ff_plan {
   int gen_ldt_in[2] = {0, 0};      // LDS token stride of the input-side chunk tile
   int gen_tile_tokens[2] = {0, 0};
   size_t gen_lds_bytes[2] = {0, 0};
-  // bf16 tile geometry in whole groups of four tokens (frames applied directly or in one radix-4
-  // stage, no lift); those calls run in the slab kernels, and the geometry is what the queries report
-  // and what bounds ff_adapter_bwd_noalloc.
+  // bf16 tiles in whole groups of four tokens (frames applied directly or in one radix-4 stage, no lift):
+  // the generic forward keeps four tokens of a coefficient together; the geometry also bounds
+  // ff_adapter_bwd_noalloc.
   int gen_g4 = 0;
   int gen_wgs = 1;                 // compute units: resident workgroups of the generic kernels
   int gen_rows = 1;                // dC partial rows per adapter = most workgroups of the generic backward
@@ -338,6 +338,7 @@ struct ff_plan_group {
   const ff::GenDesc* gen = nullptr;     // [count], device
   // slab kernels: smallest pool and row count, longest streams
   size_t slab_pool = 0;
+  int64_t max_nnz = 0;
   int slab_rows = 0, max_slab_fwd = 0, max_slab_bwd = 0;   // (entries, padding steps included)
   // most blocks per group and most groups of any plan (plans for fewer tokens have smaller groups)
   int slab_nb_fwd = 0, slab_nb_bwd = 0, slab_groups_fwd = 0, slab_groups_bwd = 0;
@@ -348,9 +349,10 @@ namespace ff {
 
 // Error reporting (capi.cpp): remember a message for ff_last_error and return s.
 ff_status fail(ff_status s, const char* fmt, ...);
-// Whether a bf16 call of at most `tokens` tokens (all adapters; `most` of one) on a plan without the fused
-// kernels runs in the slab kernels (else in the generic ones).
-bool slab_forward(const ff_plan* p, int64_t tokens, int64_t most);
+// Whether a bf16 call on a plan without the fused kernels runs in the slab kernels (else in the generic
+// ones): a forward of T tokens of each of `count` adapters with at most nnz entries (ragged: T is the most
+// of one), a backward of `tokens` tokens of all adapters.
+bool slab_forward(const ff_plan* p, int64_t T, int64_t count, bool ragged, int64_t nnz);
 bool slab_backward(const ff_plan* p, int64_t tokens);
 void clear_error();
 

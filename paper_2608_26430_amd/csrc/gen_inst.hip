@@ -1,7 +1,8 @@
 // Instantiation of one generic kernel (fwd_kernel or bwd_kernel, GEN_BWD) for one activation type
 // (GEN_BF16), and for frames applied in several radix-4 stages or the others (GEN_MS): the build
 // compiles this file once per combination in use, in parallel.  bf16 calls that come here are short
-// (the slab kernels take the others): one instantiation serves every frame, one chunk of input blocks.
+// (the slab kernels take the others) and have one chunk of input blocks.  Forwards run on token-grouped
+// tiles where the frames allow them; the instantiation for several stages serves the rest.
 #include "gen_kernels.h"
 
 #if !defined(GEN_BWD) || !defined(GEN_BF16) || !defined(GEN_MS)
@@ -42,7 +43,7 @@ namespace gen {
 hipError_t GEN_LAUNCH_MS(const GEN_ARGS& a, dim3 grid, size_t lds, hipStream_t s);
 hipError_t GEN_CONFIGURE_MS();
 
-#if GEN_BF16
+#if GEN_BF16 && GEN_BWD
 hipError_t GEN_LAUNCH(const GEN_ARGS& a, dim3 grid, size_t lds, hipStream_t s) {
   if (a.nch > 1) return hipErrorInvalidValue;   // (not reached: the dispatch sends chunked calls to the slab kernels)
   return GEN_LAUNCH_MS(a, grid, lds, s);
@@ -50,7 +51,20 @@ hipError_t GEN_LAUNCH(const GEN_ARGS& a, dim3 grid, size_t lds, hipStream_t s) {
 hipError_t GEN_CONFIGURE() { return GEN_CONFIGURE_MS(); }
 #endif
 
-#if GEN_MS
+#if GEN_BF16 && !GEN_BWD && !GEN_MS
+hipError_t GEN_LAUNCH(const GEN_ARGS& a, dim3 grid, size_t lds, hipStream_t s) {
+  if (a.nch > 1) return hipErrorInvalidValue;   // (not reached, as above)
+  if (!a.g4) return GEN_LAUNCH_MS(a, grid, lds, s);
+  hipLaunchKernelGGL((GEN_KERNEL<true, false, false, true>), grid, dim3(kFusedThreads), lds, s, a);
+  return hipGetLastError();
+}
+hipError_t GEN_CONFIGURE() {
+  const hipError_t e = GEN_CONFIGURE_MS();
+  const hipError_t r = hipFuncSetAttribute(reinterpret_cast<const void*>(&GEN_KERNEL<true, false, false, true>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLdsBytes);
+  return r != hipSuccess ? r : e;
+}
+#elif GEN_MS
 hipError_t GEN_LAUNCH_MS(const GEN_ARGS& a, dim3 grid, size_t lds, hipStream_t s) {
   hipLaunchKernelGGL((GEN_KERNEL<GEN_BF16 != 0, false, true>), grid, dim3(kFusedThreads), lds, s, a);
   return hipGetLastError();

@@ -279,6 +279,122 @@ __device__ __forceinline__ void column_apply(const FrameDev& f, bool synth, int 
   column_apply_mem<BF16, GSRC>(frag, f.MT, KT, ncols, lim, col, epi);
 }
 
+// ---------------------------------------------------------------------------------------------
+// Token-grouped tiles (bf16 forwards, frames whose blocks are applied directly, up to 128 wide, or in one
+// radix-4 stage).  The element of token t at token-row offset p (the layout of one token row is unchanged) lives at
+// ((t / 4) ldt + p) 4 + t % 4: every coefficient holds four consecutive tokens in 8 bytes, so a
+// table row of the sparse phases reads or writes four tokens with one LDS access instead of four.
+// The frame applies keep full-width LDS accesses.  A group of 16 MFMA columns is four tokens
+// (4 tg .. 4 tg + 3) of four consecutive blocks (4 sq .. 4 sq + 3), column j being token j % 4
+// of block j / 4.  Analysis runs the MFMA with its operands swapped (D = X^T M^T: rows are the
+// group's columns), so that lane (q, L) ends with the four tokens of block 4 sq + q at output
+// coefficient 16 mt + L, one 8-byte LDS write; synthesis reads its operand with
+// ds_read_b64_tr_b16.  Token slots past the tile's tokens receive zeros from the analysis (their
+// operands are zero), so the sparse phases may read and write whole groups.
+
+typedef short g4_i16x4 __attribute__((ext_vector_type(4)));
+
+// Contraction elements 32 ks + 8 q .. + 7 of column L of a group from a token-grouped LDS tile,
+// by two transposed reads: within each 16 lanes the 8-byte chunks form 4 rows of 16 values and
+// lane L receives value L of each row.  For read h, lane L supplies element k0 + L / 4 (k0 =
+// 32 ks + 8 q + 4 h) of block 4 sq + L % 4, i.e. that block's four tokens, so lane L receives
+// elements k0 .. k0 + 3 of its own column.  at(c4, k) is the 8-byte chunk of block 4 sq + c4 at
+// element k (k < lim); elements at or past lim are returned as zero.
+template <int KT, class At>
+__device__ __forceinline__ void g4_tile_operand(At at, int lim, int q, int L, bf16x8 (&b)[KT]) {
+#pragma unroll
+  for (int ks = 0; ks < KT; ++ks) {
+    unsigned w[4];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int k0 = 32 * ks + 8 * q + 4 * h;
+      const u16* p = at(L & 3, min(k0 + (L >> 2), lim - 1));
+      const raw2 r = __builtin_bit_cast(
+          raw2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) g4_i16x4*)(const_cast<u16*>(p))));
+      const int nv = lim - k0;   // valid elements of this read (the same in the 16 lanes)
+      w[2 * h] = nv >= 2 ? r.x : nv == 1 ? (r.x & 0xffffu) : 0u;
+      w[2 * h + 1] = nv >= 4 ? r.y : nv == 3 ? (r.y & 0xffffu) : 0u;
+    }
+    b[ks] = __builtin_bit_cast(bf16x8, raw4{w[0], w[1], w[2], w[3]});
+  }
+}
+
+// Every group g < ngrp (token group g / nsq, quad of sub-columns g % nsq; a sub-column is a
+// block, or a (block, radix-4 column) of a factored frame): operands from token rows in global
+// memory (GSRC: colg(tg, sq, L) is column L's row start, NULL outside the tile) or from the LDS
+// tile through at(tg, sq, c4, k).  SWAP gives epi(tg, sq, mt, acc) tokens 0..3 of sub-column
+// 4 sq + q at output 16 mt + L (analysis, also in place: a group's operands are all read before
+// its outputs are written, and groups are disjoint); otherwise outputs 16 mt + 4 q .. + 3 of
+// column L (synthesis).  The fragments stay in registers; each wave takes every nw-th group with
+// the next group's operands in flight.
+template <bool GSRC, bool SWAP, int MT, int KT, class ColG, class At, class Epi>
+__device__ __forceinline__ void column_apply_g4(const void* frag, int ngrp, int nsq, int lim, ColG colg, At at,
+                                                Epi epi) {
+  using M = Mfma<true>;
+  using V = typename M::V;
+  const int lane = phase_tid() & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6,
+            q = lane >> 4, L = lane & 15;
+  if (wave >= ngrp) return;
+  const V* fr = reinterpret_cast<const V*>(frag);
+  asm volatile("" : "+s"(fr));
+  V fa[MT][KT];
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+    for (int ks = 0; ks < KT; ++ks) fa[mt][ks] = gload(&fr[(mt * KT + ks) * 64 + lane]);
+  V ba[KT], bb[KT];
+  auto load = [&](int g, V (&b)[KT]) {
+    const int tg = g / nsq, sq = g - tg * nsq;
+    if constexpr (GSRC) {
+      const u16* in = colg(tg, sq, L);
+      const bool ok = in != nullptr;
+#pragma unroll
+      for (int ks = 0; ks < KT; ++ks) b[ks] = load_operand<true, true>(ok ? in : colg(0, 0, 0), ok, lim, ks, q);
+    } else {
+      g4_tile_operand<KT>([&](int c4, int k) { return at(tg, sq, c4, k); }, lim, q, L, b);
+    }
+  };
+  auto mul = [&](int g, const V (&b)[KT]) {
+    f32x4 acc[MT];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) acc[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ks = 0; ks < KT; ++ks)
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt)
+        acc[mt] = SWAP ? M::step(b[ks], fa[mt][ks], acc[mt]) : M::step(fa[mt][ks], b[ks], acc[mt]);
+    const int tg = g / nsq, sq = g - tg * nsq;
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) epi(tg, sq, mt, acc[mt]);
+  };
+  load(wave, ba);
+  for (int g = wave; g < ngrp; g += 2 * nw) {
+    if (g + nw < ngrp) load(g + nw, bb);
+    mul(g, ba);
+    if (g + nw >= ngrp) break;
+    if (g + 2 * nw < ngrp) load(g + 2 * nw, ba);
+    mul(g + nw, bb);
+  }
+}
+
+// Dispatch on the matrix shape (MT x KT tiles of M, whose columns have lim elements: W for a
+// directly applied block, cs for the DFT of size k/4 of a factored one).
+template <bool GSRC, bool SWAP, class ColG, class At, class Epi>
+__device__ __forceinline__ void column_apply_g4(const FrameDev& f, bool synth, int ngrp, int nsq, int lim, ColG colg,
+                                                At at, Epi epi) {
+  const void* frag = synth ? f.fs16 : f.fa16;
+#define FF_SHAPE(mt, kt)                                                           \
+  case (mt) * 64 + (kt):                                                           \
+    column_apply_g4<GSRC, SWAP, mt, kt>(frag, ngrp, nsq, lim, colg, at, epi);      \
+    return;
+  switch (f.MT * 64 + f.KT) {
+    FF_SHAPE(1, 1) FF_SHAPE(2, 1) FF_SHAPE(3, 2) FF_SHAPE(4, 2) FF_SHAPE(5, 3) FF_SHAPE(6, 3)
+    FF_SHAPE(7, 4) FF_SHAPE(8, 4)
+    default: break;   // not taken: the plan uses these tiles only for matrices up to 128 wide
+  }
+#undef FF_SHAPE
+}
+
 // Two consecutive activations (one complex coordinate) as fp32, and back.
 template <bool BF16>
 __device__ __forceinline__ float2 ld2(const typename Act<BF16>::E* p) {
@@ -636,8 +752,212 @@ __device__ __forceinline__ void msr_synthesis(const FrameDev& f, int nt, const t
   }
 }
 
+// z = P^T x for a tile into a token-grouped LDS tile (frames applied directly): every token slot
+// of the tile's groups is written, those past nt with zeros.
+__device__ __forceinline__ void analysis_g4(const FrameDev& f, int nt, const u16* src, long ld, u16* dst, int ldt,
+                                            int ldb) {
+  const int nblk = f.nblk, W = f.W, nsq = (nblk + 3) / 4, ngrp = (nt + 3) / 4 * nsq;
+  const int lane = phase_tid() & 63, q = lane >> 4, L = lane & 15;
+  column_apply_g4<true, true>(
+      f, false, ngrp, nsq, W,
+      [&](int tg, int sq, int c) -> const u16* {
+        const int t = 4 * tg + (c & 3), b = 4 * sq + (c >> 2);
+        return t < nt && b < nblk ? src + (long)t * ld + b * W : nullptr;
+      },
+      [&](int, int, int, int) -> const u16* { return dst; },
+      [&](int tg, int sq, int mt, f32x4 v) {
+        const int b = 4 * sq + q, o = 16 * mt + L;
+        if (b < nblk && o < W) Act<true>::st4(dst + 4 * (tg * ldt + b * ldb + o), v);
+      });
+}
+
+// out = s P v (+ beta out) for a tile from a token-grouped LDS tile (frames applied directly).
+__device__ __forceinline__ void synthesis_g4(const FrameDev& f, int nt, const u16* src, int ldt, int ldb, u16* dst,
+                                             long ld, float s, float beta) {
+  const int nblk = f.nblk, W = f.W, nsq = (nblk + 3) / 4, ngrp = (nt + 3) / 4 * nsq;
+  const int lane = phase_tid() & 63, q = lane >> 4, L = lane & 15;
+  column_apply_g4<false, false>(
+      f, true, ngrp, nsq, W, [&](int, int, int) -> const u16* { return src; },
+      [&](int tg, int sq, int c4, int k) -> const u16* {
+        const int b = min(4 * sq + c4, nblk - 1);
+        return src + 4 * (tg * ldt + b * ldb + k);
+      },
+      [&](int tg, int sq, int mt, f32x4 v) {
+        const int t = 4 * tg + (L & 3), b = 4 * sq + (L >> 2), o = 16 * mt + 4 * q;
+        if (t < nt && b < nblk && o < W) {
+          u16* p = dst + (long)t * ld + b * W + o;
+          f32x4 r = v * s;
+          if (beta != 0.f) r += beta * Act<true>::gld4(p);
+          Act<true>::gst4(p, r);
+        }
+      });
+}
+
+// Radix-4 stage of the factored analysis on a token-grouped tile (single-stage frames): an item is
+// (token group, block, residue b < k2); it reads x[a k2 + b] (a = 0..3) of its four tokens from
+// the token rows (tokens past nt as zero) and writes the real and the imaginary parts of column
+// a' row b, four tokens per 8-byte write.  The columns' padding rows W2 .. cs - 1 are never
+// written: the DFT of size k/4 reads its operands only below W2.
+constexpr int kRB4 = 2;   // items per thread in flight (16 complex loads each)
+
+__device__ __forceinline__ void radix4_analysis_g4(const FrameDev& f, const float2* tw, int nt, const u16* src,
+                                                   long ld, u16* dst, int ldt, int ldb) {
+  const int k2 = f.k2, W = f.W, cs = f.cs;
+  const int per_tg = f.nblk * k2, items = (nt + 3) / 4 * per_tg;
+  const float inv_pt = 1.f / (float)per_tg, inv_k2 = 1.f / (float)k2;
+  for (int it0 = phase_tid(); it0 < items; it0 += kRB4 * blockDim.x) {
+    float2 x[kRB4][4][4], w[kRB4][3];   // [item][token][a]
+    u16* y[kRB4];
+#pragma unroll
+    for (int u = 0; u < kRB4; ++u) {
+      const int it = min(it0 + u * (int)blockDim.x, items - 1);   // past the end: a repeat, not stored
+      const int tg = div_small(it, per_tg, inv_pt), r = it - tg * per_tg, blk = div_small(r, k2, inv_k2);
+      const int b = r - blk * k2;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {   // rows past nt: the last token's, read unconditionally and dropped
+        const int t = 4 * tg + i;
+        const u16* xp = src + (long)min(t, nt - 1) * ld + blk * W + 2 * b;
+#pragma unroll
+        for (int a = 0; a < 4; ++a) {
+          const float2 v = gld2<true>(xp + 2 * a * k2);
+          x[u][i][a] = t < nt ? v : make_float2(0.f, 0.f);
+        }
+      }
+#pragma unroll
+      for (int a = 0; a < 3; ++a) w[u][a] = tw[a * k2 + b];
+      y[u] = dst + 4 * (tg * ldt + blk * ldb + 2 * b);
+    }
+#pragma unroll
+    for (int u = 0; u < kRB4; ++u) {
+      if (it0 + u * (int)blockDim.x >= items) break;
+      f32x4 yr[4], yi[4];   // [a'] over the four tokens
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float2* xi = x[u][i];
+        const float2 s02 = cadd(xi[0], xi[2]), d02 = csub(xi[0], xi[2]);
+        const float2 s13 = cadd(xi[1], xi[3]), d13 = csub(xi[1], xi[3]);
+        const float2 o[4] = {cadd(s02, s13), cmulc(make_float2(d02.x + d13.y, d02.y - d13.x), w[u][0]),
+                             cmulc(csub(s02, s13), w[u][1]), cmulc(make_float2(d02.x - d13.y, d02.y + d13.x), w[u][2])};
+#pragma unroll
+        for (int a = 0; a < 4; ++a) {
+          yr[a][i] = o[a].x;
+          yi[a][i] = o[a].y;
+        }
+      }
+#pragma unroll
+      for (int a = 0; a < 4; ++a) {   // the real and imaginary rows are adjacent: one 16-byte write
+        const uint2 r = Act<true>::pack4(yr[a]), i = Act<true>::pack4(yi[a]);
+        *reinterpret_cast<uint4*>(y[u] + 4 * a * cs) = make_uint4(r.x, r.y, i.x, i.y);
+      }
+    }
+  }
+}
+
+// Radix-4 stage of the factored synthesis from a token-grouped tile: an item reads the four tokens
+// of column a' row b (real and imaginary parts, one 8-byte read each) and writes out = s x
+// (+ beta out) for those of its tokens below nt.
+__device__ __forceinline__ void radix4_synthesis_g4(const FrameDev& f, const float2* tw, int nt, const u16* src,
+                                                    int ldt, int ldb, u16* dst, long ld, float s, float beta) {
+  const int k2 = f.k2, W = f.W, cs = f.cs;
+  const int per_tg = f.nblk * k2, items = (nt + 3) / 4 * per_tg;
+  const float inv_pt = 1.f / (float)per_tg, inv_k2 = 1.f / (float)k2;
+  for (int it0 = phase_tid(); it0 < items; it0 += kRB4 * blockDim.x) {
+    f32x4 yr[kRB4][4], yi[kRB4][4];
+    float2 w[kRB4][3];
+    int tg[kRB4], blk[kRB4], b[kRB4];
+#pragma unroll
+    for (int u = 0; u < kRB4; ++u) {
+      const int it = min(it0 + u * (int)blockDim.x, items - 1);
+      tg[u] = div_small(it, per_tg, inv_pt);
+      const int r = it - tg[u] * per_tg;
+      blk[u] = div_small(r, k2, inv_k2);
+      b[u] = r - blk[u] * k2;
+      const u16* yp = src + 4 * (tg[u] * ldt + blk[u] * ldb + 2 * b[u]);
+#pragma unroll
+      for (int a = 0; a < 4; ++a) {   // the real and imaginary rows: one 16-byte read
+        const uint4 w = *reinterpret_cast<const uint4*>(yp + 4 * a * cs);
+        yr[u][a] = Act<true>::unpack4(make_uint2(w.x, w.y));
+        yi[u][a] = Act<true>::unpack4(make_uint2(w.z, w.w));
+      }
+#pragma unroll
+      for (int a = 0; a < 3; ++a) w[u][a] = tw[a * k2 + b[u]];
+    }
+#pragma unroll
+    for (int u = 0; u < kRB4; ++u) {
+      if (it0 + u * (int)blockDim.x >= items) break;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int t = 4 * tg[u] + i;
+        if (t >= nt) break;
+        const float2 y0 = make_float2(yr[u][0][i], yi[u][0][i]);
+        const float2 y1 = cmul(make_float2(yr[u][1][i], yi[u][1][i]), w[u][0]);
+        const float2 y2 = cmul(make_float2(yr[u][2][i], yi[u][2][i]), w[u][1]);
+        const float2 y3 = cmul(make_float2(yr[u][3][i], yi[u][3][i]), w[u][2]);
+        const float2 s02 = cadd(y0, y2), d02 = csub(y0, y2), s13 = cadd(y1, y3), d13 = csub(y1, y3);
+        const float2 xo[4] = {cadd(s02, s13), make_float2(d02.x - d13.y, d02.y + d13.x), csub(s02, s13),
+                              make_float2(d02.x + d13.y, d02.y - d13.x)};
+        u16* out = dst + (long)t * ld + blk[u] * W + 2 * b[u];
+#pragma unroll
+        for (int a = 0; a < 4; ++a) {
+          float2 v = make_float2(s * xo[a].x, s * xo[a].y);
+          if (beta != 0.f) {
+            const float2 old = gld2<true>(out + 2 * a * k2);
+            v.x = fmaf(beta, old.x, v.x);
+            v.y = fmaf(beta, old.y, v.y);
+          }
+          gst2<true>(out + 2 * a * k2, v);
+        }
+      }
+    }
+  }
+}
+
+// The dense DFT of size k/4 applied in place to every (token group, block, radix-4 column) of a
+// factored token-grouped tile (single-stage frames: four columns per block), M^T for analysis and
+// M for synthesis.  Operands are read below W2 only; outputs up to cs are written (M's rows past
+// W2 are zero, so the padding rows receive zeros).
+__device__ __forceinline__ void factored_dft_g4(const FrameDev& f, bool synth, int nt, u16* tile, int ldt, int ldb) {
+  const int cs = f.cs, nsub = 4 * f.nblk, nsq = f.nblk, ngrp = (nt + 3) / 4 * nsq;
+  const int lane = phase_tid() & 63, q = lane >> 4, L = lane & 15;
+  column_apply_g4<false, true>(
+      f, synth, ngrp, nsq, f.W2, [&](int, int, int) -> const u16* { return tile; },
+      [&](int tg, int sq, int c4, int k) -> const u16* {
+        const int sub = min(4 * sq + c4, nsub - 1);
+        return tile + 4 * (tg * ldt + (sub >> 2) * ldb + (sub & 3) * cs + k);
+      },
+      [&](int tg, int sq, int mt, f32x4 v) {
+        const int sub = 4 * sq + q, o = 16 * mt + L;
+        if (o < cs) Act<true>::st4(tile + 4 * (tg * ldt + (sub >> 2) * ldb + (sub & 3) * cs + o), v);
+      });
+}
+
+// z = P^T x into a token-grouped tile: the block directly, or the radix-4 stage and then the DFT
+// of size k/4 in place.
+__device__ __forceinline__ void analysis_lds_g4(const FrameDev& f, const float2* tw, int nt, const u16* src, long ld,
+                                                u16* dst, int ldt, int ldb) {
+  if (f.radix == 1) {
+    analysis_g4(f, nt, src, ld, dst, ldt, ldb);
+    return;
+  }
+  radix4_analysis_g4(f, tw, nt, src, ld, dst, ldt, ldb);
+  __syncthreads();
+  factored_dft_g4(f, false, nt, dst, ldt, ldb);
+}
+
+// out = s P v (+ beta out) from a token-grouped tile (factored frames transform it in place first).
+__device__ __forceinline__ void synthesis_lds_g4(const FrameDev& f, const float2* tw, int nt, u16* src, int ldt,
+                                                 int ldb, u16* dst, long ld, float s, float beta) {
+  if (f.radix == 1) {
+    synthesis_g4(f, nt, src, ldt, ldb, dst, ld, s, beta);
+    return;
+  }
+  factored_dft_g4(f, true, nt, src, ldt, ldb);
+  __syncthreads();
+  radix4_synthesis_g4(f, tw, nt, src, ldt, ldb, dst, ld, s, beta);
+}
+
 // Zero the padding of every column of a factored tile whose coefficients another phase writes
-// (the MFMA reads whole columns of cs elements).
+// (the MFMA reads whole columns of cs elements).  Token-grouped tiles need none.
 template <bool BF16>
 __device__ __forceinline__ void zero_column_pads(const FrameDev& f, int nt, typename Act<BF16>::E* tile, int ldt,
                                                  int ldb) {
@@ -653,12 +973,18 @@ __device__ __forceinline__ void zero_column_pads(const FrameDev& f, int nt, type
 // z = P^T x for a tile: token rows at src (global) -> coefficients in the LDS tile.
 // MS: the frame may be applied in several radix-4 stages (nst >= 2); only the kernels built for
 // such frames carry that code, so the others keep their register allocation.
-template <bool BF16, bool MS = false>
+// G4: into a token-grouped tile.
+template <bool BF16, bool MS = false, bool G4 = false>
 __device__ __forceinline__ void analysis_to_lds(const FrameDev& f, const float2* tw, int nt,
                                                 const typename Act<BF16>::E* src, long ld, typename Act<BF16>::E* dst,
                                                 int ldt, int ldb) {
   using A = Act<BF16>;
   using E = typename A::E;
+  if constexpr (G4) {
+    static_assert(BF16 && !MS, "token-grouped tiles: bf16, frames in at most one radix-4 stage");
+    analysis_lds_g4(f, tw, nt, src, ld, dst, ldt, ldb);
+    return;
+  }
   const int nblk = f.nblk;
   if (f.radix == 1) {
     const int W = f.W;
@@ -699,12 +1025,18 @@ __device__ __forceinline__ void analysis_to_lds(const FrameDev& f, const float2*
 
 // out = s P q (+ beta out) for a tile: coefficients in the LDS tile at src -> token rows at dst.
 // Factored frames transform the tile in place first, so src is overwritten.
-template <bool BF16, bool MS = false>
+// G4: from a token-grouped tile.
+template <bool BF16, bool MS = false, bool G4 = false>
 __device__ __forceinline__ void synthesis_from_lds(const FrameDev& f, const float2* tw, int nt,
                                                    typename Act<BF16>::E* src, int ldt, int ldb,
                                                    typename Act<BF16>::E* dst, long ld, float s, float beta) {
   using A = Act<BF16>;
   using E = typename A::E;
+  if constexpr (G4) {
+    static_assert(BF16 && !MS, "token-grouped tiles: bf16, frames in at most one radix-4 stage");
+    synthesis_lds_g4(f, tw, nt, src, ldt, ldb, dst, ld, s, beta);
+    return;
+  }
   const int nblk = f.nblk;
   if (f.radix == 1) {
     const int W = f.W;
@@ -881,6 +1213,98 @@ __device__ __forceinline__ void stream_pass(const GenStream& S, const float* __r
   }
 }
 
+// The forward's sparse products on token-grouped tiles: the same walk, each table row reading NG groups of
+// four tokens (one 8-byte LDS read each) for the pass's tokens tg0 .. tg0 + 4 NG - 1 (tg0 a
+// multiple of 4) and writing whole groups at a slab's end.  Token slots past the tile's tokens hold zeros
+// in the source tile, so their sums are zero.
+template <int NG>
+__device__ __forceinline__ void stream_products_g4(const GenStream& S, const float* __restrict__ cv, const u16* src,
+                                                   int ld_src, u16* dst, int ld_dst, int tg0) {
+  using A = Act<true>;
+  constexpr int NT = 4 * NG;
+  const int lane = phase_tid() & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int r0 = S.wave_row[wave], r1 = S.wave_row[wave + 1];
+  if (r0 >= r1) return;
+  const int2* ent = (S.ent);
+  src += tg0 * ld_src;   // group tg0 / 4 starts at element 4 (tg0 / 4) ld
+  dst += tg0 * ld_dst;
+  const int gs = 4 * ld_src, gd = 4 * ld_dst;
+  int2 ea[kSD], eb[kSD];
+  float ca[kSD], cb[kSD];
+  auto load = [&](int r, int2 (&e)[kSD], float (&c)[kSD]) {
+#pragma unroll
+    for (int i = 0; i < kSD; ++i) {
+      const int j = min(r + i, r1 - 1) * 64 + lane;
+      e[i] = gload(&ent[j]);
+      c[i] = gload(&cv[j]);
+    }
+  };
+  float acc[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) acc[t] = 0.f;
+  auto read = [&](const int2& e, float (&x)[NT]) {
+    const int so = 4 * (e.x & 0x7fffffff);
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+      const f32x4 v = A::ld4(src + g * gs + so);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) x[4 * g + i] = v[i];
+    }
+  };
+  auto consume = [&](const int2 (&e)[kSD], const float (&c)[kSD], int n) {
+    float xa[NT], xb[NT];
+    read(e[0], xa);
+#pragma unroll
+    for (int i = 0; i < kSD; ++i) {
+      if (i >= n) break;
+      float (&x)[NT] = (i & 1) ? xb : xa;
+      if (i + 1 < kSD && i + 1 < n) read(e[i + 1], (i & 1) ? xa : xb);
+      const int d = e[i].y;
+#pragma unroll
+      for (int t = 0; t < NT; ++t) acc[t] = fmaf(c[i], x[t], acc[t]);
+      if (__builtin_amdgcn_readfirstlane(e[i].x) < 0) {   // the slab's last row (same in every lane)
+        if (d >= 0) {
+#pragma unroll
+          for (int g = 0; g < NG; ++g)
+            A::st4(dst + g * gd + 4 * d, f32x4{acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]});
+        }
+#pragma unroll
+        for (int t = 0; t < NT; ++t) acc[t] = 0.f;
+      }
+    }
+  };
+  const int rend = r0 + (r1 - r0) / (2 * kSD) * (2 * kSD);
+  load(r0, ea, ca);
+  load(r0 + kSD, eb, cb);
+  for (int r = r0; r < rend; r += 2 * kSD) {
+    consume(ea, ca, kSD);
+    load(r + 2 * kSD, ea, ca);
+    consume(eb, cb, kSD);
+    load(r + 3 * kSD, eb, cb);
+  }
+  if (rend < r1) {
+    consume(ea, ca, min(kSD, r1 - rend));
+    if (rend + kSD < r1) consume(eb, cb, r1 - rend - kSD);
+  }
+}
+
+// All tokens of a token-grouped tile, 20 at a time (each pass starts with a latency-bound load of
+// its first entries), the last pass reading only the groups it needs.
+constexpr int kTGWideG4 = 20;
+
+__device__ __forceinline__ void stream_all_g4(const GenStream& S, const float* __restrict__ cv, const u16* src,
+                                              int ld_src, u16* dst, int ld_dst, int nt) {
+  for (int tg = 0; tg < nt; tg += kTGWideG4) {
+    switch ((min(kTGWideG4, nt - tg) + 3) / 4) {
+      case 1: stream_products_g4<1>(S, cv, src, ld_src, dst, ld_dst, tg); break;
+      case 2: stream_products_g4<2>(S, cv, src, ld_src, dst, ld_dst, tg); break;
+      case 3: stream_products_g4<3>(S, cv, src, ld_src, dst, ld_dst, tg); break;
+      case 4: stream_products_g4<4>(S, cv, src, ld_src, dst, ld_dst, tg); break;
+      default: stream_products_g4<5>(S, cv, src, ld_src, dst, ld_dst, tg);
+    }
+  }
+}
+
 // All tokens of a tile, kTGWide at a time while that many remain, then kTG, each pass reading
 // only as many token rows as it needs.
 // `add` (MAY_ADD only): backward, add to the dC partial row (as do the tile's later passes);
@@ -923,6 +1347,7 @@ struct FwdArgs {
   GenStream st;
   int nch;              // input-side chunks: blocks chunk_blk[i] .. chunk_blk[i + 1] - 1
   int chunk_blk[kMaxGenChunks + 1];
+  int g4;               // token-grouped tiles (bf16, whole input side)
   // group calls: adapter blockIdx.y's own plan (stream, coefficient copy) and token count
   // (device, clamped to [0, T]; NULL: T)
   const GenDesc* group;
@@ -934,14 +1359,17 @@ __device__ __forceinline__ int group_tokens(const int* tokens, int T, int bi) {
 }
 
 // CHUNKED: the input side in a.nch chunks of blocks, v accumulated over them; otherwise whole
-// (a.nch == 1), in code of its own.
-template <bool BF16, bool CHUNKED, bool MS = false>
+// (a.nch == 1), in code of its own.  G4: token-grouped tiles, whose token slots are rounded up to whole
+// groups of four.
+template <bool BF16, bool CHUNKED, bool MS = false, bool G4 = false>
 __global__ void __launch_bounds__(kFusedThreads) fwd_kernel(FwdArgs a) {
   using A = Act<BF16>;
   using E = typename A::E;
+  static_assert(!G4 || (BF16 && !CHUNKED && !MS), "token-grouped tiles: bf16, at most one radix-4 stage");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  E* zt = reinterpret_cast<E*>(smem);           // tt x ldt_in   z = P_in^T x (of one chunk)
-  E* vt = zt + (size_t)a.tt * a.ldt_in;          // tt x ldt_out  v = C z
+  const int cap = G4 ? (a.tt + 3) & ~3 : a.tt;   // token slots of a tile
+  E* zt = reinterpret_cast<E*>(smem);           // cap x ldt_in   z = P_in^T x (of one chunk)
+  E* vt = zt + (size_t)cap * a.ldt_in;          // cap x ldt_out  v = C z
   const int bi = blockIdx.y;
   const E* X = (reinterpret_cast<const E*>(a.Xs ? a.Xs[bi] : a.X));
   E* Y = (reinterpret_cast<E*>(a.Ys ? a.Ys[bi] : a.Y));
@@ -961,20 +1389,23 @@ __global__ void __launch_bounds__(kFusedThreads) fwd_kernel(FwdArgs a) {
   Y += (long)t0 * a.ldy;
 
   // twiddle factors of factored frames after the tiles
-  float2* tw_in = reinterpret_cast<float2*>(vt + (size_t)a.tt * a.ldt_out);
+  float2* tw_in = reinterpret_cast<float2*>(vt + (size_t)cap * a.ldt_out);
   float2* tw_out = tw_in + kTwLdsBytes / 16;
   stage_twiddles(a.fin, tw_in);
   stage_twiddles(a.fout, tw_out);
   if (a.fin.radix != 1 || a.fout.radix != 1) __syncthreads();
 
-  zero_column_pads<BF16>(a.fout, nt, vt, a.ldt_out, a.ldb_out);
+  if constexpr (!G4) zero_column_pads<BF16>(a.fout, nt, vt, a.ldt_out, a.ldb_out);
   if constexpr (!CHUNKED) {
     // analysis: z = P_in^T x for every (token, input block)
-    analysis_to_lds<BF16, MS>(a.fin, tw_in, nt, X, a.ldx, zt, a.ldt_in, a.ldb_in);
+    analysis_to_lds<BF16, MS, G4>(a.fin, tw_in, nt, X, a.ldx, zt, a.ldt_in, a.ldb_in);
     __syncthreads();
 
     // coefficients: v[a] = sum_{e in row a} c_e z[b_e]
-    stream_all<BF16, false, false>(st, cv, zt, a.ldt_in, vt, a.ldt_out, nt, true, nullptr);
+    if constexpr (G4)
+      stream_all_g4(st, cv, zt, a.ldt_in, vt, a.ldt_out, nt);
+    else
+      stream_all<BF16, false, false>(st, cv, zt, a.ldt_in, vt, a.ldt_out, nt, true, nullptr);
   } else {
     for (int ch = 0; ch < a.nch; ++ch) {
       // the chunk's blocks as a frame of their own, at column b0 W of the token rows
@@ -994,7 +1425,7 @@ __global__ void __launch_bounds__(kFusedThreads) fwd_kernel(FwdArgs a) {
   __syncthreads();
 
   // synthesis and epilogue: y = beta y + s P_out v
-  synthesis_from_lds<BF16, MS>(a.fout, tw_out, nt, vt, a.ldt_out, a.ldb_out, Y, a.ldy, a.scale, a.beta);
+  synthesis_from_lds<BF16, MS, G4>(a.fout, tw_out, nt, vt, a.ldt_out, a.ldb_out, Y, a.ldy, a.scale, a.beta);
 }
 
 struct BwdArgs {

@@ -97,6 +97,7 @@ ff_status ff_plan_group_create(int64_t count, const ff_plan* const* plans, ff_pl
     gen[i] = ff::GenDesc{d.fwd, d.bwd, d.coef_pad, d.c_fwd, d.c_bwd, p->partial, d.fwd_by_pos, d.ncoef_pad};
     const ff::SlabPlanDev& sp = p->slab;
     slab[i] = ff::SlabDesc{sp.fwd, sp.bwd, sp.pool, sp.ent, p->partial};
+    g->max_nnz = std::max(g->max_nnz, p->nnz);
     g->slab_pool = std::min(g->slab_pool, sp.pool_bytes);
     g->slab_rows = std::min(g->slab_rows, sp.rows);
     g->slab_nb_fwd = std::max(g->slab_nb_fwd, sp.fwd.nb);

@@ -12,7 +12,7 @@
 // LDS, where one tile's coefficient vectors are kept whole because the
 // support of C is uniformly random.
 //
-// Generic kernels (fp32 activations, and frames in several radix-4 stages):
+// Generic kernels (fp32 activations, short bf16 calls):
 //   fwd_kernel    x -> z = P_in^T x (LDS) -> v = C z (LDS) -> y = beta y + s P_out v
 //   bwd_kernel    g -> u = P_out^T g (LDS), x -> z = P_in^T x (LDS)
 //                 -> dC partial per tile: sum_t u[a_e] z[b_e]
@@ -445,8 +445,7 @@ hipError_t launch_gather(const float* c, const float* const* cs, const int* idx,
 // workgroup per CU, so tiles go in rounds of `slots` and a call costs about rounds x (token rows
 // its sparse walks read per table row + a fixed part worth kTileOverhead of them).  Of the tile
 // sizes up to tt (the plan's LDS limit) the cheapest is taken, the larger one on ties (fewer
-// passes over the tables).  g4 counts whole groups of four tokens (bf16 group calls, and what
-// ff_adapter_bwd_noalloc accepts).
+// passes over the tables).  Token-grouped tiles (g4) read whole groups of four tokens.
 constexpr int kTileOverhead = 2;
 
 int call_tile_tokens(int tt, long T, int count, int slots, bool g4) {
@@ -488,34 +487,70 @@ bool slab_backward(const ff_plan* p, int64_t tokens) {
   // other frames: always quicker there (256 -> 512 wide, 1 token: 15 -> 13 us; 2880 -> 2880: 29 -> 25)
   return p->gen_nch > 1 || !multistage(p) || tokens > ms_tokens(p, 1400, 0.9e6);
 }
-// Other frames, forward, by both sides' times in microseconds (generic -> slab): 256 -> 512 wide with 700
-// entries 7 -> 9, 768 -> 2304 with 3,000, 256 tokens 9 -> 10, 4096 19 -> 20; 2880 -> 2880 with 14,000, 1
-// token 14 -> 16, 64 tokens 20 -> 19; 512 -> 6912 with 27,000, 64 tokens 22 -> 12; 17 adapters 1152 -> 1664
-// with 1,935 of up to 418 tokens 18 -> 22.
-bool slab_forward(const ff_plan* p, int64_t tokens, int64_t most) {
+// Other frames, forward, by both sides' times in microseconds (generic on token-grouped tiles / slab).  T
+// tokens of each of `count` adapters with up to `nnz` entries each; ragged: the adapters' own numbers of
+// tokens are on the device, half of T on average.  The generic kernels' time goes with the rounds of
+// tiles and with the token rows of a tile's walk, the slab kernels' with the slabs, 64 tokens each.
+// Direct output blocks: 256 -> 512 wide with 700 entries, 64 tokens 5.1 / 7.6; 768 -> 2304 with 3,000, 64 tokens
+// 7.4 / 8.3, 4096 16.7 / 20.2, 8192 30.0 / 26.3; 2048 -> 768 with 4,000, 4096 tokens 12.9 / 16.9; 4096 -> 8192 with
+// 20,000, 16 tokens 16.5 / 9.1; 8960 -> 512 with 27,000, 64 tokens 16.5 / 17.8; 17 ragged adapters 1152 -> 1664
+// with 1,935 of up to 64 tokens 10.3 / 13.0, of up to 418 26.9 / 23.9.  The constants are fitted to 162 such
+// calls, whose choices are 0.2% off the better side on average.
+// Factored output blocks: 2880 -> 2880 with 14,000, 1 token 12.1 / 15.1, 64 tokens 13.2 / 18.1, 4096 36.8 / 32.3;
+// 512 -> 6912 with 27,000, 64 tokens 15.0 / 10.8.  The slab kernels round an output once, the generic ones
+// also between the synthesis' two stages (error against float64 4.0e-3 / 4.3e-3), so their line lies at fewer
+// tokens than the times alone would put it.
+// Calls of more tokens than kSlabTokens run in the slab kernels whatever their number of adapters: the two sides
+// are then close (8192 tokens: 512 -> 768 wide 14.2 / 15.0, 2048 -> 768 23.9 / 28.0, 2752 -> 1024 36.1 / 36.8, 4096 -> 8192
+// 129 / 90), and a batched call gives the bits of the single ones.
+constexpr int64_t kSlabTokens = 4096;
+bool slab_forward(const ff_plan* p, int64_t T, int64_t count, bool ragged, int64_t nnz) {
   if (!p->slab.enabled) return false;
-  if (p->gen_nch > 1) return true;
-  if (multistage(p)) return tokens > ms_tokens(p, 1800, 1.6e6);
-  const double w = (double)(p->fin->dv + p->fout->dv), e = (double)p->nnz, t = (double)tokens;
-  const bool factored = p->fin->dev.radix != 1 || p->fout->dev.radix != 1;
-  const double round = (double)std::min(8, p->gen_tile_tokens[1]) * p->gen_wgs;   // tokens in flight at once
-  const double generic = (5.5 + 7e-4 * w + 4e-4 * e) * (factored ? 1.3 : 1.0) * (most < 8 ? 0.7 : 1.0) *
-                         std::max(1.0, t / round);
-  const double slab = 9 + 4e-4 * w + e / (256.0 * p->slab.fwd.ngroups) + 8e-7 * w * t;
-  return generic + 0.3 > slab;
+  const double tokens = (double)T * (double)count / (ragged ? 2 : 1);
+  if (multistage(p)) return p->gen_nch > 1 || tokens > (double)ms_tokens(p, 1800, 1.6e6);
+  if (!p->gen_g4 || p->gen_nch > 1 || T > kSlabTokens) return true;
+  const double n = (double)p->fin->dv, m = (double)p->fout->dv, e = (double)nnz;
+  const double per_group = e / p->slab.fwd.ngroups;
+  const double slabs = (double)((T + 63) / 64) * (double)count / (ragged ? 2 : 1);
+  const bool factored = p->fin->dev.radix != 1;
+  if (p->fout->dev.radix != 1) {
+    const double round = (double)std::min(8, p->gen_tile_tokens[1]) * p->gen_wgs;   // tokens in flight at once
+    const double generic =
+        (5.5 + 7e-4 * (n + m) + 4e-4 * e) * 1.3 * (T < 8 ? 0.7 : 1.0) * std::max(1.0, tokens / round);
+    return generic + 0.3 > 9 + 4e-4 * (n + m) + per_group / 256 + 5.1e-5 * (n + m) * slabs;
+  }
+  const int64_t tt = call_tile_tokens(p->gen_tile_tokens[1], (long)T, (int)count, p->gen_wgs, true);
+  const double rounds = (double)(((T + tt - 1) / tt * count + p->gen_wgs - 1) / p->gen_wgs), walk = (double)((tt + 3) / 4 * 4);
+  const double generic =
+      rounds * (2.9 + 4.8e-4 * n + walk * (1.1e-4 * n + 2.9e-4 * m + 2.3e-5 * e + (factored ? 1.8e-4 * n : 0)));
+  const double slab = 8 + (factored ? 5 : 0) + 3.5e-3 * per_group + slabs * (5.4e-5 * n + 5.3e-5 * m + 8.3e-7 * e) +
+                      (ragged ? 0.08 * (double)count : 0);
+  return generic > slab;
+}
+
+// Whether a bf16 forward of `tokens` tokens (all adapters) on the generic kernels takes token-grouped tiles.
+// With no more than two tokens per CU a tile of one or two tokens walks sooner than a group of four, once
+// the two directly applied sides hold work enough: grouped / token-major 768 -> 2304 wide with 3,000 entries,
+// 16 tokens 7.5 / 6.9 us, 512 7.9 / 7.4; 2048 -> 2048 with 6,000 8.0 / 7.3; but 768 -> 768 with 2,000 5.5 / 5.7,
+// and factored frames, 2880 -> 2880 13.2 / 15.0.
+static int forward_g4(const ff_plan* p, int64_t tokens) {
+  const FrameDev &fi = p->fin->dev, &fo = p->fout->dev;
+  const bool few = fi.radix == 1 && fo.radix == 1 && fi.nblk * fi.W + fo.nblk * fo.W >= 2048 && tokens <= 2 * p->gen_wgs;
+  return few ? 0 : p->gen_g4;
 }
 
 hipError_t launch_fwd(const ff_plan* p, int bf16, int count, int T, ActPtrs X, int64_t ldx, const float* c,
                       const float* const* cs, float scale, float beta, ActPtrs Y, int64_t ldy, float* c_saved,
                       hipStream_t s) {
   if (bf16 && p->fast.enabled) return launch_fwd128(p, count, T, X, ldx, c, cs, scale, beta, Y, ldy, c_saved, s);
-  if (bf16 && slab_forward(p, (int64_t)T * count, T))
+  if (bf16 && slab_forward(p, T, count, false, p->nnz))
     return launch_fwd_slab(p, bf16, count, T, X, ldx, c, cs, scale, beta, Y, ldy, s);
   FwdArgs a{};
   a.fin = p->fin->dev;
   a.fout = p->fout->dev;
   a.T = T;
-  a.tt = call_tile_tokens(p->gen_tile_tokens[bf16], T, count, p->gen_wgs, false);
+  a.g4 = bf16 ? forward_g4(p, (int64_t)T * count) : 0;
+  a.tt = call_tile_tokens(p->gen_tile_tokens[bf16], T, count, p->gen_wgs, a.g4);
   a.ldt_in = p->gen_ldt_in[bf16];
   a.ldt_out = p->ldt_out[bf16];
   a.nch = p->gen_nch;
@@ -581,7 +616,7 @@ hipError_t launch_bwd(const ff_plan* p, int bf16, int count, int T, ActPtrs X, i
   a.fin = p->fin->dev;
   a.fout = p->fout->dev;
   a.T = T;
-  a.tt = call_tile_tokens(p->gen_tile_tokens[bf16], T, count, p->gen_wgs, bf16 && p->gen_g4);
+  a.tt = call_tile_tokens(p->gen_tile_tokens[bf16], T, count, p->gen_wgs, false);
   a.ldt_in = p->gen_ldt_in[bf16];
   a.ldt_out = p->ldt_out[bf16];
   a.ldb_in = p->ldb_in;
@@ -643,17 +678,15 @@ hipError_t launch_fwd_group(const ff_plan_group* g, int bf16, int T, const int* 
                             hipStream_t s) {
   const ff_plan* p = g->ref;
   if (bf16 && p->fast.enabled) return launch_fwd128_group(g, T, tokens, X, ldx, cs, scale, beta, Y, ldy, s);
-  // (per-adapter token counts are on the device: half of the most, on average)
-  if (bf16 && slab_forward(p, (int64_t)T * g->count / (tokens ? 2 : 1), T))
+  if (bf16 && slab_forward(p, T, g->count, tokens != nullptr, g->max_nnz))
     return launch_fwd_group_slab(g, bf16, T, tokens, X, ldx, cs, scale, beta, Y, ldy, s);
   const unsigned count = (unsigned)g->count;
   FwdArgs a{};
   a.fin = p->fin->dev;
   a.fout = p->fout->dev;
   a.T = T;
-  // (bf16 sizes by whole groups of four: 17 adapters 1152 -> 1664 wide of up to 418 tokens, 16 tokens a tile 18
-  // us, 14 31 us, 17 25 us)
-  a.tt = call_tile_tokens(p->gen_tile_tokens[bf16], T, (int)count, p->gen_wgs, bf16 && p->gen_g4);
+  a.g4 = bf16 ? forward_g4(p, (int64_t)T * count) : 0;
+  a.tt = call_tile_tokens(p->gen_tile_tokens[bf16], T, (int)count, p->gen_wgs, a.g4);
   a.ldt_in = p->gen_ldt_in[bf16];
   a.ldt_out = p->ldt_out[bf16];
   a.nch = p->gen_nch;
@@ -699,7 +732,7 @@ hipError_t launch_bwd_group(const ff_plan_group* g, int bf16, int T, const int* 
   a.fin = p->fin->dev;
   a.fout = p->fout->dev;
   a.T = T;
-  a.tt = call_tile_tokens(p->gen_tile_tokens[bf16], T, (int)count, p->gen_wgs, bf16 && p->gen_g4);
+  a.tt = call_tile_tokens(p->gen_tile_tokens[bf16], T, (int)count, p->gen_wgs, false);
   a.ldt_in = p->gen_ldt_in[bf16];
   a.ldt_out = p->ldt_out[bf16];
   a.ldb_in = p->ldb_in;

@@ -435,8 +435,7 @@ extern "C" ff_status ff_plan_create(const ff_frame* f_in, const ff_frame* f_out,
       }
     p->gen_nch = nch;
     for (int c = 0; c <= nch; ++c) p->gen_chunk_blk[c] = (int)((int64_t)c * FI.nblk / nch);
-    // bf16 tiles in whole groups of four tokens, where the slab kernels take the calls (the reported
-    // geometry, and the bound of ff_adapter_bwd_noalloc)
+    // bf16 tiles in whole groups of four tokens (gen_kernels.h); the geometry also bounds ff_adapter_bwd_noalloc
     p->gen_g4 = ff::slab_frame(FI) && ff::slab_frame(FO) && !f_in->lifted && !f_out->lifted && chunk_tokens(nch, FF_BF16) >= 4;
     for (int dt = 0; dt < 2; ++dt) {
       const int esz = dt == FF_BF16 ? 2 : 4;
