@@ -106,8 +106,11 @@ ff_status check_bwd(const ff_plan* p, int64_t T, int act, const void* X, int64_t
 // has its own copy of the array at its own address, taken once per device with
 // hipGetSymbolAddress; host code uses that address only, never the array's name.  Calls on one
 // device share the array, so overlapping calls on one device race.
-// Calls are accepted up to kScratchBytes (the generic kernels' need); the slab kernels split a call
-// so that its entries, dC partial rows and at least one source slab fit kScratchArray.
+// Calls are accepted up to kScratchBytes, the generic kernels' need: two or more times the stream's 4 bytes an
+// entry, so a support of at most 4.2 M entries.  The slab kernels' need then fits kScratchArray: their
+// stream is at most 1.5 times the support and 448 entries per group (slab_bundles), of 12 bytes with one
+// partial row (75 + 7 MB), or 8 bytes beside up to 40 MiB of partial rows of 20 MiB at most (42 + 42 MB),
+// and one slab of both sides is at most 10 MB.  They split a call to fit.
 constexpr size_t kScratchBytes = (size_t)32 << 20;
 constexpr size_t kScratchArray = (size_t)96 << 20;
 static __device__ __align__(256) unsigned char scratch[kScratchArray];

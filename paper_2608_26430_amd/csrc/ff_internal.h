@@ -166,7 +166,9 @@ struct FastPlanDev {
 // longest row (shorter rows padded with entries that read the source slab's row of zeros).  Each of
 // a workgroup's waves walks a contiguous run of the group's steps, a multiple of four; entry l of step
 // k of a batch of four is element 64 batch + 4 l + k.  Entry word: source position |
-// row in the group << kSlabDstShift | kRowLast at a bundle's last step.
+// row in the group << kSlabDstShift | (kRowLast | level << kSlabLevelShift) at a bundle's last step.
+// Rows of very different lengths: a bundle of level L holds 16 >> L rows, each in 2^L neighbouring entries
+// of a step, whose sums are added up at the bundle's end.
 constexpr int kSlabRowBytes = 128;      // one coefficient of one slab: 64 bf16 or 32 fp32 tokens
 constexpr int kSlabWaves = 4;
 constexpr int kSlabThreads = 64 * kSlabWaves;
@@ -174,6 +176,8 @@ constexpr int kSlabPadSteps = 16;       // readable steps past a stream's end
 constexpr uint32_t kSlabSrcMask = 0x1FFFFu;
 constexpr int kSlabDstShift = 17;
 constexpr uint32_t kSlabDstMask = 0x3FFu;
+constexpr int kSlabLevelShift = 27, kSlabMaxLevel = 4;
+constexpr uint32_t kSlabLevelMask = 0x7u << kSlabLevelShift;
 // Bytes of workspace a plan spends on slabs (all its adapters together): calls that need more are
 // split.  Half the 256 MB last-level cache, so that the second pass finds the first one's
 // results there beside the activations streaming through.

@@ -474,6 +474,16 @@ __device__ __forceinline__ float quad_sum(float x) {
   return x + quad_swap<2>(x);
 }
 
+// The end of a bundle whose rows are spread over several entries (`last`: its last entry word): the sums of
+// a row's entries, 2^level neighbouring quads, added up in all of them.
+template <int N>
+__device__ __forceinline__ void merge_quads(unsigned last, float (&acc)[N]) {
+  const int end = 4 << ((last & kSlabLevelMask) >> kSlabLevelShift);
+  for (int d = 4; d < end; d <<= 1)
+#pragma unroll
+    for (int t = 0; t < N; ++t) acc[t] += __shfl_xor(acc[t], d);
+}
+
 template <bool BF16>
 __device__ __forceinline__ void unpack16(u32x4v w, float (&x)[SlabT<BF16>::TC]) {
 #pragma unroll
@@ -561,8 +571,10 @@ __device__ __forceinline__ void slab_walk(const uint2* ent, int s0, int s1, cons
 #pragma unroll
           for (int t = 0; t < TC; ++t) acc[k * TC + t] = fmaf(cc, x[k][t], acc[k * TC + t]);
       }
-      if (__builtin_amdgcn_readfirstlane((int)b.w[i]) < 0) {   // the bundle's last step (uniform)
+      const int last = __builtin_amdgcn_readfirstlane((int)b.w[i]);
+      if (last < 0) {   // the bundle's last step (uniform)
         if constexpr (DX) {
+          if (last & kSlabLevelMask) merge_quads((unsigned)last, acc);
           *reinterpret_cast<u32x4v*>(tile + tile_at(row, 16 * c)) = pack16<BF16>(acc);
           *reinterpret_cast<u32x4v*>(tile + tile_at(row, 64 + 16 * c)) = pack16<BF16>(acc + TC);
 #pragma unroll

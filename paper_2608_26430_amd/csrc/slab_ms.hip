@@ -408,7 +408,9 @@ __device__ __forceinline__ void ms_walk(const uint2* ent, int s0, int s1, const 
         for (int k = 0; k < 2; ++k)
 #pragma unroll
           for (int t = 0; t < TC; ++t) acc[k * TC + t] = fmaf(cc, x[k][t], acc[k * TC + t]);
-        if (__builtin_amdgcn_readfirstlane((int)b.w[i]) < 0) {   // the bundle's last step (uniform)
+        const int last = __builtin_amdgcn_readfirstlane((int)b.w[i]);
+        if (last < 0) {   // the bundle's last step (uniform)
+          if (last & kSlabLevelMask) merge_quads((unsigned)last, acc);
           const unsigned row = (b.w[i] >> kSlabDstShift) & kSlabDstMask;
           if (row != dump) {
             unsigned char* p = dst + row * (unsigned)kSlabRowBytes + 16u * c;

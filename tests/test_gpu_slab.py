@@ -31,7 +31,7 @@ def _ok(name, got, ref, bound):
 # (n, rho_in, m, rho_out, nnz, T): 32-wide blocks; 8-wide ones, 24 x 8 rows a remainder of 64-row groups;
 # 344-wide factored ones on both sides, and with direct ones on either; several stages: 4^2 x 17 and
 # 4^2 x 20 (two stages), 4^3 x 17 (three), beyond the generic kernels' token counts; 16500 tokens: two slabs
-# per dC partial row
+# per dC partial row; and last, wide enough that the shortest forwards take the slab kernels too
 CASES = [(2048, 128, 2048, 128, 30000, t) for t in (1, 15, 63, 64, 65)] + [
     (520, 130, 1032, 258, 30000, 81),
     (2752, 16, 2752, 16, 30000, 70),
@@ -41,15 +41,35 @@ CASES = [(2048, 128, 2048, 128, 30000, t) for t in (1, 15, 63, 64, 65)] + [
     (640, 2, 640, 2, 900, 4449),
     (2176, 2, 2176, 2, 3000, 2561),
     (256, 16, 256, 16, 600, 16500),
-]
+] + [(2048, 128, 4096, 256, 60000, t) for t in (1, 15, 63, 64, 65)]
 
 
 @pytest.mark.parametrize("case", CASES, ids=lambda c: "n%d_m%d_nnz%d_T%d" % (c[0], c[2], c[4], c[5]))
 def test_slab_parity(dev, case):
     n, rn, m, rm, nnz, T = case
-    k_in, k_out, s = n // rn, m // rm, 0.173
     g = inputs.rng(n + 3 * m + T)
-    rows, cols = inputs.support(g, m, n, nnz)
+    _parity(dev, n, rn, m, rm, *inputs.support(g, m, n, nnz), T, g)
+
+
+# rows and columns of very different lengths, whose entries share a step among several lanes: blocks applied
+# directly, in one radix-4 stage and in two, on either side
+@pytest.mark.parametrize("case", [(520, 130, 1032, 258, 81), (2752, 16, 2048, 32, 65), (2048, 32, 2752, 16, 70),
+                                  (544, 2, 544, 2, 5009)], ids=lambda c: "n%d_m%d_T%d" % (c[0], c[2], c[4]))
+def test_slab_uneven_supports(dev, case):
+    n, rn, m, rm, T = case
+    g = inputs.rng(n + m)
+    C = np.zeros((m, n), dtype=bool)
+    C[:, :rn:8] = True          # a dense column in every fourth block (canonical order runs through the blocks)
+    C[1:rm:16] = True           # a dense row in every eighth
+    C[:, 1] = g.random(m) < 0.2
+    C[g.integers(0, m, 200), g.integers(0, n, 200)] = True
+    rows, cols = np.nonzero(C)
+    p = g.permutation(rows.size)
+    _parity(dev, n, rn, m, rm, rows[p].astype(np.int32), cols[p].astype(np.int32), T, g)
+
+
+def _parity(dev, n, rn, m, rm, rows, cols, T, g):
+    k_in, k_out, s, nnz = n // rn, m // rm, 0.173, rows.size
     vals = inputs.gaussian(g, (nnz,), std=0.02)
     X, G = inputs.gaussian(g, (T, n), dtype="bf16"), inputs.gaussian(g, (T, m), dtype="bf16")
     plan = ff.plan_create(ff.framegen(n, k_in, rn), ff.framegen(m, k_out, rm), rows, cols, max_tokens=T)

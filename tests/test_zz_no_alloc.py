@@ -65,6 +65,20 @@ def test_noalloc_matches_plain_backward(dev, case):
         assert torch.equal(ref, got), f"output {i} differs from ff_adapter_bwd"
 
 
+def test_noalloc_takes_uneven_supports(dev):
+    """Two dense columns in each block of a 16384 x 16384 support: accepted by its 13 MiB of coefficients and
+    partial sums, so it runs, however unevenly the entries lie."""
+    n = 16384
+    g = inputs.rng(9)
+    cols = np.arange(256)
+    rows = np.concatenate([g.choice(n, 6600, replace=False) for _ in cols]).astype(np.int32)
+    f = ff.framegen(n, 64, 256)
+    plan = ff.plan_create(f, f, rows, np.repeat(cols, 6600).astype(np.int32), max_tokens=4)
+    pairs = _call_pair(dev, plan, "bf16", 4, 3, 0.2, 0.5, True)
+    torch.cuda.synchronize()
+    assert all(torch.equal(ref, got) for ref, got in pairs)
+
+
 def test_noalloc_refuses_oversized_call(dev):
     n = m = 4096
     T = 16384
