@@ -131,8 +131,19 @@ void ff_frame_destroy(ff_frame* f);
  * entry streams, so that coefficient reads need no index.
  *   max_tokens  : largest T any later call will pass.
  *   max_batch   : largest `count` of later batched calls (>= 1).
- * Allocates all device workspace here.  Errors: FF_EINVAL (range, duplicate
- * entry, null pointer), FF_ENOMEM, FF_EDEVICE.  On error *out is NULL.
+ * Allocates all device workspace here (FF_Q_WORKSPACE_BYTES), whichever activation
+ * type the calls will have.  It belongs to one call at a time, and each plan
+ * holds its own: plans whose bf16 calls pass a side's coefficients through memory
+ * (all but those with FF_Q_FAST128 and those of frames with k rho != d) take 2
+ * bytes for every coefficient of the wider side (of both with frames in several
+ * radix-4 stages) and token of the longest call of max_batch adapters, up to 128
+ * MiB, beside the partial sums of dC.  An MLP projection 4096 <-> 11008 with
+ * 50,000 entries and 4096 tokens holds 104 MiB, a 28672 -> 8192 one with 200,000
+ * and 8192 tokens 211 MiB: let layers of one shape share a plan (max_batch, or
+ * calls one after the other) where their supports agree, and ask for no more
+ * tokens than are used where they do not.
+ * Errors: FF_EINVAL (range, duplicate entry, null pointer), FF_ENOMEM,
+ * FF_EDEVICE.  On error *out is NULL.
  */
 ff_status ff_plan_create(const ff_frame* f_in, const ff_frame* f_out, int64_t nnz,
                          const int32_t* rows, const int32_t* cols, int64_t max_tokens,

@@ -214,3 +214,26 @@ def test_factored_frames_keep_fp32_twiddles(dev, k, factored_input):
     close("dC", user_dc(plan, dC), u[rows] * z[cols])
     if factored_input:
         close("dX", to_np(dX[t]), synthesis(_bf16(vals * u[rows])))
+
+
+def test_plan_workspace_is_one_calls_scratch(dev):
+    """A plan holds the scratch of one call at a time: the generic kernels' partial rows (fp32, 256 rows of the
+    entry stream) and the slab kernels' slabs lie in the same memory.  A call of either kind then leaves nothing
+    that the other reads."""
+    n, m, T, nnz, s = 2048, 2752, 4096, 20000, 0.3
+    g = inputs.rng(31)
+    rows, cols = inputs.support(g, m, n, nnz)
+    plan = ff.plan_create(ff.framegen(n, 64, 32), ff.framegen(m, 172, 16), rows, cols, max_tokens=T)
+    slabs = (m + 1) * T * 2                                     # the wider side's coefficients
+    assert plan.query(2) < slabs + 64 * 4 * 1.8 * nnz + 80 * 1.8 * nnz   # + partial rows of 64 slabs + tables
+    c = plan_c(plan, inputs.gaussian(g, (nnz,), std=0.02), dev)
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(8)
+    X, G = (torch.randn((T, d), generator=gen, device=dev) for d in (n, m))
+    calls = [lambda dt=dt: (ff.adapter_fwd(plan, X.to(dt), c, s), *ff.adapter_bwd(plan, X.to(dt), G.to(dt), c, s))
+             for dt in (torch.float32, torch.bfloat16)]
+    first = [f() for f in calls]
+    again = [f() for f in calls[::-1]][::-1]
+    torch.cuda.synchronize()
+    for a, b in zip(first, again):
+        assert all(torch.equal(x, y) for x, y in zip(a, b))
