@@ -22,7 +22,7 @@ SOURCES = [("capi.cpp", "capi.cpp.o", []), ("framegen.cpp", "framegen.cpp.o", []
            ("optim.hip", "optim.hip.o", []), ("group.cpp", "group.cpp.o", []),
            ("lift.hip", "lift.hip.o", []), ("slab.hip", "slab.hip.o", []),
            ("slab_ms.hip", "slab_ms.hip.o", [])] + [
-    ("slab_inst.hip", f"slab_bf16_{r}.o", ["-DSLAB_BF16=1", f"-DSLAB_RADIX={int(r == 'radix')}"])
+    ("slab_inst.hip", f"slab_{r}.o", [f"-DSLAB_RADIX={int(r == 'radix')}"])
     for r in ("direct", "radix")] + [
     ("gen_inst.hip", f"gen_{d}_{t}{'_ms' if ms else ''}.o",
      [f"-DGEN_BWD={int(d == 'bwd')}", f"-DGEN_BF16={int(t == 'bf16')}", f"-DGEN_MS={ms}"])

@@ -169,11 +169,12 @@ struct FastPlanDev {
 // row in the group << kSlabDstShift | (kRowLast | level << kSlabLevelShift) at a bundle's last step.
 // Rows of very different lengths: a bundle of level L holds 16 >> L rows, each in 2^L neighbouring entries
 // of a step, whose sums are added up at the bundle's end.
-constexpr int kSlabRowBytes = 128;      // one coefficient of one slab: 64 bf16 or 32 fp32 tokens
+constexpr int kSlabTokens = 64;         // of a slab
+constexpr int kSlabRowBytes = 128;      // one coefficient of one slab, bf16
 constexpr int kSlabWaves = 4;
 constexpr int kSlabThreads = 64 * kSlabWaves;
 constexpr int kSlabPadSteps = 16;       // readable steps past a stream's end
-constexpr uint32_t kSlabSrcMask = 0x1FFFFu;
+constexpr uint32_t kSlabSrcMask = 0x1FFFFu;   // (both sides of an fp32 token fit LDS: at most 40,960 coefficients)
 constexpr int kSlabDstShift = 17;
 constexpr uint32_t kSlabDstMask = 0x3FFu;
 constexpr int kSlabLevelShift = 27, kSlabMaxLevel = 4;
@@ -419,19 +420,19 @@ hipError_t launch_bwd_lifted(const ff_plan* p, int bf16, int T, const void* X, i
                              const BwdScratch* ws = nullptr);
 hipError_t launch_merge_lifted(const ff_plan* p, const float* c, float scale, int w_bf16, float beta, void* W,
                                int64_t ldw, hipStream_t s);
-// Slab kernels (slab.hip): the calls of plans with slab.enabled, arguments as for launch_fwd / launch_bwd and
+// Slab kernels (slab.hip): the bf16 calls of plans with slab.enabled, arguments as for launch_fwd / launch_bwd and
 // the group calls.
 hipError_t configure_slab();
-hipError_t launch_fwd_slab(const ff_plan* p, int bf16, int count, int T, ActPtrs X, int64_t ldx, const float* c,
+hipError_t launch_fwd_slab(const ff_plan* p, int count, int T, ActPtrs X, int64_t ldx, const float* c,
                            const float* const* cs, float scale, float beta, ActPtrs Y, int64_t ldy, hipStream_t s);
-hipError_t launch_bwd_slab(const ff_plan* p, int bf16, int count, int T, ActPtrs X, int64_t ldx, ActPtrs G,
+hipError_t launch_bwd_slab(const ff_plan* p, int count, int T, ActPtrs X, int64_t ldx, ActPtrs G,
                            int64_t ldg, const float* c, const float* const* cs, float scale, float beta_dx, ActPtrs dX,
                            int64_t lddx, bool want_dx, int accumulate_dc, float* dC, float* const* dCs, bool want_dc,
                            hipStream_t s, const BwdScratch* ws);
-hipError_t launch_fwd_group_slab(const ff_plan_group* g, int bf16, int T, const int* tokens, const void* const* X,
+hipError_t launch_fwd_group_slab(const ff_plan_group* g, int T, const int* tokens, const void* const* X,
                                  int64_t ldx, const float* const* cs, float scale, float beta, void* const* Y,
                                  int64_t ldy, hipStream_t s);
-hipError_t launch_bwd_group_slab(const ff_plan_group* g, int bf16, int T, const int* tokens, const void* const* X,
+hipError_t launch_bwd_group_slab(const ff_plan_group* g, int T, const int* tokens, const void* const* X,
                                  int64_t ldx, const void* const* G, int64_t ldg, const float* const* cs, float scale,
                                  float beta_dx, void* const* dX, int64_t lddx, bool want_dx, int accumulate_dc,
                                  float* const* dCs, bool want_dc, hipStream_t s);

@@ -500,15 +500,15 @@ bool slab_backward(const ff_plan* p, int64_t tokens) {
 // 512 -> 6912 with 27,000, 64 tokens 15.0 / 10.8.  The slab kernels round an output once, the generic ones
 // also between the synthesis' two stages (error against float64 4.0e-3 / 4.3e-3), so their line lies at fewer
 // tokens than the times alone would put it.
-// Calls of more tokens than kSlabTokens run in the slab kernels whatever their number of adapters: the two sides
+// Calls of more tokens than kSlabCallTokens run in the slab kernels whatever their number of adapters: the two sides
 // are then close (8192 tokens: 512 -> 768 wide 14.2 / 15.0, 2048 -> 768 23.9 / 28.0, 2752 -> 1024 36.1 / 36.8, 4096 -> 8192
 // 129 / 90), and a batched call gives the bits of the single ones.
-constexpr int64_t kSlabTokens = 4096;
+constexpr int64_t kSlabCallTokens = 4096;
 bool slab_forward(const ff_plan* p, int64_t T, int64_t count, bool ragged, int64_t nnz) {
   if (!p->slab.enabled) return false;
   const double tokens = (double)T * (double)count / (ragged ? 2 : 1);
   if (multistage(p)) return p->gen_nch > 1 || tokens > (double)ms_tokens(p, 1800, 1.6e6);
-  if (!p->gen_g4 || p->gen_nch > 1 || T > kSlabTokens) return true;
+  if (!p->gen_g4 || p->gen_nch > 1 || T > kSlabCallTokens) return true;
   const double n = (double)p->fin->dv, m = (double)p->fout->dv, e = (double)nnz;
   const double per_group = e / p->slab.fwd.ngroups;
   const double slabs = (double)((T + 63) / 64) * (double)count / (ragged ? 2 : 1);
@@ -544,7 +544,7 @@ hipError_t launch_fwd(const ff_plan* p, int bf16, int count, int T, ActPtrs X, i
                       hipStream_t s) {
   if (bf16 && p->fast.enabled) return launch_fwd128(p, count, T, X, ldx, c, cs, scale, beta, Y, ldy, c_saved, s);
   if (bf16 && slab_forward(p, T, count, false, p->nnz))
-    return launch_fwd_slab(p, bf16, count, T, X, ldx, c, cs, scale, beta, Y, ldy, s);
+    return launch_fwd_slab(p, count, T, X, ldx, c, cs, scale, beta, Y, ldy, s);
   FwdArgs a{};
   a.fin = p->fin->dev;
   a.fout = p->fout->dev;
@@ -610,7 +610,7 @@ hipError_t launch_bwd(const ff_plan* p, int bf16, int count, int T, ActPtrs X, i
                          want_dc, c_saved, s, ws);
   if (ws && count != 1) return hipErrorInvalidValue;   // a caller's scratch serves one adapter
   if (bf16 && slab_backward(p, (int64_t)T * count))
-    return launch_bwd_slab(p, bf16, count, T, X, ldx, G, ldg, c, cs, scale, beta_dx, dX, lddx, want_dx, accumulate_dc,
+    return launch_bwd_slab(p, count, T, X, ldx, G, ldg, c, cs, scale, beta_dx, dX, lddx, want_dx, accumulate_dc,
                            dC, dCs, want_dc, s, ws);
   BwdArgs a{};
   a.fin = p->fin->dev;
@@ -679,7 +679,7 @@ hipError_t launch_fwd_group(const ff_plan_group* g, int bf16, int T, const int* 
   const ff_plan* p = g->ref;
   if (bf16 && p->fast.enabled) return launch_fwd128_group(g, T, tokens, X, ldx, cs, scale, beta, Y, ldy, s);
   if (bf16 && slab_forward(p, T, g->count, tokens != nullptr, g->max_nnz))
-    return launch_fwd_group_slab(g, bf16, T, tokens, X, ldx, cs, scale, beta, Y, ldy, s);
+    return launch_fwd_group_slab(g, T, tokens, X, ldx, cs, scale, beta, Y, ldy, s);
   const unsigned count = (unsigned)g->count;
   FwdArgs a{};
   a.fin = p->fin->dev;
@@ -725,7 +725,7 @@ hipError_t launch_bwd_group(const ff_plan_group* g, int bf16, int T, const int* 
     return launch_bwd128_group(g, T, tokens, X, ldx, G, ldg, cs, scale, beta_dx, dX, lddx, want_dx, accumulate_dc,
                                dCs, want_dc, s);
   if (bf16 && slab_backward(p, (int64_t)T * g->count / (tokens ? 2 : 1)))
-    return launch_bwd_group_slab(g, bf16, T, tokens, X, ldx, G, ldg, cs, scale, beta_dx, dX, lddx, want_dx,
+    return launch_bwd_group_slab(g, T, tokens, X, ldx, G, ldg, cs, scale, beta_dx, dX, lddx, want_dx,
                                  accumulate_dc, dCs, want_dc, s);
   const unsigned count = (unsigned)g->count;
   BwdArgs a{};

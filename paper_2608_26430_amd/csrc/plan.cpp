@@ -564,8 +564,7 @@ extern "C" ff_status ff_plan_create(const ff_frame* f_in, const ff_frame* f_out,
   // the slab kernels' streams (bf16 calls): rows of C into output positions, columns into input ones.
   const bool slab_ms = ff::slab_ms_frame(FI) || ff::slab_ms_frame(FO);
   const bool slab = (ff::slab_frame(FI) || ff::slab_ms_frame(FI)) && (ff::slab_frame(FO) || ff::slab_ms_frame(FO)) &&
-                    !f_in->lifted && !f_out->lifted && n < (int64_t)ff::kSlabSrcMask && m < (int64_t)ff::kSlabSrcMask &&
-                    !fast;
+                    !f_in->lifted && !f_out->lifted && !fast;
   SlabStreamHost sfwd, sbwd;
   if (slab) {
     // position of a coefficient: whole blocks in order, a factored block's columns in turn
@@ -580,7 +579,7 @@ extern "C" ff_status ff_plan_create(const ff_frame* f_in, const ff_frame* f_out,
       pos_in[e] = position(FI, cloc[e]);
       pos_out[e] = position(FO, rloc[e]);
     }
-    const int64_t slabs = (max_tokens + ff::kSlabRowBytes / 2 - 1) / (ff::kSlabRowBytes / 2) * max_batch;
+    const int64_t slabs = (max_tokens + ff::kSlabTokens - 1) / ff::kSlabTokens * max_batch;
     sfwd = build_slab_stream(pos_in, n, pos_out, FO, slabs);
     sbwd = build_slab_stream(pos_out, m, pos_in, FI, slabs);
   }
@@ -750,7 +749,7 @@ extern "C" ff_status ff_plan_create(const ff_frame* f_in, const ff_frame* f_out,
                                       (fast ? ff::fast128_partial_floats(b_st.size()) : 0));
   // slab kernels: dC partial rows (one per slab while they are few), the pool of source slabs
   // (every adapter's whole call, up to the bound; at least one slab) and the entries' copy
-  const int64_t slab_tokens = ff::kSlabRowBytes / 2, nslabs = std::max<int64_t>(1, (max_tokens + slab_tokens - 1) / slab_tokens);
+  const int64_t slab_tokens = ff::kSlabTokens, nslabs = std::max<int64_t>(1, (max_tokens + slab_tokens - 1) / slab_tokens);
   int slab_rows = 0;
   size_t slab_partial = 0, slab_pool = 0, slab_ent = 0;
   if (slab) {

@@ -9,11 +9,9 @@ namespace {
 
 using namespace slab;
 
-const SlabLaunch& kernels_for(const FrameDev& f) { return f.radix == 1 ? launch_bf16_direct() : launch_bf16_radix(); }
+const SlabLaunch& kernels_for(const FrameDev& f) { return f.radix == 1 ? launch_direct() : launch_radix(); }
 
 unsigned pad8(long n) { return (unsigned)((n + 7) / 8 * 8); }
-
-int slab_tokens(int bf16) { return kSlabRowBytes / (bf16 ? 2 : 4); }
 
 void record(hipEvent_t ev, hipStream_t s) {
   if (ev) (void)hipEventRecord(ev, s);
@@ -32,8 +30,8 @@ struct Lds {
   int stage;
   size_t bytes;
 };
-Lds lds_layout(const FrameDev& f, int nb, int bf16) {
-  const int rows = nb * f.W, S = slab_tokens(bf16), vl = bf16 ? 8 : 4, cb = rows / vl;
+Lds lds_layout(const FrameDev& f, int nb) {
+  const int rows = nb * f.W, S = Slab::S, vl = Slab::TC, cb = rows / vl;
   const int tile = (rows + 1) * kTileRow, stage = S * (cb | 1) * 16;
   if (f.radix == 1) return {tile, (size_t)(tile + stage)};
   const int windows = S * (4 * ((f.W2 + vl - 1) / vl) | 1) * 16;
@@ -49,7 +47,7 @@ void partial_rows(int T, int S, int rows, int* sg, int* nrows) {
 
 // First pass over `count` adapters: slabs slab0 .. slab0 + nslab - 1 of `side`; `entries` on the
 // launch that also writes the destination stream's entries.
-hipError_t launch_analysis(const Side& side, const SlabStream& st, int bf16, int count, int a0, int T, int slab0, int nslab,
+hipError_t launch_analysis(const Side& side, const SlabStream& st, int count, int a0, int T, int slab0, int nslab,
                            unsigned char* ws, long ws_adapter, uint2* ent, long ent_adapter, bool entries,
                            const float* c, const float* const* cs, const SlabDesc* group, const int* tokens, int bwd,
                            int max_ent, hipStream_t s) {
@@ -79,7 +77,7 @@ hipError_t launch_analysis(const Side& side, const SlabStream& st, int bf16, int
   a.bwd = bwd;
   const unsigned nprep = pad8((a.nent + threads - 1) / threads);
   if (ms) {
-    a.nwork = (int)pad8((long)nslab * (slab_tokens(bf16) / kMsTok) * f.nblk);
+    a.nwork = (int)pad8((long)nslab * (Slab::S / kMsTok) * f.nblk);
     return launch_ms_analysis(a, dim3((unsigned)a.nwork + nprep, (unsigned)count), s);
   }
   // groups of at most 128 rows (wider ones leave fewer workgroups to hide the latencies), several per
@@ -89,7 +87,7 @@ hipError_t launch_analysis(const Side& side, const SlabStream& st, int bf16, int
   a.gpw = (int)std::max<long>(1, std::min<long>(4, (long)nslab * a.ngroups * count / 2048));
   a.runs = (a.ngroups + a.gpw - 1) / a.gpw;
   a.nwork = (int)pad8((long)nslab * a.runs);
-  const Lds l = lds_layout(f, a.nb, bf16);
+  const Lds l = lds_layout(f, a.nb);
   a.stage_off = l.stage;
   return kernels_for(f).analysis(a, dim3((unsigned)a.nwork + nprep, (unsigned)count), l.bytes, s);
 }
@@ -110,7 +108,7 @@ struct Launch {
   unsigned grid;
   size_t lds;   // (0: multi-stage)
 };
-Launch pass_args(SlabArgs& a, const FrameDev& dst, const FrameDev& src, const SlabStream& st, int bf16, int T, int slab0,
+Launch pass_args(SlabArgs& a, const FrameDev& dst, const FrameDev& src, const SlabStream& st, int T, int slab0,
                  int nslab, int sg, int nb, int ngroups) {
   a.f = dst;
   a.fa = dst.wa16;
@@ -128,7 +126,7 @@ Launch pass_args(SlabArgs& a, const FrameDev& dst, const FrameDev& src, const Sl
   a.zrow = st.zrow;
   const unsigned grid = pad8((long)ngroups * a.nruns);
   if (slab_ms_frame(dst)) return {grid, 0};
-  const Lds l = lds_layout(dst, nb, bf16);
+  const Lds l = lds_layout(dst, nb);
   a.stage_off = l.stage;
   return {grid, l.bytes};
 }
@@ -146,7 +144,7 @@ hipError_t launch_pass(const SlabArgs& a, const Launch& l, bool bwd, bool dx, bo
   o.T = a.T;
   o.slab0 = a.slab0;
   o.nslab = a.nslab;
-  o.nwork = (int)pad8((long)a.nslab * (SlabT<true>::S / kMsTok) * a.f.nblk);
+  o.nwork = (int)pad8((long)a.nslab * (Slab::S / kMsTok) * a.f.nblk);
   o.ws = a.wd;
   o.ws_adapter = a.ws_adapter;
   o.Y = a.Y;
@@ -170,7 +168,7 @@ size_t call_bytes(const FrameDev& src, const FrameDev& dst) {
 
 hipError_t configure_slab() {
   hipError_t e = hipSuccess;
-  for (const SlabLaunch* l : {&launch_bf16_direct(), &launch_bf16_radix()}) {
+  for (const SlabLaunch* l : {&launch_direct(), &launch_radix()}) {
     const hipError_t r = l->configure();
     if (r != hipSuccess) e = r;
   }
@@ -178,11 +176,11 @@ hipError_t configure_slab() {
   return r != hipSuccess ? r : e;
 }
 
-hipError_t launch_fwd_slab(const ff_plan* p, int bf16, int count, int T, ActPtrs X, int64_t ldx, const float* c,
+hipError_t launch_fwd_slab(const ff_plan* p, int count, int T, ActPtrs X, int64_t ldx, const float* c,
                            const float* const* cs, float scale, float beta, ActPtrs Y, int64_t ldy, hipStream_t s) {
   hipEvent_t e0, e1;
   take_timing_events(&e0, &e1);
-  const int S = slab_tokens(bf16), nslab = (T + S - 1) / S;
+  const int S = Slab::S, nslab = (T + S - 1) / S;
   if (nslab == 0) return hipSuccess;
   const FrameDev &fi = p->fin->dev, &fo = p->fout->dev;
   const SlabStream& st = p->slab.fwd;
@@ -194,11 +192,11 @@ hipError_t launch_fwd_slab(const ff_plan* p, int bf16, int count, int T, ActPtrs
     for (int s0 = 0; s0 < nslab; s0 += sp.slabs) {
       const int na = std::min(sp.adapters, count - a0), ns = std::min(sp.slabs, nslab - s0);
       uint2* ent = p->slab.ent + (long)a0 * p->slab.ent_adapter;
-      hipError_t e = launch_analysis({&fi, X, ldx}, st, bf16, na, a0, T, s0, ns, p->slab.pool, ws_adapter, ent,
+      hipError_t e = launch_analysis({&fi, X, ldx}, st, na, a0, T, s0, ns, p->slab.pool, ws_adapter, ent,
                                      p->slab.ent_adapter, s0 == 0, c, cs, nullptr, nullptr, 0, 0, s);
       if (e != hipSuccess) return e;
       SlabArgs a{};
-      const Launch l = pass_args(a, fo, fi, st, bf16, T, s0, ns, 1, st.nb, st.ngroups);
+      const Launch l = pass_args(a, fo, fi, st, T, s0, ns, 1, st.nb, st.ngroups);
       a.ws = p->slab.pool;
       a.wd = p->slab.pool + (size_t)sp.slabs * side_bytes(fi);
       a.ws_adapter = ws_adapter;
@@ -216,13 +214,13 @@ hipError_t launch_fwd_slab(const ff_plan* p, int bf16, int count, int T, ActPtrs
   return hipGetLastError();
 }
 
-hipError_t launch_bwd_slab(const ff_plan* p, int bf16, int count, int T, ActPtrs X, int64_t ldx, ActPtrs G,
+hipError_t launch_bwd_slab(const ff_plan* p, int count, int T, ActPtrs X, int64_t ldx, ActPtrs G,
                            int64_t ldg, const float* c, const float* const* cs, float scale, float beta_dx, ActPtrs dX,
                            int64_t lddx, bool want_dx, int accumulate_dc, float* dC, float* const* dCs, bool want_dc,
                            hipStream_t s, const BwdScratch* ws) {
   hipEvent_t e0, e1;
   take_timing_events(&e0, &e1);
-  const int S = slab_tokens(bf16), nslab = (T + S - 1) / S;
+  const int S = Slab::S, nslab = (T + S - 1) / S;
   const FrameDev &fi = p->fin->dev, &fo = p->fout->dev;
   const SlabStream& st = p->slab.bwd;
   int sg = 1, nrows = 0;
@@ -253,17 +251,17 @@ hipError_t launch_bwd_slab(const ff_plan* p, int bf16, int count, int T, ActPtrs
       const int na = std::min(sp.adapters, count - a0), ns = std::min(sp.slabs, nslab - s0);
       uint2* ent = ents + (long)a0 * p->slab.ent_adapter;
       // a dC-only call reads no coefficients (its entries carry zeros)
-      hipError_t e = launch_analysis({&fo, G, ldg}, st, bf16, na, a0, T, s0, ns, pool, ws_adapter, ent, p->slab.ent_adapter,
+      hipError_t e = launch_analysis({&fo, G, ldg}, st, na, a0, T, s0, ns, pool, ws_adapter, ent, p->slab.ent_adapter,
                                      s0 == 0, want_dx ? c : nullptr, want_dx ? cs : nullptr, nullptr, nullptr, 1, 0, s);
       if (e != hipSuccess) return e;
       unsigned char* wd = pool + (size_t)sp.slabs * side_bytes(fo);
       if (want_dc && slab_ms_frame(fi)) {
-        e = launch_analysis({&fi, X, ldx}, st, bf16, na, a0, T, s0, ns, wd, ws_adapter, nullptr, 0, false, nullptr, nullptr,
+        e = launch_analysis({&fi, X, ldx}, st, na, a0, T, s0, ns, wd, ws_adapter, nullptr, 0, false, nullptr, nullptr,
                             nullptr, nullptr, 1, 0, s);
         if (e != hipSuccess) return e;
       }
       SlabArgs a{};
-      const Launch l = pass_args(a, fi, fo, st, bf16, T, s0, ns, sg, st.nb, st.ngroups);
+      const Launch l = pass_args(a, fi, fo, st, T, s0, ns, sg, st.nb, st.ngroups);
       a.ws = pool;
       a.wd = wd;
       a.ws_adapter = ws_adapter;
@@ -339,13 +337,13 @@ __global__ void __launch_bounds__(64 * kRedWaves) slab_reduce_group(const SlabDe
 
 }  // namespace
 
-hipError_t launch_fwd_group_slab(const ff_plan_group* g, int bf16, int T, const int* tokens, const void* const* X,
+hipError_t launch_fwd_group_slab(const ff_plan_group* g, int T, const int* tokens, const void* const* X,
                                  int64_t ldx, const float* const* cs, float scale, float beta, void* const* Y,
                                  int64_t ldy, hipStream_t s) {
   const ff_plan* p = g->ref;
   hipEvent_t e0, e1;
   take_timing_events(&e0, &e1);
-  const int S = slab_tokens(bf16), nslab = (T + S - 1) / S, count = (int)g->count;
+  const int S = Slab::S, nslab = (T + S - 1) / S, count = (int)g->count;
   if (nslab == 0) return hipSuccess;
   const FrameDev &fi = p->fin->dev, &fo = p->fout->dev;
   const SlabStream& st = p->slab.fwd;
@@ -354,11 +352,11 @@ hipError_t launch_fwd_group_slab(const ff_plan_group* g, int bf16, int T, const 
   record(e0, s);
   for (int s0 = 0; s0 < nslab; s0 += sp.slabs) {
     const int ns = std::min(sp.slabs, nslab - s0);
-    hipError_t e = launch_analysis({&fi, {nullptr, X}, ldx}, st, bf16, count, 0, T, s0, ns, nullptr, 0, nullptr, 0, s0 == 0,
+    hipError_t e = launch_analysis({&fi, {nullptr, X}, ldx}, st, count, 0, T, s0, ns, nullptr, 0, nullptr, 0, s0 == 0,
                                    nullptr, cs, g->slab, tokens, 0, g->max_slab_fwd, s);
     if (e != hipSuccess) return e;
     SlabArgs a{};
-    const Launch l = pass_args(a, fo, fi, st, bf16, T, s0, ns, 1, g->slab_nb_fwd, g->slab_groups_fwd);
+    const Launch l = pass_args(a, fo, fi, st, T, s0, ns, 1, g->slab_nb_fwd, g->slab_groups_fwd);
     a.ws_adapter = (long)((size_t)sp.slabs * side_bytes(fi));
     a.Ys = Y;
     a.ldy = (long)ldy;
@@ -373,14 +371,14 @@ hipError_t launch_fwd_group_slab(const ff_plan_group* g, int bf16, int T, const 
   return hipGetLastError();
 }
 
-hipError_t launch_bwd_group_slab(const ff_plan_group* g, int bf16, int T, const int* tokens, const void* const* X,
+hipError_t launch_bwd_group_slab(const ff_plan_group* g, int T, const int* tokens, const void* const* X,
                                  int64_t ldx, const void* const* G, int64_t ldg, const float* const* cs, float scale,
                                  float beta_dx, void* const* dX, int64_t lddx, bool want_dx, int accumulate_dc,
                                  float* const* dCs, bool want_dc, hipStream_t s) {
   const ff_plan* p = g->ref;
   hipEvent_t e0, e1;
   take_timing_events(&e0, &e1);
-  const int S = slab_tokens(bf16), nslab = (T + S - 1) / S, count = (int)g->count;
+  const int S = Slab::S, nslab = (T + S - 1) / S, count = (int)g->count;
   const FrameDev &fi = p->fin->dev, &fo = p->fout->dev;
   const SlabStream& st = p->slab.bwd;
   int sg = 1, nrows = 0;
@@ -390,17 +388,17 @@ hipError_t launch_bwd_group_slab(const ff_plan_group* g, int bf16, int T, const 
   record(e0, s);
   for (int s0 = 0; s0 < nslab; s0 += sp.slabs) {
     const int ns = std::min(sp.slabs, nslab - s0);
-    hipError_t e = launch_analysis({&fo, {nullptr, G}, ldg}, st, bf16, count, 0, T, s0, ns, nullptr, 0, nullptr, 0, s0 == 0,
+    hipError_t e = launch_analysis({&fo, {nullptr, G}, ldg}, st, count, 0, T, s0, ns, nullptr, 0, nullptr, 0, s0 == 0,
                                    nullptr, want_dx ? cs : nullptr, g->slab, tokens, 1, g->max_slab_bwd, s);
     if (e != hipSuccess) return e;
     const long wd = (long)((size_t)sp.slabs * side_bytes(fo));   // in each adapter's pool
     if (want_dc && slab_ms_frame(fi)) {
-      e = launch_analysis({&fi, {nullptr, X}, ldx}, st, bf16, count, 0, T, s0, ns, nullptr, wd, nullptr, 0, false, nullptr,
+      e = launch_analysis({&fi, {nullptr, X}, ldx}, st, count, 0, T, s0, ns, nullptr, wd, nullptr, 0, false, nullptr,
                           nullptr, g->slab, tokens, 1, 0, s);
       if (e != hipSuccess) return e;
     }
     SlabArgs a{};
-    const Launch l = pass_args(a, fi, fo, st, bf16, T, s0, ns, sg, g->slab_nb_bwd, g->slab_groups_bwd);
+    const Launch l = pass_args(a, fi, fo, st, T, s0, ns, sg, g->slab_nb_bwd, g->slab_groups_bwd);
     a.ws_adapter = wd;
     a.Xs = X;
     a.ldx = (long)ldx;

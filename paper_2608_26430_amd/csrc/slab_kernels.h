@@ -1,7 +1,7 @@
 // Slab kernels: forward and backward of the adapter in two passes through a coefficient-major
 // workspace, for frames whose blocks are applied directly (up to 128 wide) or in one radix-4 stage.
 //
-// A slab is S consecutive tokens (64 bf16, 32 fp32).  The workspace holds one side's coefficients
+// A slab is S = 64 consecutive tokens (bf16).  The workspace holds one side's coefficients
 // as [slab][coefficient position][S tokens]: 128 bytes, one cache line, per coefficient and slab,
 // plus one row of zeros per slab that padding entries read.  Position of block b's local
 // coefficient: b W + a' W2 + 2 l + s for frequency a' + 4 l of a factored block, b W + c of a
@@ -36,12 +36,11 @@ namespace slab {
 
 using namespace gen;
 
-template <bool BF16>
-struct SlabT {
-  static constexpr int ESZ = BF16 ? 2 : 4;
-  static constexpr int S = kSlabRowBytes / ESZ;   // tokens per slab
-  static constexpr int TC = 16 / ESZ;             // tokens per 16 bytes
-  static constexpr int NTG = S / 16;              // groups of 16 tokens (MFMA columns)
+struct Slab {
+  static constexpr int ESZ = 2;
+  static constexpr int S = kSlabTokens;   // tokens per slab
+  static constexpr int TC = 16 / ESZ;     // tokens per 16 bytes
+  static constexpr int NTG = S / 16;      // groups of 16 tokens (MFMA columns)
 };
 
 typedef short i16x4v __attribute__((ext_vector_type(4)));
@@ -100,12 +99,8 @@ __device__ __forceinline__ void stage_store(const unsigned char* stage, int nt, 
   }
 }
 
-template <bool BF16>
 __device__ __forceinline__ u32x4v pack16(const float* x) {
-  if constexpr (BF16)
-    return u32x4v{pk_bf2(x[0], x[1]), pk_bf2(x[2], x[3]), pk_bf2(x[4], x[5]), pk_bf2(x[6], x[7])};
-  else
-    return u32x4v{__float_as_uint(x[0]), __float_as_uint(x[1]), __float_as_uint(x[2]), __float_as_uint(x[3])};
+  return u32x4v{pk_bf2(x[0], x[1]), pk_bf2(x[2], x[3]), pk_bf2(x[4], x[5]), pk_bf2(x[6], x[7])};
 }
 
 // A value at a wave-uniform address that nothing writes while the kernel runs, through the scalar
@@ -139,9 +134,8 @@ struct Items {
 };
 
 // Most work items of a wave with factored blocks (whose matrices have at most KS KT rows).
-template <bool BF16>
 constexpr int radix_items(int KT) {
-  return (2 * (Mfma<BF16>::KS / 16) * KT + kSlabWaves - 1) / kSlabWaves;
+  return (2 * (Mfma<true>::KS / 16) * KT + kSlabWaves - 1) / kSlabWaves;
 }
 
 template <class V, int KT>
@@ -151,14 +145,10 @@ __device__ __forceinline__ void load_frags(const void* frag, int mt, int lane, V
 }
 
 // Four tokens (4 q .. + 3 of group tg) of one coefficient row into the tile.
-template <bool BF16>
 __device__ __forceinline__ void put_tokens(unsigned char* tile, int row, int tg, int q, f32x4 v) {
-  constexpr int ESZ = SlabT<BF16>::ESZ;
+  constexpr int ESZ = Slab::ESZ;
   unsigned char* p = tile + tile_at(row, (16 * tg + 4 * q) * ESZ);
-  if constexpr (BF16)
-    *reinterpret_cast<uint2*>(p) = Act<true>::pack4(v);
-  else
-    *reinterpret_cast<f32x4*>(p) = v;
+  *reinterpret_cast<uint2*>(p) = Act<true>::pack4(v);
 }
 
 // Coefficients of the staged token rows into the tile: z = P^T x for nb blocks.  MFMA with swapped
@@ -166,13 +156,13 @@ __device__ __forceinline__ void put_tokens(unsigned char* tile, int row, int tg,
 // Contraction windows are clamped to the column (element min(KS ks + VL q, W2 - VL) + j, repeated
 // elements having zero weights in `frag`), so that every read stays inside the block.
 // Directly applied blocks: stage and tile are different LDS.
-template <bool BF16, int KT>
+template <int KT>
 __device__ __forceinline__ void analysis_direct(const FrameDev& f, const void* frag, int have,
-                                                typename Mfma<BF16>::V (&fr)[KT], const unsigned char* stage, int cb,
+                                                Mfma<true>::V (&fr)[KT], const unsigned char* stage, int cb,
                                                 int nb, unsigned char* tile) {
-  using M = Mfma<BF16>;
-  using V = typename M::V;
-  constexpr int ESZ = SlabT<BF16>::ESZ, NTH = SlabT<BF16>::NTG / 2;
+  using M = Mfma<true>;
+  using V = M::V;
+  constexpr int ESZ = Slab::ESZ, NTH = Slab::NTG / 2;
   const int lane = phase_tid() & 63, q = lane >> 4, L = lane & 15, W = f.W, sb = stage_stride(cb);
   const Items items(f.MT, nb);
   for (int it = items.i0; it < items.i1; ++it) {
@@ -194,7 +184,7 @@ __device__ __forceinline__ void analysis_direct(const FrameDev& f, const void* f
     const int o = 16 * mt + L;
     if (o < W) {
 #pragma unroll
-      for (int g = 0; g < NTH; ++g) put_tokens<BF16>(tile, bl * W + o, NTH * th + g, q, acc[g]);
+      for (int g = 0; g < NTH; ++g) put_tokens(tile, bl * W + o, NTH * th + g, q, acc[g]);
     }
   }
 }
@@ -206,10 +196,9 @@ __device__ __forceinline__ void analysis_direct(const FrameDev& f, const void* f
 __device__ __forceinline__ int radix_windows(int W2, int VL) { return (W2 + VL - 1) / VL; }
 __device__ __forceinline__ int radix_stride(int nw) { return (4 * nw | 1) * 16; }
 
-template <bool BF16>
 __device__ __forceinline__ void radix_load(const FrameDev& f, const unsigned char* src, long ld, int nt,
                                            unsigned char* lds) {
-  using T = SlabT<BF16>;
+  using T = Slab;
   constexpr int VL = T::TC, NC = VL / 2, S = T::S, kU = 3;
   const int tid = phase_tid(), W2 = f.W2, nw = radix_windows(W2, VL), sb = radix_stride(nw);
   const float inv = 1.f / (float)nw;
@@ -245,13 +234,8 @@ __device__ __forceinline__ void radix_load(const FrameDev& f, const unsigned cha
         float2 v[4];
 #pragma unroll
         for (int a = 0; a < 4; ++a) {
-          if constexpr (BF16) {
-            const unsigned word = x[u][a][k];
-            v[a] = make_float2(__uint_as_float(word << 16), __uint_as_float(word & 0xffff0000u));
-          } else {
-            const unsigned re = x[u][a][2 * k], im = x[u][a][2 * k + 1];
-            v[a] = make_float2(__uint_as_float(re), __uint_as_float(im));
-          }
+          const unsigned word = x[u][a][k];
+          v[a] = make_float2(__uint_as_float(word << 16), __uint_as_float(word & 0xffff0000u));
         }
         const float2 s02 = cadd(v[0], v[2]), d02 = csub(v[0], v[2]);
         const float2 s13 = cadd(v[1], v[3]), d13 = csub(v[1], v[3]);
@@ -265,24 +249,23 @@ __device__ __forceinline__ void radix_load(const FrameDev& f, const unsigned cha
         }
       }
 #pragma unroll
-      for (int a = 0; a < 4; ++a) *reinterpret_cast<u32x4v*>(lds + t * sb + 16 * a * nw) = pack16<BF16>(y[a]);
+      for (int a = 0; a < 4; ++a) *reinterpret_cast<u32x4v*>(lds + t * sb + 16 * a * nw) = pack16(y[a]);
     }
   }
 }
 
 // The DFTs of size k/4 of the four columns.  The tile takes the windows' LDS, so the results wait in
 // registers until every wave has read its operands.
-template <bool BF16, int KT>
+template <int KT>
 __device__ __forceinline__ void analysis_radix(const FrameDev& f, const void* frag, unsigned char* lds) {
-  using M = Mfma<BF16>;
-  using V = typename M::V;
-  constexpr int NTH = SlabT<BF16>::NTG / 2, NI = radix_items<BF16>(KT);
-  using R = typename std::conditional<BF16, uint2, f32x4>::type;
+  using M = Mfma<true>;
+  using V = M::V;
+  constexpr int NTH = Slab::NTG / 2, NI = radix_items(KT);
   const int lane = phase_tid() & 63, q = lane >> 4, L = lane & 15, W2 = f.W2, nw = radix_windows(W2, M::VL),
             sb = radix_stride(nw);
   const Items items(f.MT, 1);
   V fr[KT];
-  R out[NI][NTH][4];
+  uint2 out[NI][NTH][4];
   int have = -1;
 #pragma unroll
   for (int n = 0; n < NI; ++n) {
@@ -311,10 +294,7 @@ __device__ __forceinline__ void analysis_radix(const FrameDev& f, const void* fr
     for (int g = 0; g < NTH; ++g)
 #pragma unroll
       for (int a = 0; a < 4; ++a) {
-        if constexpr (BF16)
-          out[n][g][a] = Act<true>::pack4(acc[g][a]);
-        else
-          out[n][g][a] = acc[g][a];
+        out[n][g][a] = Act<true>::pack4(acc[g][a]);
       }
     __builtin_amdgcn_sched_barrier(0);   // one item after the other (registers)
   }
@@ -331,32 +311,32 @@ __device__ __forceinline__ void analysis_radix(const FrameDev& f, const void* fr
     for (int g = 0; g < NTH; ++g)
 #pragma unroll
       for (int a = 0; a < 4; ++a)
-        *reinterpret_cast<R*>(lds + tile_at(a * W2 + o, (16 * (NTH * th + g) + 4 * q) * SlabT<BF16>::ESZ)) = out[n][g][a];
+        *reinterpret_cast<uint2*>(lds + tile_at(a * W2 + o, (16 * (NTH * th + g) + 4 * q) * Slab::ESZ)) = out[n][g][a];
   }
 }
 
 // Token rows of a group of blocks -> coefficients in the tile, with the barriers around them.  LDS:
 // the tile first; directly applied blocks' stage after it.
-template <bool BF16, int KT, bool RADIX>
+template <int KT, bool RADIX>
 __device__ __forceinline__ void group_analysis(const FrameDev& f, const void* frag, const unsigned char* rows, long ld,
                                                int nt, int nb, unsigned char* tile, unsigned char* stage) {
   if constexpr (RADIX) {
-    radix_load<BF16>(f, rows, ld, nt, stage);
+    radix_load(f, rows, ld, nt, stage);
     __syncthreads();
-    analysis_radix<BF16, KT>(f, frag, stage);
+    analysis_radix<KT>(f, frag, stage);
   } else {
-    const int cb = nb * f.W * SlabT<BF16>::ESZ / 16;
+    const int cb = nb * f.W * Slab::ESZ / 16;
     // the wave's first fragments travel with the rows
-    typename Mfma<BF16>::V fr[KT];
+    Mfma<true>::V fr[KT];
     const Items items(f.MT, nb);
     int mt = -1, bl, th;
     if (items.i0 < items.i1) {
       items.get(items.i0, mt, bl, th);
-      load_frags<typename Mfma<BF16>::V, KT>(frag, mt, phase_tid() & 63, fr);
+      load_frags<Mfma<true>::V, KT>(frag, mt, phase_tid() & 63, fr);
     }
-    stage_load<SlabT<BF16>::S>(rows, ld, nt, cb, stage);
+    stage_load<Slab::S>(rows, ld, nt, cb, stage);
     __syncthreads();
-    analysis_direct<BF16, KT>(f, frag, mt, fr, stage, cb, nb, tile);
+    analysis_direct<KT>(f, frag, mt, fr, stage, cb, nb, tile);
   }
   __syncthreads();
 }
@@ -417,9 +397,9 @@ __device__ __forceinline__ void copy_entry(const AnaArgs& a, int bi, int j) {
 // results wait in fp32), which bounds its registers.
 constexpr int slab_wgs(int KT, bool RADIX, bool BETA = false) { return RADIX && (KT >= 4 || BETA) ? 2 : 3; }
 
-template <bool BF16, int KT, bool RADIX>
+template <int KT, bool RADIX>
 __global__ void __launch_bounds__(kSlabThreads, slab_wgs(KT, RADIX)) slab_analysis(AnaArgs a) {
-  constexpr int S = SlabT<BF16>::S, ESZ = SlabT<BF16>::ESZ;
+  constexpr int S = Slab::S, ESZ = Slab::ESZ;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int bi = blockIdx.y;
   unsigned char* ws = a.ws + (long)bi * a.ws_adapter;
@@ -447,7 +427,7 @@ __global__ void __launch_bounds__(kSlabThreads, slab_wgs(KT, RADIX)) slab_analys
   for (int g = run * a.gpw; g < g1; ++g) {
     const int blk0 = g * a.nb, nb = min(a.nb, f.nblk - blk0);
     if (g > run * a.gpw) __syncthreads();   // the previous group's tile is copied
-    group_analysis<BF16, KT, RADIX>(f, a.frag, X + (long)blk0 * f.W * ESZ, a.ld * ESZ, nt, nb, smem,
+    group_analysis<KT, RADIX>(f, a.frag, X + (long)blk0 * f.W * ESZ, a.ld * ESZ, nt, nb, smem,
                                     smem + (RADIX ? 0 : a.stage_off));
     unsigned char* o = out + (long)blk0 * f.W * kSlabRowBytes;
     for (int i = phase_tid(); i < nb * f.W * 8; i += kSlabThreads)
@@ -484,30 +464,21 @@ __device__ __forceinline__ void merge_quads(unsigned last, float (&acc)[N]) {
     for (int t = 0; t < N; ++t) acc[t] += __shfl_xor(acc[t], d);
 }
 
-template <bool BF16>
-__device__ __forceinline__ void unpack16(u32x4v w, float (&x)[SlabT<BF16>::TC]) {
+__device__ __forceinline__ void unpack16(u32x4v w, float (&x)[Slab::TC]) {
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const unsigned v = w[i];
-    if constexpr (BF16) {
-      x[2 * i] = __uint_as_float(v << 16);
-      x[2 * i + 1] = __uint_as_float(v & 0xffff0000u);
-    } else {
-      x[i] = __uint_as_float(v);
-    }
+    x[2 * i] = __uint_as_float(v << 16);
+    x[2 * i + 1] = __uint_as_float(v & 0xffff0000u);
   }
 }
 
 // sum += products of two 16-byte pieces of tokens (bf16 pairs exactly, fp32 accumulation).
-template <bool BF16>
 __device__ __forceinline__ float dot16(u32x4v a, u32x4v b, float sum) {
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const unsigned x = a[i], y = b[i];
-    if constexpr (BF16)
-      sum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, x), __builtin_bit_cast(bf16x2_t, y), sum, false);
-    else
-      sum = fmaf(__uint_as_float(x), __uint_as_float(y), sum);
+    sum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, x), __builtin_bit_cast(bf16x2_t, y), sum, false);
   }
   return sum;
 }
@@ -521,10 +492,10 @@ __device__ __forceinline__ float dot16(u32x4v a, u32x4v b, float sum) {
 // Batches of four steps, stored so that lane (e, c) of one load holds entry e of step c: entries two
 // batches ahead, source rows one batch ahead.  Every batch is consumed whole on every path, so that
 // the waits are counted exactly.
-template <bool BF16, bool DX, bool DC>
+template <bool DX, bool DC>
 __device__ __forceinline__ void slab_walk(const uint2* ent, int s0, int s1, const unsigned char* src,
                                           unsigned char* tile, float* part, bool add) {
-  constexpr int TC = SlabT<BF16>::TC;
+  constexpr int TC = Slab::TC;
   if (s0 >= s1) return;
   const int lane = phase_tid() & 63, c = lane & 3;
   const uint2* ep = ent + lane;
@@ -558,13 +529,13 @@ __device__ __forceinline__ void slab_walk(const uint2* ent, int s0, int s1, cons
           z[1] = *reinterpret_cast<const u32x4v*>(tile + tile_at(row, 64 + 16 * c));
         }
         start = false;
-        const float d = quad_sum(dot16<BF16>(b.g[i][1], z[1], dot16<BF16>(b.g[i][0], z[0], 0.f)));
+        const float d = quad_sum(dot16(b.g[i][1], z[1], dot16(b.g[i][0], z[0], 0.f)));
         dcv = c == i ? d : dcv;
       }
       if constexpr (DX) {
         float x[2][TC];
-        unpack16<BF16>(b.g[i][0], x[0]);
-        unpack16<BF16>(b.g[i][1], x[1]);
+        unpack16(b.g[i][0], x[0]);
+        unpack16(b.g[i][1], x[1]);
         const float cc = __uint_as_float(b.c[i]);
 #pragma unroll
         for (int k = 0; k < 2; ++k)
@@ -575,8 +546,8 @@ __device__ __forceinline__ void slab_walk(const uint2* ent, int s0, int s1, cons
       if (last < 0) {   // the bundle's last step (uniform)
         if constexpr (DX) {
           if (last & kSlabLevelMask) merge_quads((unsigned)last, acc);
-          *reinterpret_cast<u32x4v*>(tile + tile_at(row, 16 * c)) = pack16<BF16>(acc);
-          *reinterpret_cast<u32x4v*>(tile + tile_at(row, 64 + 16 * c)) = pack16<BF16>(acc + TC);
+          *reinterpret_cast<u32x4v*>(tile + tile_at(row, 16 * c)) = pack16(acc);
+          *reinterpret_cast<u32x4v*>(tile + tile_at(row, 64 + 16 * c)) = pack16(acc + TC);
 #pragma unroll
           for (int t = 0; t < 2 * TC; ++t) acc[t] = 0.f;
         }
@@ -617,25 +588,17 @@ __device__ __forceinline__ void zero_rows(unsigned char* tile, const unsigned sh
 
 // The operand of 16 tokens tg of one column and contraction window (first row row0) from the tile:
 // lane (q, L) gets token L at the VL elements of its window.
-template <bool BF16>
-__device__ __forceinline__ typename Mfma<BF16>::V tile_operand(const unsigned char* tile, int row0, int tg, int L) {
-  if constexpr (BF16) {
-    unsigned w[4];
+__device__ __forceinline__ Mfma<true>::V tile_operand(const unsigned char* tile, int row0, int tg, int L) {
+  unsigned w[4];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const unsigned char* p = tile + tile_at(row0 + 4 * h + (L >> 2), 32 * tg + 8 * (L & 3));
-      const raw2 r = __builtin_bit_cast(raw2, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                                                  (__attribute__((address_space(3))) i16x4v*)(const_cast<unsigned char*>(p))));
-      w[2 * h] = r.x;
-      w[2 * h + 1] = r.y;
-    }
-    return __builtin_bit_cast(bf16x8, raw4{w[0], w[1], w[2], w[3]});
-  } else {
-    f32x4 v;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) v[j] = *reinterpret_cast<const float*>(tile + tile_at(row0 + j, 64 * tg + 4 * L));
-    return v;
+  for (int h = 0; h < 2; ++h) {
+    const unsigned char* p = tile + tile_at(row0 + 4 * h + (L >> 2), 32 * tg + 8 * (L & 3));
+    const raw2 r = __builtin_bit_cast(raw2, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                                                (__attribute__((address_space(3))) i16x4v*)(const_cast<unsigned char*>(p))));
+    w[2 * h] = r.x;
+    w[2 * h + 1] = r.y;
   }
+  return __builtin_bit_cast(bf16x8, raw4{w[0], w[1], w[2], w[3]});
 }
 
 // out = s P v (+ beta out) from the tile for one group of blocks of a slab, through the stage, where
@@ -644,14 +607,14 @@ __device__ __forceinline__ typename Mfma<BF16>::V tile_operand(const unsigned ch
 // columns leaves each lane with two complex coordinates of all four, which the radix-4 stage, twiddles
 // included, combines in registers in fp32; their stage takes the tile's LDS, so the results wait in registers until
 // every wave has read the tile.
-template <bool BF16, int KT, bool RADIX, bool BETA>
+template <int KT, bool RADIX, bool BETA>
 __device__ __forceinline__ void group_synthesis(const FrameDev& f, const void* frag, unsigned char* tile,
                                                 unsigned char* stage, int nb, int nt, unsigned char* dst, long ld,
                                                 float s, float beta) {
-  using M = Mfma<BF16>;
-  using V = typename M::V;
-  using A = Act<BF16>;
-  constexpr int ESZ = SlabT<BF16>::ESZ, S = SlabT<BF16>::S, NTH = SlabT<BF16>::NTG / 2;
+  using M = Mfma<true>;
+  using V = M::V;
+  using A = Act<true>;
+  constexpr int ESZ = Slab::ESZ, S = Slab::S, NTH = Slab::NTG / 2;
   const int lane = phase_tid() & 63, q = lane >> 4, L = lane & 15;
   const int W2 = f.W2, cb = nb * f.W * ESZ / 16, sb = stage_stride(cb);
   const Items items(f.MT, nb);
@@ -676,13 +639,13 @@ __device__ __forceinline__ void group_synthesis(const FrameDev& f, const void* f
         const int e = min(ks * M::KS + q * M::VL, W2 - M::VL);
 #pragma unroll
         for (int g = 0; g < NTH; ++g)
-          acc[g] = M::step(fr[ks], tile_operand<BF16>(tile, bl * W2 + e, NTH * th + g, L), acc[g]);
+          acc[g] = M::step(fr[ks], tile_operand(tile, bl * W2 + e, NTH * th + g, L), acc[g]);
       }
       const int o = 16 * mt + 4 * q;
       if (o < W2) {
 #pragma unroll
         for (int g = 0; g < NTH; ++g) {
-          auto* p = reinterpret_cast<typename A::E*>(stage + (16 * (NTH * th + g) + L) * sb) + bl * W2 + o;
+          auto* p = reinterpret_cast<A::E*>(stage + (16 * (NTH * th + g) + L) * sb) + bl * W2 + o;
           f32x4 v = acc[g] * s;
           if (BETA) v += beta * A::ld4(p);
           A::st4(p, v);
@@ -690,11 +653,11 @@ __device__ __forceinline__ void group_synthesis(const FrameDev& f, const void* f
       }
     }
   } else {
-    constexpr int NI = radix_items<BF16>(KT);
+    constexpr int NI = radix_items(KT);
     V fr[KT];
     float2 tw[2][3];   // of the lane's two complex coordinates
     // results as stored, or in fp32 until the old values are added
-    using O = typename std::conditional<BF16 && !BETA, unsigned, float2>::type;
+    using O = typename std::conditional<!BETA, unsigned, float2>::type;
     O out[NI][NTH][2][4];   // [item][token group][complex coordinate][a]
 #pragma unroll
     for (int n = 0; n < NI; ++n) {
@@ -722,7 +685,7 @@ __device__ __forceinline__ void group_synthesis(const FrameDev& f, const void* f
           const int e = min(ks * M::KS + q * M::VL, W2 - M::VL);
 #pragma unroll
           for (int a = 0; a < 4; ++a)
-            acc[a] = M::step(fr[ks], tile_operand<BF16>(tile, a * W2 + e, NTH * th + g, L), acc[a]);
+            acc[a] = M::step(fr[ks], tile_operand(tile, a * W2 + e, NTH * th + g, L), acc[a]);
         }
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
@@ -740,7 +703,7 @@ __device__ __forceinline__ void group_synthesis(const FrameDev& f, const void* f
           x[3] = make_float2(d02.x + d13.y, d02.y - d13.x);   // d02 - i d13
 #pragma unroll
           for (int a = 0; a < 4; ++a) {
-            if constexpr (BF16 && !BETA)
+            if constexpr (!BETA)
               out[n][g][u][a] = pk_bf2(s * x[a].x, s * x[a].y);
             else
               out[n][g][u][a] = make_float2(s * x[a].x, s * x[a].y);
@@ -770,10 +733,10 @@ __device__ __forceinline__ void group_synthesis(const FrameDev& f, const void* f
           if (16 * (NTH * th + g) >= nt) break;   // uniform
 #pragma unroll
           for (int a = 0; a < 4; ++a) {
-            auto* p = reinterpret_cast<typename A::E*>(stage + (16 * (NTH * th + g) + L) * sb) + a * W2 + o;
+            auto* p = reinterpret_cast<A::E*>(stage + (16 * (NTH * th + g) + L) * sb) + a * W2 + o;
             if constexpr (BETA) {
-              const float2 old = ld2<BF16>(p), v = out[n][g][u][a];
-              st2<BF16>(p, make_float2(fmaf(beta, old.x, v.x), fmaf(beta, old.y, v.y)));
+              const float2 old = ld2<true>(p), v = out[n][g][u][a];
+              st2<true>(p, make_float2(fmaf(beta, old.x, v.x), fmaf(beta, old.y, v.y)));
             } else {
               *reinterpret_cast<O*>(p) = out[n][g][u][a];
             }
@@ -817,9 +780,9 @@ struct SlabArgs {
   const int* tokens;
 };
 
-template <bool BF16, int KT, bool RADIX, bool BWD, bool DX, bool DC, bool BETA>
+template <int KT, bool RADIX, bool BWD, bool DX, bool DC, bool BETA>
 __device__ __forceinline__ void slab_pass(SlabArgs& a) {
-  constexpr int S = SlabT<BF16>::S, ESZ = SlabT<BF16>::ESZ;
+  constexpr int S = Slab::S, ESZ = Slab::ESZ;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int bi = blockIdx.y;
   const unsigned char* ws = a.ws + (long)bi * a.ws_adapter;
@@ -863,30 +826,30 @@ __device__ __forceinline__ void slab_pass(SlabArgs& a) {
     if (nt <= 0) break;   // uniform
     if (sl > sl0) __syncthreads();   // the previous slab's LDS reads are done
     if constexpr (DC)   // z of the group's blocks into the tile
-      group_analysis<BF16, KT, RADIX>(f, a.fa, X + t0 * a.ldx * ESZ, a.ldx * ESZ, nt, nb, smem, stage);
+      group_analysis<KT, RADIX>(f, a.fa, X + t0 * a.ldx * ESZ, a.ldx * ESZ, nt, nb, smem, stage);
     const unsigned char* src = ws + (long)(sl - a.slab0) * a.src_slab;
     int zfirst = 0;
     if ((!BWD || DX) && z0 + (int)(threadIdx.x >> 3) < z1) zfirst = (int)gload(a.zrow + z0 + (threadIdx.x >> 3));
-    slab_walk<BF16, !BWD || DX, DC>(ent, s0, s1, src, smem, DC ? part + (long)row * a.pstride : nullptr, sl != row * a.sg);
+    slab_walk<!BWD || DX, DC>(ent, s0, s1, src, smem, DC ? part + (long)row * a.pstride : nullptr, sl != row * a.sg);
     if constexpr (!BWD || DX) {
       zero_rows(smem, a.zrow + z0, z1 - z0, zfirst);
       __syncthreads();
-      group_synthesis<BF16, KT, RADIX, BETA>(f, a.fs, smem, stage, nb, nt, Y + t0 * a.ldy * ESZ, a.ldy * ESZ, a.scale, a.beta);
+      group_synthesis<KT, RADIX, BETA>(f, a.fs, smem, stage, nb, nt, Y + t0 * a.ldy * ESZ, a.ldy * ESZ, a.scale, a.beta);
     }
   }
 }
 
-template <bool BF16, int KT, bool RADIX, bool BETA>
+template <int KT, bool RADIX, bool BETA>
 __global__ void __launch_bounds__(kSlabThreads, slab_wgs(KT, RADIX, BETA)) slab_fwd(SlabArgs a) {
-  slab_pass<BF16, KT, RADIX, false, true, false, BETA>(a);
+  slab_pass<KT, RADIX, false, true, false, BETA>(a);
 }
 
-template <bool BF16, int KT, bool RADIX, bool DX, bool DC, bool BETA>
+template <int KT, bool RADIX, bool DX, bool DC, bool BETA>
 __global__ void __launch_bounds__(kSlabThreads, slab_wgs(KT, RADIX, BETA)) slab_bwd(SlabArgs a) {
-  slab_pass<BF16, KT, RADIX, true, DX, DC, BETA>(a);
+  slab_pass<KT, RADIX, true, DX, DC, BETA>(a);
 }
 
-// One activation type and frame kind (slab_inst.hip).
+// One frame kind (slab_inst.hip).
 struct SlabLaunch {
   hipError_t (*analysis)(const AnaArgs&, dim3 grid, size_t lds, hipStream_t s);
   hipError_t (*fwd)(const SlabArgs&, dim3 grid, size_t lds, hipStream_t s);
@@ -913,8 +876,8 @@ hipError_t launch_ms_synthesis(const MsOutArgs& a, dim3 grid, hipStream_t s);
 hipError_t launch_ms_pass(const SlabArgs& a, bool bwd, bool dx, bool dc, dim3 grid, hipStream_t s);
 hipError_t configure_ms();
 
-const SlabLaunch& launch_bf16_direct();
-const SlabLaunch& launch_bf16_radix();
+const SlabLaunch& launch_direct();
+const SlabLaunch& launch_radix();
 
 }  // namespace slab
 }  // namespace ff

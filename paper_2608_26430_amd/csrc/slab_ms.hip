@@ -181,7 +181,7 @@ __global__ void __launch_bounds__(kMsThreads, 2) ms_analysis(AnaArgs a) {
   }
   const FrameDev& f = a.f;
   const MsTile tile(xcd_item(blockIdx.x, a.nwork, bi), f.nblk);
-  const long ts = (long)(a.slab0 + tile.sl) * SlabT<true>::S, t0 = ts + kMsTok * tile.quarter;
+  const long ts = (long)(a.slab0 + tile.sl) * Slab::S, t0 = ts + kMsTok * tile.quarter;
   if (tile.sl >= a.nslab || ts >= T) return;   // uniform
   const int nt = (int)max(0L, min((long)kMsTok, T - t0));
   const int k2 = f.k2, W2 = f.W2, TS = ms_token_stride(k2), R = ms_region(k2), ncol = 1 << (2 * S);
@@ -272,7 +272,7 @@ __global__ void __launch_bounds__(kMsThreads, 2) ms_synthesis(MsOutArgs a) {
   }
   const FrameDev& f = a.f;
   const MsTile tile(xcd_item(blockIdx.x, a.nwork, bi), f.nblk);
-  const long t0 = (long)(a.slab0 + tile.sl) * SlabT<true>::S + kMsTok * tile.quarter;
+  const long t0 = (long)(a.slab0 + tile.sl) * Slab::S + kMsTok * tile.quarter;
   if (tile.sl >= a.nslab || t0 >= T) return;   // uniform
   const int nt = (int)min((long)kMsTok, T - t0);
   const int k2 = f.k2, W2 = f.W2, TS = ms_token_stride(k2), R = ms_region(k2), ncol = 1 << (2 * S);
@@ -364,7 +364,7 @@ __global__ void __launch_bounds__(kMsThreads, 2) ms_synthesis(MsOutArgs a) {
 template <bool DX, bool DC>
 __device__ __forceinline__ void ms_walk(const uint2* ent, int s0, int s1, const unsigned char* src, unsigned char* dst,
                                         const unsigned char* zero, unsigned dump, float* part, bool add) {
-  constexpr int TC = SlabT<true>::TC;
+  constexpr int TC = Slab::TC;
   if (s0 >= s1) return;
   const int lane = phase_tid() & 63, c = lane & 3;
   const uint2* ep = ent + lane;
@@ -396,13 +396,13 @@ __device__ __forceinline__ void ms_walk(const uint2* ent, int s0, int s1, const 
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       if constexpr (DC) {
-        const float d = quad_sum(dot16<true>(b.g[i][1], b.z[i][1], dot16<true>(b.g[i][0], b.z[i][0], 0.f)));
+        const float d = quad_sum(dot16(b.g[i][1], b.z[i][1], dot16(b.g[i][0], b.z[i][0], 0.f)));
         dcv = c == i ? d : dcv;
       }
       if constexpr (DX) {
         float x[2][TC];
-        unpack16<true>(b.g[i][0], x[0]);
-        unpack16<true>(b.g[i][1], x[1]);
+        unpack16(b.g[i][0], x[0]);
+        unpack16(b.g[i][1], x[1]);
         const float cc = __uint_as_float(b.c[i]);
 #pragma unroll
         for (int k = 0; k < 2; ++k)
@@ -414,8 +414,8 @@ __device__ __forceinline__ void ms_walk(const uint2* ent, int s0, int s1, const 
           const unsigned row = (b.w[i] >> kSlabDstShift) & kSlabDstMask;
           if (row != dump) {
             unsigned char* p = dst + row * (unsigned)kSlabRowBytes + 16u * c;
-            gstore(reinterpret_cast<u32x4v*>(p), pack16<true>(acc));
-            gstore(reinterpret_cast<u32x4v*>(p + 64), pack16<true>(acc + TC));
+            gstore(reinterpret_cast<u32x4v*>(p), pack16(acc));
+            gstore(reinterpret_cast<u32x4v*>(p + 64), pack16(acc + TC));
           }
 #pragma unroll
           for (int t = 0; t < 2 * TC; ++t) acc[t] = 0.f;
@@ -446,7 +446,7 @@ __device__ __forceinline__ void ms_walk(const uint2* ent, int s0, int s1, const 
 
 template <bool BWD, bool DX, bool DC>
 __global__ void __launch_bounds__(kSlabThreads, DC ? 2 : 3) ms_pass(SlabArgs a) {
-  constexpr int S = SlabT<true>::S;
+  constexpr int S = Slab::S;
   const int bi = blockIdx.y;
   const unsigned char* ws = a.ws + (long)bi * a.ws_adapter;
   unsigned char* wd = a.wd + (long)bi * a.ws_adapter;
