@@ -223,7 +223,7 @@ ff_status ff_adapter_bwd(const ff_plan* p, int64_t T, int act, const void* X, in
  * (bitwise those of ff_adapter_bwd) and errors are those of ff_adapter_bwd;
  * the backward's scratch (the coefficients in its own order, the dC partial
  * sums and, where the coefficients of a side pass through memory, those of some
- * tokens at a time) lives instead in an array that the library's code object
+ * tokens at a time) lives instead in a 96 MiB array that the library's code object
  * holds on every device it runs on, until the process ends.  Nothing is allocated
  * and no memset node is issued: the scratch is cleared by a fill kernel where
  * it must start at zero.
@@ -379,8 +379,11 @@ double ff_lr_linear_warmup(int64_t step, int64_t warmup, int64_t total, double b
  * ff_time_next_kernel -- instrumentation for benchmarks.  Arms this thread so
  * that the next hot-path call records the hipEvent_t `ev_start` just before and
  * `ev_stop` just after its main kernel (the fused forward, the fused backward,
- * or the merge), on that call's stream; the arming is then cleared.  Passing
- * NULL for both disarms.  Results are unaffected.
+ * or the merge), on that call's stream; the arming is then cleared.  Where a call
+ * passes a side's coefficients through memory, that is the launches from the first
+ * analysis to the last synthesis, two to four for every part that the call is split
+ * into.  The reordering of the coefficients and the reduction of dC lie outside.
+ * Passing NULL for both disarms.  Results are unaffected.
  */
 ff_status ff_time_next_kernel(void* ev_start, void* ev_stop);
 

@@ -261,10 +261,10 @@ def test_batched_matches_single_calls(dev, dtype):
 @pytest.mark.parametrize("shape", [(2752, 16, 1024, 16, 3000), (768, 64, 2304, 64, 3000)],
                          ids=["factored_in", "direct_vit"])
 def test_generic_backward_many_tiles_per_workgroup(dev, dtype, shape):
-    """The generic backward runs at most one workgroup per CU, looping over tiles: with several
+    """The generic backward (fp32) runs at most one workgroup per CU, looping over tiles: with several
     tiles per workgroup, a dX-only call (no dC rows to accumulate into), a dC-only call and a
-    call with both match the oracle, and dC is deterministic.  Shapes: a factored input frame,
-    and directly applied frames (token-grouped tiles in bf16)."""
+    call with both match the oracle, and dC is deterministic.  In bf16 the same calls run in the slab
+    kernels, over many slabs.  Shapes: a factored input frame, and directly applied frames."""
     n, rn, m, rm, nnz = shape
     f_in, f_out = ff.framegen(n, n // rn, rn), ff.framegen(m, m // rm, rm)
     g = inputs.rng(4242)
@@ -298,10 +298,8 @@ def test_generic_backward_many_tiles_per_workgroup(dev, dtype, shape):
 
 
 def test_grouped_tiles_several_walk_passes(dev):
-    """bf16 token-grouped tiles of more than 20 tokens, whose sparse walks take several passes (in
-    the backward the later passes add into the dC partial rows), with two tiles per backward
-    workgroup: a 256 x 256 layer at 30,720 tokens, for which a call takes 60-token tiles.  y and dX
-    on sampled tokens, dC over all tokens."""
+    """A 256 x 256 layer at 30,720 bf16 tokens, which run in the slab kernels: two slabs per dC partial row.  y and
+    dX on sampled tokens, dC over all tokens.  (The same plan's token-grouped tiles hold 60 tokens and more.)"""
     n = m = 256
     rn = 16
     nnz, T = 512, 30720
@@ -332,12 +330,34 @@ def test_grouped_tiles_several_walk_passes(dev):
     assert torch.equal(dC, dC2), "dC is not deterministic"
 
 
+def test_grouped_forward_several_walk_passes(dev):
+    """A batched bf16 forward on token-grouped tiles of more than 20 tokens, whose sparse walks take several
+    passes: eight 256 x 256 adapters of 3997 tokens, two rounds of 60-token tiles and a ragged last one."""
+    n, rn, nnz, T, count, s = 256, 16, 512, 3997, 8, 0.37
+    f = ff.framegen(n, n // rn, rn)
+    g = inputs.rng(7272)
+    rows, cols = inputs.support(g, n, n, nnz)
+    plan = ff.plan_create(f, f, rows, cols, max_tokens=T, max_batch=count)
+    assert plan.gen_token_groups and plan.gen_tile_tokens("bf16") >= 60
+    vals = [inputs.gaussian(g, (nnz,), std=0.02) for _ in range(count)]
+    X = [inputs.gaussian(g, (T, n), dtype="bf16") for _ in range(count)]
+    Xd = [torch_act(x, "bf16", dev) for x in X]
+    Yd = [torch.zeros_like(x) for x in Xd]
+    c = [plan_c(plan, v, dev) for v in vals]
+    ff.adapter_fwd_batched(plan, Xd, c, s, Yd)
+    torch.cuda.synchronize()
+    P = oracle_frame(n // rn, rn, n)
+    tok = np.unique(np.concatenate([_sample_tokens(T, 64, 13), np.arange(T - 70, T)]))
+    for x, v, y in zip(X, vals, Yd):
+        assert rel(to_np(y[tok]), O.adapter_fwd(P, P, rows, cols, v, s, x[tok])) <= TOL["bf16"]
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_generic_input_chunks(dev, dtype):
     """An input side too wide to sit whole next to the output side for 8 tokens (factored
-    256-wide blocks) and a dense enough support (nnz >= 4 (n + m)): the generic kernels take the
-    input side a chunk of blocks at a time.  The forward (v summed over chunks; also with beta)
-    matches the oracle; with several tiles per workgroup, a dX-only call, a dC-only call and a
+    256-wide blocks) and a dense enough support (nnz >= 4 (n + m)): the generic kernels (fp32) take the
+    input side a chunk of blocks at a time; bf16 calls run in the slab kernels.  The forward (v summed
+    over chunks; also with beta) matches the oracle; with several tiles per workgroup, a dX-only call, a dC-only call and a
     call with both match the oracle, dC is deterministic, and beta accumulates into dX."""
     n, rn, m, rm, nnz = 8192, 64, 2048, 64, 42000
     f_in, f_out = ff.framegen(n, n // rn, rn), ff.framegen(m, m // rm, rm)

@@ -1,8 +1,10 @@
 """The slab kernels (bf16: source side -> coefficient-major workspace -> destination side) at the sizes where
 they can go wrong: token counts around a slab of 64 and a group of 16, blocks applied directly, in one
 radix-4 stage and in several, on either side, groups with a remainder, several slabs per dC partial row, and
-calls split over the workspace.  Supports are dense enough, or calls long enough, that the dispatch takes
-these kernels in both directions.  Element-wise bounds against the oracle as in the other parity tests."""
+calls split over the workspace.  Backwards run here throughout (frames in several stages: past the generic
+kernels' token counts), forwards where the support is dense enough or the call long enough for the
+dispatch's line; the others cover the generic forward at the same sizes.  Element-wise bounds against the
+oracle as in the other parity tests."""
 import numpy as np
 import pytest
 
@@ -42,6 +44,12 @@ CASES = [(2048, 128, 2048, 128, 30000, t) for t in (1, 15, 63, 64, 65)] + [
     (2176, 2, 2176, 2, 3000, 2561),
     (256, 16, 256, 16, 600, 16500),
 ] + [(2048, 128, 4096, 256, 60000, t) for t in (1, 15, 63, 64, 65)]
+# the other shapes of the DFT of size k2 in two stages (k2 = 32, 36, 44, 52, 60) and in three (32), each just past
+# the generic kernels' token counts; two blocks in two stages; and a block in two stages with directly applied
+# and factored ones on the other side; and the longest calls that still run in the generic kernels
+STAGES = [(1024, 2, 1024, 2, 1500, 3401), (1024, 2, 1024, 2, 1500, 2271), (1152, 2, 1152, 2, 1500, 3217), (1408, 2, 1408, 2, 1500, 2961),
+          (1664, 2, 1664, 2, 1500, 2785), (1920, 2, 1920, 2, 1500, 2657), (4096, 2, 4096, 2, 3000, 2209),
+          (2176, 4, 2176, 4, 2000, 2561), (1152, 2, 768, 64, 1500, 3489), (688, 4, 1152, 2, 1500, 3569)]
 
 
 @pytest.mark.parametrize("case", CASES, ids=lambda c: "n%d_m%d_nnz%d_T%d" % (c[0], c[2], c[4], c[5]))
@@ -49,6 +57,14 @@ def test_slab_parity(dev, case):
     n, rn, m, rm, nnz, T = case
     g = inputs.rng(n + 3 * m + T)
     _parity(dev, n, rn, m, rm, *inputs.support(g, m, n, nnz), T, g)
+
+
+@pytest.mark.parametrize("case", STAGES, ids=lambda c: "n%d_m%d_nnz%d_T%d" % (c[0], c[2], c[4], c[5]))
+def test_slab_parity_several_stages(dev, case):
+    """As above; the tokens that are not compared are zero, so that the oracle's dC takes those alone."""
+    n, rn, m, rm, nnz, T = case
+    g = inputs.rng(n + 3 * m + T)
+    _parity(dev, n, rn, m, rm, *inputs.support(g, m, n, nnz), T, g, few=True)
 
 
 # rows and columns of very different lengths, whose entries share a step among several lanes: blocks applied
@@ -68,10 +84,17 @@ def test_slab_uneven_supports(dev, case):
     _parity(dev, n, rn, m, rm, rows[p].astype(np.int32), cols[p].astype(np.int32), T, g)
 
 
-def _parity(dev, n, rn, m, rm, rows, cols, T, g):
+def _parity(dev, n, rn, m, rm, rows, cols, T, g, few=False):
     k_in, k_out, s, nnz = n // rn, m // rm, 0.173, rows.size
     vals = inputs.gaussian(g, (nnz,), std=0.02)
     X, G = inputs.gaussian(g, (T, n), dtype="bf16"), inputs.gaussian(g, (T, m), dtype="bf16")
+    # rows are independent of one another: the edges of the calls' slabs and groups, and some between
+    e = 5 if few else 20
+    t = np.unique(np.concatenate([np.arange(min(T, e)), np.arange(max(0, T - e), T),
+                                  np.clip([47, 48, 63, 64, 127, 128], 0, T - 1), inputs.rng(T).integers(0, T, e)]))
+    if few:
+        zero = np.setdiff1d(np.arange(T), t)
+        X[zero] = G[zero] = 0
     plan = ff.plan_create(ff.framegen(n, k_in, rn), ff.framegen(m, k_out, rm), rows, cols, max_tokens=T)
     assert not plan.fast128
     _, Xd = guarded(T, n, n + 8, "bf16", dev, X)
@@ -87,9 +110,6 @@ def _parity(dev, n, rn, m, rm, rows, cols, T, g):
     torch.cuda.synchronize()
     assert guards_intact(ybuf, T, m, m + 8, "bf16") and guards_intact(dxbuf, T, n, n + 24, "bf16")
     P_in, P_out = oracle_frame(k_in, rn, n), oracle_frame(k_out, rm, m)
-    # rows are independent of one another: the edges of the calls' slabs and groups, and some between
-    t = np.unique(np.concatenate([np.arange(min(T, 20)), np.arange(max(0, T - 20), T),
-                                  np.clip([47, 48, 63, 64, 127, 128], 0, T - 1), inputs.rng(T).integers(0, T, 20)]))
     fb = FwdBounds(P_in, P_out, rows, cols, vals, s, X[t], "bf16", k_in, k_out)
     _ok("y", to_np(Y[t]), fb.y, fb.by)
     _ok("y coef", fb.coef(to_np(Y[t])), fb.v, fb.bv)
@@ -100,9 +120,55 @@ def _parity(dev, n, rn, m, rm, rows, cols, T, g):
     _ok("dX coef", bt.coef(to_np(dX[t])), bt.q, bt.bq)
     bbb = BwdBounds(P_in, P_out, rows, cols, vals, s, X[t], G[t], "bf16", k_in, k_out, beta_dx0=-1.5 * to_np(dX[t]))
     _ok("dX beta", to_np(dXb[t]), bbb.dx, bbb.bdx)
-    b = BwdBounds(P_in, P_out, rows, cols, vals, s, X, G, "bf16", k_in, k_out)
+    b = bt if few else BwdBounds(P_in, P_out, rows, cols, vals, s, X, G, "bf16", k_in, k_out)
     _ok("dC", user_dc(plan, dC), b.dc, b.bdc)
     assert torch.equal(dC, dC2), "dC is not deterministic"
+
+
+# frames, entries, the plans' max_tokens, tokens per adapter: adapters ending in different slabs (and groups of
+# blocks of different sizes, by max_tokens); several slabs per partial row (400,000 entries: 23 rows); a call
+# split over the smallest pool (36 slabs of the wide side); several stages
+GROUPS = [((2048, 128), (4096, 256), 20000, (400, 512, 4096, 400, 20000), (0, 5, 64, 65, 400)),
+          ((2752, 16), (2048, 32), 20000, (400, 500, 9000), (400, 129, 1)),
+          ((2048, 32), (2752, 16), 400000, (1700, 1700), (1700, 70)),
+          ((28672, 128), (256, 16), 30000, (2400, 2500), (1300, 2400)),
+          ((256, 16), (28672, 128), 30000, (2500, 2400), (2400, 1300)),
+          ((1024, 2), (1024, 2), 1500, (2600, 2600, 3000), (2600, 2491, 2599))]
+
+
+@pytest.mark.parametrize("ragged", [False, True], ids=["same_tokens", "per_adapter_tokens"])
+@pytest.mark.parametrize("case", GROUPS, ids=lambda c: "n%d_m%d_T%d" % (c[0][0], c[1][0], max(c[4])))
+def test_slab_groups(dev, case, ragged):
+    """Group calls against the single calls of each plan on the adapter's own tokens.  Each is within 4.5e-3 of the
+    exact result (one bf16 rounding per stage; dC: fp32 sums of rounded products), in the 2-norm."""
+    (n, rn), (m, rm), nnz, max_tokens, toks = case
+    T, count, s = min(max_tokens), len(toks), 0.3
+    toks = toks if ragged else (T,) * count
+    g = inputs.rng(n + m + nnz)
+    f_in, f_out = ff.framegen(n, n // rn, rn), ff.framegen(m, m // rm, rm)
+    plans = [ff.plan_create(f_in, f_out, *inputs.support(g, m, n, nnz), max_tokens=t) for t in max_tokens]
+    group = ff.plan_group(plans)
+    c = [plan_c(p, inputs.gaussian(g, (nnz,), std=0.02), dev) for p in plans]
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(9)
+    X, G = ([torch.randn((T, d), generator=gen, device=dev).bfloat16() for _ in plans] for d in (n, m))
+    Y, dX = ([torch.full((T, d), 7.0, device=dev, dtype=torch.bfloat16) for _ in plans] for d in (m, n))
+    dC = [torch.full((p.coef_slots,), float("nan"), device=dev) for p in plans]
+    tokens = torch.tensor(toks, dtype=torch.int32, device=dev) if ragged else None
+    ff.adapter_fwd_group(group, X, c, s, Y, tokens=tokens)
+    ff.adapter_bwd_group(group, X, G, c, s, dX, dC, tokens=tokens)
+    torch.cuda.synchronize()
+
+    def close(a, b):
+        d, r = (a.double() - b.double()).norm(), b.double().norm()
+        return bool(d <= 9e-3 * r)
+
+    for i, t in enumerate(toks):
+        assert torch.all(Y[i][t:] == 7) and torch.all(dX[i][t:] == 7), f"adapter {i}: written past its tokens"
+        y = ff.adapter_fwd(plans[i], X[i][:t], c[i], s)
+        dx, dc = ff.adapter_bwd(plans[i], X[i][:t], G[i][:t], c[i], s)
+        torch.cuda.synchronize()
+        assert close(Y[i][:t], y) and close(dX[i][:t], dx) and close(dC[i], dc), f"adapter {i}"
 
 
 @pytest.mark.parametrize("wide_in", [True, False], ids=["wide_input", "wide_output"])

@@ -3,8 +3,8 @@
 The no-allocation backward keeps its scratch in an array of the library's code object, shared by
 every call on the device and holding whatever the previous call left there.  Two calls in a row,
 the second on fewer tokens (so it reads a region the first one filled with other values), must
-give bitwise the results of the plain backward on the fused 128-wide kernels and on the generic
-ones; a call needing more scratch than the array holds is refused and writes nothing.
+give bitwise the results of the plain backward on the fused 128-wide kernels, the generic and the
+slab ones; a call needing more scratch than the array holds is refused and writes nothing.
 """
 import numpy as np
 import pytest
@@ -46,10 +46,12 @@ def _call_pair(dev, plan, dtype, T, seed, s, beta, acc):
 
 
 # (n, rho_in, m, rho_out, nnz, dtype, T first, T second): the fused 128-wide kernels at the
-# q_proj layer's full 4096 tokens, and the generic kernels (fp32; bf16 with factored blocks)
+# q_proj layer's full 4096 tokens, the generic kernels (fp32), the slab kernels (factored blocks), and a frame in
+# two stages, whose long calls run there and whose short ones run in the generic kernels
 CASES = [(4096, 64, 4096, 64, 10000, "bf16", 4096, 37),
          (256, 16, 512, 32, 700, "f32", 300, 9),
-         (2752, 16, 1024, 16, 4000, "bf16", 200, 3)]
+         (2752, 16, 1024, 16, 4000, "bf16", 200, 3),
+         (1024, 2, 1024, 2, 1500, "bf16", 2400, 70)]
 
 
 @pytest.mark.parametrize("case", CASES, ids=lambda c: "n%d_m%d_%s" % (c[0], c[2], c[5]))
