@@ -487,6 +487,26 @@ bool slab_backward(const ff_plan* p, int64_t tokens) {
   // other frames: always quicker there (256 -> 512 wide, 1 token: 15 -> 13 us; 2880 -> 2880: 29 -> 25)
   return p->gen_nch > 1 || !multistage(p) || tokens > ms_tokens(p, 1400, 0.9e6);
 }
+// Whether a bf16 forward of `tokens` tokens (all adapters) on the generic kernels takes token-grouped tiles, whose
+// walk serves whole groups of four.  Where the tokens of a CU leave two or three places of a group empty
+// (1, 2, 5 or 6 of them), token-major tiles are sooner done on directly applied sides that hold work
+// enough, grouped / token-major: 768 -> 2304 wide with 3,000 entries, 16 tokens 7.5 / 6.9 us, 512 7.9 / 7.4, 1500
+// 10.8 / 10.3 (with beta 12.8 / 11.8); 2048 -> 2048 with 6,000, 16 tokens 8.0 / 7.3; 8-wide blocks, 512 -> 512 with
+// 900, 180 tokens 5.7 / 5.1; on wider sides 3 tokens too, 3072 -> 6144 with 9,500, 730 tokens 13.8 / 12.8; but
+// 24-wide blocks, 768 -> 768 with 2,000, 64 tokens 5.5 / 5.7, and factored frames, 2880 -> 2880 with 14,000
+// 13.2 / 15.0.  A factored output side reads its old values token by token, four to a thread in a group:
+// 1024 -> 2752 with beta, 300 tokens 12.0 / 11.2.
+static int forward_g4(const ff_plan* p, int64_t tokens, bool beta) {
+  const FrameDev &fi = p->fin->dev, &fo = p->fout->dev;
+  const int64_t per_cu = (tokens + p->gen_wgs - 1) / p->gen_wgs;
+  const int width = fi.nblk * fi.W + fo.nblk * fo.W;
+  const bool gaps = (per_cu <= 6 && (per_cu - 1) % 4 < 2) || (per_cu == 3 && width >= 4000);
+  const bool work = width >= 1792 || fi.nblk + fo.nblk >= 128;
+  if (fi.radix == 1 && fo.radix == 1 && work && gaps) return 0;
+  if (fi.radix == 1 && fo.radix != 1 && beta && per_cu <= 2) return 0;
+  return p->gen_g4;
+}
+
 // Other frames, forward, by both sides' times in microseconds (generic on token-grouped tiles / slab).  T
 // tokens of each of `count` adapters with up to `nnz` entries each; ragged: the adapters' own numbers of
 // tokens are on the device, half of T on average.  The generic kernels' time goes with the rounds of
@@ -494,8 +514,8 @@ bool slab_backward(const ff_plan* p, int64_t tokens) {
 // Direct output blocks: 256 -> 512 wide with 700 entries, 64 tokens 5.1 / 7.6; 768 -> 2304 with 3,000, 64 tokens
 // 7.4 / 8.3, 4096 16.7 / 20.2, 8192 30.0 / 26.3; 2048 -> 768 with 4,000, 4096 tokens 12.9 / 16.9; 4096 -> 8192 with
 // 20,000, 16 tokens 16.5 / 9.1; 8960 -> 512 with 27,000, 64 tokens 16.5 / 17.8; 17 ragged adapters 1152 -> 1664
-// with 1,935 of up to 64 tokens 10.3 / 13.0, of up to 418 26.9 / 23.9.  The constants are fitted to 162 such
-// calls, whose choices are 0.2% off the better side on average.
+// with 1,935 of up to 64 tokens 10.3 / 13.0, of up to 418 26.9 / 23.9.  The constants are fitted to 391 such
+// calls, whose choices are 0.3% off the better side on average.
 // Factored output blocks: 2880 -> 2880 with 14,000, 1 token 12.1 / 15.1, 64 tokens 13.2 / 18.1, 4096 36.8 / 32.3;
 // 512 -> 6912 with 27,000, 64 tokens 15.0 / 10.8.  The slab kernels round an output once, the generic ones
 // also between the synthesis' two stages (error against float64 4.0e-3 / 4.3e-3), so their line lies at fewer
@@ -519,24 +539,16 @@ bool slab_forward(const ff_plan* p, int64_t T, int64_t count, bool ragged, int64
         (5.5 + 7e-4 * (n + m) + 4e-4 * e) * 1.3 * (T < 8 ? 0.7 : 1.0) * std::max(1.0, tokens / round);
     return generic + 0.3 > 9 + 4e-4 * (n + m) + per_group / 256 + 5.1e-5 * (n + m) * slabs;
   }
-  const int64_t tt = call_tile_tokens(p->gen_tile_tokens[1], (long)T, (int)count, p->gen_wgs, true);
-  const double rounds = (double)(((T + tt - 1) / tt * count + p->gen_wgs - 1) / p->gen_wgs), walk = (double)((tt + 3) / 4 * 4);
+  const bool g4 = forward_g4(p, T * count, false) != 0;
+  const int64_t tt = call_tile_tokens(p->gen_tile_tokens[1], (long)T, (int)count, p->gen_wgs, g4);
+  const double rounds = (double)(((T + tt - 1) / tt * count + p->gen_wgs - 1) / p->gen_wgs);
+  const double walk = (double)(g4 ? (tt + 3) / 4 * 4 : std::max<int64_t>(tt, 4));
   const double generic =
-      rounds * (2.9 + 4.8e-4 * n + walk * (1.1e-4 * n + 2.9e-4 * m + 2.3e-5 * e + (factored ? 1.8e-4 * n : 0)));
-  const double slab = 8 + (factored ? 5 : 0) + 3.5e-3 * per_group + slabs * (5.4e-5 * n + 5.3e-5 * m + 8.3e-7 * e) +
-                      (ragged ? 0.08 * (double)count : 0);
+      rounds * (2.7 + 6.4e-5 * n + 1.9e-4 * e +
+                walk * (0.12 + 9.5e-5 * n + 2.6e-4 * m + 1.6e-5 * e + (factored ? 1.4e-4 * n : 0)));
+  const double slab = 8.4 + 2.9e-5 * m + (factored ? 2.6 : 0) + 3.5e-3 * per_group +
+                      slabs * (4.5e-5 * n + 3.4e-5 * m + 5.5e-6 * e) + (ragged ? 0.37 * (double)count : 0);
   return generic > slab;
-}
-
-// Whether a bf16 forward of `tokens` tokens (all adapters) on the generic kernels takes token-grouped tiles.
-// With no more than two tokens per CU a tile of one or two tokens walks sooner than a group of four, once
-// the two directly applied sides hold work enough: grouped / token-major 768 -> 2304 wide with 3,000 entries,
-// 16 tokens 7.5 / 6.9 us, 512 7.9 / 7.4; 2048 -> 2048 with 6,000 8.0 / 7.3; but 768 -> 768 with 2,000 5.5 / 5.7,
-// and factored frames, 2880 -> 2880 13.2 / 15.0.
-static int forward_g4(const ff_plan* p, int64_t tokens) {
-  const FrameDev &fi = p->fin->dev, &fo = p->fout->dev;
-  const bool few = fi.radix == 1 && fo.radix == 1 && fi.nblk * fi.W + fo.nblk * fo.W >= 2048 && tokens <= 2 * p->gen_wgs;
-  return few ? 0 : p->gen_g4;
 }
 
 hipError_t launch_fwd(const ff_plan* p, int bf16, int count, int T, ActPtrs X, int64_t ldx, const float* c,
@@ -549,7 +561,7 @@ hipError_t launch_fwd(const ff_plan* p, int bf16, int count, int T, ActPtrs X, i
   a.fin = p->fin->dev;
   a.fout = p->fout->dev;
   a.T = T;
-  a.g4 = bf16 ? forward_g4(p, (int64_t)T * count) : 0;
+  a.g4 = bf16 ? forward_g4(p, (int64_t)T * count, beta != 0.f) : 0;
   a.tt = call_tile_tokens(p->gen_tile_tokens[bf16], T, count, p->gen_wgs, a.g4);
   a.ldt_in = p->gen_ldt_in[bf16];
   a.ldt_out = p->ldt_out[bf16];
@@ -685,7 +697,7 @@ hipError_t launch_fwd_group(const ff_plan_group* g, int bf16, int T, const int* 
   a.fin = p->fin->dev;
   a.fout = p->fout->dev;
   a.T = T;
-  a.g4 = bf16 ? forward_g4(p, (int64_t)T * count) : 0;
+  a.g4 = bf16 ? forward_g4(p, (int64_t)T * count, beta != 0.f) : 0;
   a.tt = call_tile_tokens(p->gen_tile_tokens[bf16], T, (int)count, p->gen_wgs, a.g4);
   a.ldt_in = p->gen_ldt_in[bf16];
   a.ldt_out = p->ldt_out[bf16];
